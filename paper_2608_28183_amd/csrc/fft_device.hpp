@@ -105,6 +105,39 @@ __device__ __forceinline__ void st_stream(float4* p, float4 v) {
   const nlos_f4 w = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(w, reinterpret_cast<nlos_f4*>(p));
 }
+
+// A buffer view of the bytes at a wave-uniform base: a load from kBufNone returns zero and a
+// store to it is dropped, both without memory traffic, so that a thread issues the same
+// accesses whether an element is wanted or not (no branch between loads in flight).
+// Offsets in bytes, below kBufMax.
+constexpr unsigned int kBufNone = 0xfffffff8u;
+constexpr long long kBufMax = 0xfffffff0LL;
+typedef unsigned int nlos_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned int nlos_u4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_view(const void* base) {
+  const unsigned long long b = reinterpret_cast<unsigned long long>(base);
+  const unsigned int lo = __builtin_amdgcn_readfirstlane((unsigned int)b);
+  const unsigned int hi = __builtin_amdgcn_readfirstlane((unsigned int)(b >> 32));
+  void* u = reinterpret_cast<void*>((unsigned long long)hi << 32 | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(u, 0, (unsigned int)kBufMax, 0x00020000);
+}
+// NT: non-temporal
+template <bool NT>
+__device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, unsigned int off) {
+  const nlos_u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, NT ? 2 : 0);
+  return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+template <bool NT>
+__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, unsigned int off, float2 v) {
+  __builtin_amdgcn_raw_buffer_store_b64(nlos_u2{__float_as_uint(v.x), __float_as_uint(v.y)}, r, off, 0, NT ? 2 : 0);
+}
+template <bool NT>
+__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, unsigned int off, float4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(
+      nlos_u4{__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)}, r, off, 0,
+      NT ? 2 : 0);
+}
+
 // multiply by -i (forward) or +i (inverse)
 template <bool INV>
 __device__ __forceinline__ float2 rot90(float2 a) {

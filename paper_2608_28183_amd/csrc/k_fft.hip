@@ -10,10 +10,13 @@
 #include "nlos_internal.hpp"
 #include "prec.hpp"
 
+#include <algorithm>
+
 namespace nlos {
 
 // NT: non-temporal loads and stores of the FP32 complex lines (the f-k volumes)
-template <int N, int E, int T_, bool INV, int LD, int ST, int SP = SP_F32, bool NT = false>
+// LIST: the tiles of a.items with their bounds (LD_C64 -> ST_C64)
+template <int N, int E, int T_, bool INV, int LD, int ST, int SP = SP_F32, bool NT = false, bool LIST = false>
 __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_fft(StridedArgs a,
                                                                               const float2* __restrict__ tw) {
   using C = StridedCfg<N, E, T_>;
@@ -25,12 +28,38 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_fft(S
   const int tid = threadIdx.x;
   const int c = tid % T;
   const int p = tid / T;
-  const long long plane = blockIdx.y;
-  const int col = blockIdx.x * T + c;
+  long long plane = blockIdx.y;
+  int col = blockIdx.x * T + c, lim = N / 2;
+  if constexpr (LIST) {
+    const uint2 e = a.items[blockIdx.x];
+    plane = item_plane(e);
+    lim = item_lim(e);
+    col = (int)e.y + c;
+  }
   const bool colok = col < a.ncols;
+  // index n within the item's bound on the signed index
+  auto within = [&](int n) { return !LIST || n <= lim || n >= N - lim; };
 
   float2 v[E_];
-  if constexpr (SP == SP_F32 || LD == LD_TAU_SCALED) {
+  if constexpr (LIST) {
+    constexpr int ES = SP == SP_F32 ? 8 : 4;
+    const __amdgpu_buffer_rsrc_t in = buf_view(static_cast<const char*>(a.in) + plane * a.in_plane * ES);
+    typename ST_::R raw[E_];
+    static_for<E_>([&](auto j_) {
+      constexpr int j = decltype(j_)::value;
+      const int n = stage_in_index<N, S::R0, E_>(p, j / S::R0, j % S::R0);
+      const bool want = colok && n < a.n_in && (!INV || within(n));
+      const unsigned int off = want ? ES * ((unsigned)n * (unsigned)a.in_line + (unsigned)col) : kBufNone;
+      if constexpr (SP == SP_F32) raw[j] = buf_ld<NT>(in, off);
+      else raw[j] = __builtin_amdgcn_raw_buffer_load_b32(in, off, 0, 2);
+    });
+    const int e = SP == SP_F16 ? -a.e_in[a.e_per_col && colok ? col : 0] : 0;
+#pragma unroll
+    for (int j = 0; j < E_; ++j) {
+      v[j] = ST_::cvt(raw[j]);
+      if constexpr (SP == SP_F16) v[j] = ldexp2(v[j], e);
+    }
+  } else if constexpr (SP == SP_F32 || LD == LD_TAU_SCALED) {
     static_for<E / S::R0>([&](auto b_) {
       static_for<S::R0>([&](auto r_) {
         constexpr int b = decltype(b_)::value, r = decltype(r_)::value;
@@ -70,7 +99,7 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_fft(S
   if constexpr (ST == ST_C64 && SP != SP_F32) {
     const int e = SP == SP_F16 ? a.e_out[a.e_per_col && colok ? col : 0] : 0;
     fft_run<S, INV, false>(v, p, lds, idx, tw, [&](int n, float2 val) {
-      if (colok && n < a.n_out)
+      if (colok && n < a.n_out && (INV || within(n)))
         ST_::st(static_cast<typename ST_::T*>(a.out), plane * a.out_plane + (long long)n * a.out_line + col,
                 SP == SP_F16 ? ldexp2(val, e) : val);
     });
@@ -78,7 +107,7 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_fft(S
   }
   auto store = [&](int n, float2 val) {
     if constexpr (ST == ST_C64 || ST == ST_C64_SCALED) {
-      if (colok && n < a.n_out)
+      if (colok && n < a.n_out && (INV || within(n)))
       {
         const float2 w = ST == ST_C64_SCALED ? cscale(val, a.oscale) : val;
         float2* dst = static_cast<float2*>(a.out) + plane * a.out_plane + (long long)n * a.out_line + col;
@@ -116,7 +145,7 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_fft(S
 // in for the tile's first column: it reads that column, computes the same values and
 // stores them to the same places, so every thread issues the same stores and the wait
 // for the prefetched loads leaves the item's stores in flight.
-template <int N, int E, int T_, bool INV, bool IN_HALF, bool OUT_HALF>
+template <int N, int E, int T_, bool INV, bool IN_HALF, bool OUT_HALF, bool NTI, bool NTO>
 __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_c64_stream(
     StridedArgs a, const float2* __restrict__ tw, int ntiles, int nitems) {
   using C = StridedCfg<N, E, T_>;
@@ -125,6 +154,7 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_c64_s
   constexpr int RL = S::NSTAGE == 1 ? S::R0 : (S::NSTAGE == 2 ? S::R1 : S::R2);  // last radix
   constexpr int NR = IN_HALF ? E_ / 2 : E_;  // nonzero inputs per thread
   static_assert(S::R0 == E_ && RL % 2 == 0, "first radix E, even last radix");
+  static_assert(INV ? !IN_HALF : !OUT_HALF, "the item's bound is on the full side");
   __shared__ float2 lds[C::LDS_ELEMS];
   const int tid = threadIdx.x;
   const int c = tid % T;
@@ -135,47 +165,66 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_c64_s
   // then count only that loop's own loads and stores
   __builtin_amdgcn_s_waitcnt(0);
 
-  // the thread's column and plane offset of item it (a column past the end: the tile's first)
-  auto column = [&](int it, int& plane) {
-    plane = (unsigned)it / (unsigned)ntiles;
-    const int col0 = (it - plane * ntiles) * T;
-    return col0 + c < a.ncols ? col0 + c : col0;
+  auto item = [&](int it) {
+    uint2 e;
+    if (a.items != nullptr) {
+      e = a.items[it];
+    } else {
+      const int plane = (unsigned)it / (unsigned)ntiles;
+      e = make_uint2((unsigned)plane | (unsigned)(N / 2) << 16, (unsigned)((it - plane * ntiles) * T));
+    }
+    return make_uint2(__builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y));
   };
+  // the thread's column of an item (a column past the end: the tile's first)
+  auto column = [&](uint2 e) { return (int)e.y + c < a.ncols ? (int)e.y + c : (int)e.y; };
   float2 raw[NR];  // elements p + r P, r < NR, of the column
-  auto fetch = [&](int it) {
-    int plane;
-    const int col = column(it, plane);
-    const float2* in = static_cast<const float2*>(a.in) + plane * a.in_plane + col + (long long)p * a.in_line;
+  auto fetch = [&](uint2 e) {
+    const __amdgpu_buffer_rsrc_t in =
+        buf_view(static_cast<const float2*>(a.in) + item_plane(e) * a.in_plane);
+    const int lim = item_lim(e);
+    const unsigned int off = 8u * (unsigned)(column(e) + p * (int)a.in_line);
     static_for<NR>([&](auto r_) {
       constexpr int r = decltype(r_)::value;
-      raw[r] = ld_stream(in + (long long)(r * P) * a.in_line);
+      const int n = p + r * P;
+      const bool want = !INV || n <= lim || n >= N - lim;
+      raw[r] = buf_ld<NTI>(in, want ? off + 8u * (unsigned)(r * P) * (unsigned)a.in_line : kBufNone);
     });
   };
   auto idx = [&](int n) { return n * C::LDS_W + c; };
+  // the current item, the next one (its samples load during the current one) and the one
+  // after that (its entry of the list)
   int it = blockIdx.x;
-  if (it < nitems) fetch(it);
+  const int step = gridDim.x;
+  uint2 cur = item(it < nitems ? it : 0), nxt = item(it + step < nitems ? it + step : 0);
+  if (it < nitems) fetch(cur);
   // the first item's samples are needed at once; waiting here also leaves the loop's
   // own waits free of the loads issued before it
   __builtin_amdgcn_s_waitcnt(0);
-  for (; it < nitems; it += gridDim.x) {
+  for (; it < nitems; it += step) {
     float2 v[E_];
 #pragma unroll
     for (int j = 0; j < NR; ++j) v[j] = raw[j];
 #pragma unroll
     for (int j = NR; j < E_; ++j) v[j] = make_float2(0.f, 0.f);
-    int plane;
-    const int col = column(it, plane);
-    if (it + (int)gridDim.x < nitems) fetch(it + gridDim.x);
+    const uint2 e = cur;
+    cur = nxt;
+    if (it + 2 * step < nitems) nxt = item(it + 2 * step);
+    if (it + step < nitems) fetch(cur);
 
     fft_stages<S, INV>(v, p, lds, idx, twr);
     // last stage: butterfly b of thread p holds outputs n = p + b P + r (N / RL); the
     // lower half is r < RL / 2
-    float2* out = static_cast<float2*>(a.out) + plane * a.out_plane + col;
+    const __amdgpu_buffer_rsrc_t out = buf_view(static_cast<float2*>(a.out) + item_plane(e) * a.out_plane);
+    const int lim = item_lim(e);
+    const unsigned int off = 8u * (unsigned)(column(e) + p * (int)a.out_line);
     static_for<E_ / RL>([&](auto b_) {
       static_for<RL>([&](auto r_) {
         constexpr int b = decltype(b_)::value, r = decltype(r_)::value;
-        if constexpr (!OUT_HALF || r < RL / 2)
-          st_stream(out + (long long)(p + b * P + r * (N / RL)) * a.out_line, v[b * RL + r]);
+        constexpr int dn = b * P + r * (N / RL);
+        if constexpr (!OUT_HALF || r < RL / 2) {
+          const bool want = INV || p + dn <= lim || p + dn >= N - lim;
+          buf_st<NTO>(out, want ? off + 8u * (unsigned)dn * (unsigned)a.out_line : kBufNone, v[b * RL + r]);
+        }
       });
     });
     __syncthreads();  // every read of this item's exchanges before the next item's writes
@@ -432,6 +481,14 @@ static hipError_t launch_strided_n(const StridedArgs& a, int nplanes, const floa
                                    hipStream_t s) {
   using C = StridedCfg<N, E, T>;
   dim3 grid((a.ncols + C::T - 1) / C::T, nplanes);
+  if constexpr (LD == LD_C64 && ST == ST_C64 && (NT || SP != SP_F32)) {
+    if (a.items != nullptr) {
+      hipLaunchKernelGGL((strided_fft<N, E, T, INV, LD, ST, SP, NT, true>), dim3((unsigned)a.nitems), dim3(C::THREADS),
+                         0, s, a, tw);
+      return hipGetLastError();
+    }
+  }
+  if (a.items != nullptr) return hipErrorInvalidValue;
   hipLaunchKernelGGL((strided_fft<N, E, T, INV, LD, ST, SP, NT>), grid, dim3(C::THREADS), 0, s, a, tw);
   return hipGetLastError();
 }
@@ -453,17 +510,25 @@ static hipError_t launch_strided_inv(int n, const StridedArgs& a, int nplanes, c
   }
 }
 
-template <int N, bool INV, bool IN_HALF, bool OUT_HALF>
-static hipError_t launch_strided_stream_n(const StridedArgs& a, int nplanes, const float2* tw, hipStream_t s) {
+template <int N, bool INV, bool IN_HALF, bool OUT_HALF, bool NTI, bool NTO>
+static hipError_t launch_strided_stream_nt(const StridedArgs& a, int nplanes, const float2* tw, hipStream_t s) {
   using Tn = StridedTune<N, INV, LD_C64, ST_C64, SP_F32>;
   using C = StridedCfg<N, Tn::E, Tn::T>;
   const int ntiles = (a.ncols + C::T - 1) / C::T;
-  const int nitems = ntiles * nplanes;
-  auto k = strided_c64_stream<N, Tn::E, Tn::T, INV, IN_HALF, OUT_HALF>;
-  const long long res = resident_blocks<strided_c64_stream<N, Tn::E, Tn::T, INV, IN_HALF, OUT_HALF>>(C::THREADS);
+  const int nitems = a.items != nullptr ? a.nitems : ntiles * nplanes;
+  auto k = strided_c64_stream<N, Tn::E, Tn::T, INV, IN_HALF, OUT_HALF, NTI, NTO>;
+  const long long res = resident_blocks<strided_c64_stream<N, Tn::E, Tn::T, INV, IN_HALF, OUT_HALF, NTI, NTO>>(C::THREADS);
   const long long nb = res > 0 && res < nitems ? res : nitems;
   hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(C::THREADS), 0, s, a, tw, ntiles, nitems);
   return hipGetLastError();
+}
+
+template <int N, bool INV, bool IN_HALF, bool OUT_HALF>
+static hipError_t launch_strided_stream_n(const StridedArgs& a, int nplanes, const float2* tw, hipStream_t s) {
+  // the combinations the f-k passes use: forward (in either way, out streaming), inverse (in
+  // streaming, out either way)
+  if (a.nt_in && a.nt_out) return launch_strided_stream_nt<N, INV, IN_HALF, OUT_HALF, true, true>(a, nplanes, tw, s);
+  return launch_strided_stream_nt<N, INV, IN_HALF, OUT_HALF, INV, !INV>(a, nplanes, tw, s);
 }
 
 // The streaming form of the FP32 f-k strided passes: forward with a zero-padded upper
@@ -476,6 +541,7 @@ static bool launch_strided_stream(int n, bool inverse, const StridedArgs& a, int
   const bool fwd_half = !inverse && 2 * a.n_in == n && a.n_out == n;
   const bool inv_half = inverse && a.n_in == n && 2 * a.n_out == n;
   if (!fwd_half && !inv_half) return false;
+  if (8 * (a.ncols + n * std::max(a.in_line, a.out_line)) > kBufMax) return false;  // buffer offsets
   switch (n) {
     case 256: err = inverse ? launch_strided_stream_n<256, true, false, true>(a, nplanes, tw, s)
                             : launch_strided_stream_n<256, false, true, false>(a, nplanes, tw, s); return true;
@@ -485,8 +551,28 @@ static bool launch_strided_stream(int n, bool inverse, const StridedArgs& a, int
   }
 }
 
+int strided_cols(int n, bool inverse, int sp) {
+  auto cols = [&](auto n_) {
+    constexpr int N = decltype(n_)::value;
+    if (sp == SP_F32) return inverse ? StridedTune<N, true, LD_C64, ST_C64, SP_F32>::T : StridedTune<N, false, LD_C64, ST_C64, SP_F32>::T;
+    return inverse ? StridedTune<N, true, LD_C64, ST_C64, SP_F16>::T : StridedTune<N, false, LD_C64, ST_C64, SP_F16>::T;
+  };
+  switch (n) {
+    case 8: return cols(std::integral_constant<int, 8>{});
+    case 16: return cols(std::integral_constant<int, 16>{});
+    case 32: return cols(std::integral_constant<int, 32>{});
+    case 64: return cols(std::integral_constant<int, 64>{});
+    case 128: return cols(std::integral_constant<int, 128>{});
+    case 256: return cols(std::integral_constant<int, 256>{});
+    case 512: return cols(std::integral_constant<int, 512>{});
+    case 1024: return cols(std::integral_constant<int, 1024>{});
+    default: return cols(std::integral_constant<int, 2048>{});
+  }
+}
+
 hipError_t launch_strided(int n, bool inverse, int ld, int st, const StridedArgs& a, int nplanes,
                           const float2* tw, hipStream_t s, int sp, bool stream) {
+  if (a.items != nullptr && (a.nitems <= 0 || ld != LD_C64 || st != ST_C64)) return hipErrorInvalidValue;
   hipError_t err = hipSuccess;
   if (stream && sp == SP_F32 && ld == LD_C64 && st == ST_C64 && launch_strided_stream(n, inverse, a, nplanes, tw, s, err))
     return err;

@@ -58,7 +58,7 @@ __global__ __launch_bounds__((StridedCfg<N, E, T>::THREADS)) void fk_xr2c(FkXArg
     using ST_ = Stor<SP>;
     typename ST_::T* out = static_cast<typename ST_::T*>(a.out) + y * a.out_plane + 2 * cc;
     const float h = SP == SP_F16 ? ldexpf(0.5f, *a.e_out) : 0.5f;
-    for (int k = p; k <= N / 2; k += P) {
+    for (int k = p; k <= a.kmax; k += P) {
       const float2 zk = lds[idx(k)];
       const float2 zm = lds[idx((N - k) & (N - 1))];
       ST_::st2(out, (long long)k * a.nt, make_float2(h * (zk.x + zm.x), h * (zk.y - zm.y)),
@@ -68,7 +68,7 @@ __global__ __launch_bounds__((StridedCfg<N, E, T>::THREADS)) void fk_xr2c(FkXArg
   }
   if (!colok) return;
   float4* out = reinterpret_cast<float4*>(static_cast<float2*>(a.out) + y * a.out_plane + 2 * cc);
-  for (int k = p; k <= N / 2; k += P) {
+  for (int k = p; k <= a.kmax; k += P) {
     const float2 zk = lds[idx(k)];
     const float2 zm = lds[idx((N - k) & (N - 1))];
     // A = (Z[k] + conj Z[-k]) / 2, B = (Z[k] - conj Z[-k]) / (2i)
@@ -164,7 +164,9 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair(Fk
   for (long long g = blockIdx.x; g < ngroups; g += gridDim.x) {
     const long long w = g * C::L + l;
     const bool ok = w < a.nwork;
-    const PairItem it = pair_item(ok ? w : 0, a.Mx, a.My);
+    const uint2 e = pair_entry(a, ok ? w : 0);
+    const PairItem it = pair_of(a, e);
+    const int nz = (int)e.y;
     const long long src = (long long)it.ky * a.in_row + (long long)it.kx * a.nt;
     float2 v[E];
     {
@@ -188,11 +190,11 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair(Fk
       } else {
         load_first_stage<S>(raw, p, a.nt, ok, ST_::zero(), [&](int n) { return ST_::raw(in, n); });
       }
-      const int e = SP == SP_F16 ? -*a.e_in : 0;
+      const int ei = SP == SP_F16 ? -*a.e_in : 0;
 #pragma unroll
       for (int j = 0; j < E; ++j) {
         v[j] = ST_::cvt(raw[j]);
-        if constexpr (SP == SP_F16) v[j] = ldexp2(v[j], e);
+        if constexpr (SP == SP_F16) v[j] = ldexp2(v[j], ei);
       }
       if constexpr (TSCALE) {  // separate instantiation: keeps the plain pass's registers
 #pragma unroll
@@ -223,7 +225,7 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair(Fk
     typename ST_::T* outp = static_cast<typename ST_::T*>(a.out);
     // a rolled loop keeps the register footprint (and so the occupancy) of the remap low
 #pragma unroll 2
-    for (int kz = p; kz < a.nt; kz += P) {
+    for (int kz = p; kz < nz; kz += P) {
       float2 xa, xb;
       stolt_pair_nat(kz, HALF, N, A, a.norm, my, xa, xb);
       if constexpr (SP == SP_F16) {
@@ -261,31 +263,38 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair_st
     wt2[k] = tw[(k % (R0 * R1)) * (1 + k / (R0 * R1)) * (kTwiddleN / N)];
   float2* my = lds + l * C::LSTRIDE;
   auto idx = [&](int n) { return swz(n); };
-  const long long ngroups = (a.nwork + L - 1) / L;
   const float2* in = static_cast<const float2*>(a.in);
   float2* outp = static_cast<float2*>(a.out);
 
-  PairItem nit;
+  // a wave holds one column; the list entries of the pair whose samples are loading and of
+  // the one after it sit in scalar registers
+  static_assert(P % 64 == 0, "whole waves per column");
+  const int lw = __builtin_amdgcn_readfirstlane(l);
+  const int nwork = (int)a.nwork, step = gridDim.x;
+  auto entry = [&](int g) { return pair_entry_uniform(a, g * L + lw < nwork ? g * L + lw : g * L); };
   float2 raw[E / 2];  // samples p + r P (r < E/2) of the column: its stored half
-  auto fetch = [&](long long g) {
-    const long long w = g * L + l;
-    nit = pair_item(w < a.nwork ? w : g * L, a.Mx, a.My);
-    const float2* col = in + (long long)nit.ky * a.in_row + (long long)nit.kx * a.nt;
+  auto fetch = [&](uint2 e) {
+    const float2* col = in + (long long)(e.x >> 16) * a.in_row + (long long)(e.x & 0xffffu) * a.nt;
     static_for<E / 2>([&](auto r_) {
       constexpr int r = decltype(r_)::value;
       raw[r] = ld_stream(col + p + r * P);
     });
   };
-  if ((long long)blockIdx.x < ngroups) fetch(blockIdx.x);
+  const int ngroups = (nwork + L - 1) / L;
+  int g = blockIdx.x;
+  uint2 cur = entry(g < ngroups ? g : 0), nxt = entry(g + step < ngroups ? g + step : 0);
+  if (g < ngroups) fetch(cur);
   __builtin_amdgcn_s_waitcnt(0);  // tables and the first group before the loop
-  for (long long g = blockIdx.x; g < ngroups; g += gridDim.x) {
-    const PairItem it = nit;
+  for (; g < ngroups; g += step) {
+    const uint2 e = cur;
     float2 v[E];
 #pragma unroll
     for (int j = 0; j < E / 2; ++j) v[j] = raw[j];
 #pragma unroll
     for (int j = E / 2; j < E; ++j) v[j] = make_float2(0.f, 0.f);
-    if (g + gridDim.x < ngroups) fetch(g + gridDim.x);
+    cur = nxt;
+    if (g + 2 * step < ngroups) nxt = entry(g + 2 * step);
+    if (g + step < ngroups) fetch(cur);
     __syncthreads();  // the previous item's LDS reads (and, first, the tables) are done
     // the spectrum in natural order (the line stride leaves room for the repeated bin 0)
     static_assert(C::LSTRIDE > N, "room for bin N");
@@ -294,20 +303,25 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair_st
       if (n == 0) my[N] = val;
     });
     __syncthreads();
+    const PairItem it = pair_of(a, e);
     const int kxs = it.kx < a.Mx / 2 ? it.kx : it.kx - a.Mx;
     const int kys = it.ky < a.My / 2 ? it.ky : it.ky - a.My;
     const double ax = a.sxk * kxs, ay = a.syk * kys;
     const double A = ax * ax + ay * ay;
     const bool mir = it.has_mirror;
-    float2* o1 = outp + (long long)it.ky * a.out_row + (long long)it.kx * a.nt;
-    float2* o2 = mir ? outp + (long long)it.ky2 * a.out_row + (long long)it.kx2 * a.nt : o1;
+    // the column's two output rows as buffers, kz >= nz dropped
+    const __amdgpu_buffer_rsrc_t o1 = buf_view(outp + (long long)it.ky * a.out_row + (long long)it.kx * a.nt);
+    const __amdgpu_buffer_rsrc_t o2 = buf_view(outp + (long long)(mir ? it.ky2 : it.ky) * a.out_row +
+                                               (long long)(mir ? it.kx2 : it.kx) * a.nt);
+    const int nz = (int)e.y;
 #pragma unroll
     for (int i = 0; i < HALF / P; ++i) {
       const int kz = p + i * P;
-      float2 xa, xb;
-      stolt_pair_nat(kz, HALF, N, A, a.norm, my, xa, xb);
-      o1[kz] = xa;
-      o2[kz] = mir ? xb : xa;
+      float2 xa = make_float2(0.f, 0.f), xb = xa;
+      if ((p & ~63) + i * P < nz) stolt_pair_nat(kz, HALF, N, A, a.norm, my, xa, xb);
+      const unsigned int off = kz < nz ? 8u * (unsigned)kz : kBufNone;
+      buf_st<false>(o1, off, xa);
+      buf_st<false>(o2, off, mir ? xb : xa);
     }
   }
 }
@@ -520,7 +534,7 @@ hipError_t launch_fk_scales(const float* tau, long long n, int nt, float* partia
 // for the tile's first pair: it reads it, computes the same values and stores them to the
 // same place, so every thread issues the same stores (the wait for the next item's loads
 // then leaves the item's stores in flight).  Same results as fk_xr2c<N, E, T, SP_F32>.
-template <int N, int E, int T, bool IN_HALF>
+template <int N, int E, int T, bool IN_HALF, bool NTO>
 __global__ __launch_bounds__((StridedCfg<N, E, T>::THREADS)) void fk_xr2c_stream(FkXArgs a,
                                                                                  const float2* __restrict__ tw,
                                                                                  int ntiles, int nitems) {
@@ -568,14 +582,16 @@ __global__ __launch_bounds__((StridedCfg<N, E, T>::THREADS)) void fk_xr2c_stream
     if (it + (int)gridDim.x < nitems) fetch(it + gridDim.x);
     fft_run<S, false, true>(v, p, lds, idx, twr, [&](int n, float2 val) { lds[idx(n)] = val; });
     __syncthreads();
-    float4* out = reinterpret_cast<float4*>(static_cast<float2*>(a.out) + (long long)y * a.out_plane + 2 * cc);
+    const __amdgpu_buffer_rsrc_t out = buf_view(static_cast<float2*>(a.out) + (long long)y * a.out_plane);
+    const unsigned int off = 16u * (unsigned)cc;
     // A = (Z[k] + conj Z[-k]) / 2, B = (Z[k] - conj Z[-k]) / (2i), k <= N/2: k = p + r P for
     // r < E/2, and k = N/2 on p = 0
     auto put = [&](int k) {
       const float2 zk = lds[idx(k)];
       const float2 zm = lds[idx((N - k) & (N - 1))];
-      st_stream(out + (long long)k * (a.nt / 2), make_float4(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y),
-                                                            0.5f * (zk.y + zm.y), 0.5f * (zm.x - zk.x)));
+      buf_st<NTO>(out, k <= a.kmax ? off + 8u * (unsigned)k * (unsigned)a.nt : kBufNone,
+                  make_float4(0.5f * (zk.x + zm.x), 0.5f * (zk.y - zm.y), 0.5f * (zk.y + zm.y),
+                              0.5f * (zm.x - zk.x)));
     };
     static_for<E_ / 2>([&](auto r_) { put(p + decltype(r_)::value * P); });
     if (p == 0) put(N / 2);
@@ -598,12 +614,14 @@ static hipError_t launch_xr2c_n(const FkXArgs& a, int ny, const float2* tw, hipS
   // (1024-point lines would need 235+ VGPRs in the streaming form: they keep fk_xr2c)
   if constexpr (SP == SP_F32 && (N == 256 || N == 512)) {
     const int ntiles = (a.nt / 2 + T - 1) / T;
-    if ((a.nx == N || 2 * a.nx == N) && ntiles > 0 && ny > 0 && (long long)ntiles * ny < (1LL << 30)) {
+    if ((a.nx == N || 2 * a.nx == N) && ntiles > 0 && ny > 0 && (long long)ntiles * ny < (1LL << 30) &&
+        8LL * (N / 2 + 2) * a.nt <= kBufMax) {
       const int nitems = ntiles * ny;
       const bool half = 2 * a.nx == N;
-      auto k = half ? fk_xr2c_stream<N, E, T, true> : fk_xr2c_stream<N, E, T, false>;
-      const long long res = half ? resident_blocks<fk_xr2c_stream<N, E, T, true>>(C::THREADS)
-                                 : resident_blocks<fk_xr2c_stream<N, E, T, false>>(C::THREADS);
+      auto k = half ? (a.nt_out ? fk_xr2c_stream<N, E, T, true, true> : fk_xr2c_stream<N, E, T, true, false>)
+                    : (a.nt_out ? fk_xr2c_stream<N, E, T, false, true> : fk_xr2c_stream<N, E, T, false, false>);
+      const long long res = half ? resident_blocks<fk_xr2c_stream<N, E, T, true, true>>(C::THREADS)
+                                 : resident_blocks<fk_xr2c_stream<N, E, T, false, true>>(C::THREADS);
       const long long nb = res > 0 && res < nitems ? res : nitems;
       hipLaunchKernelGGL(k, dim3((unsigned)nb), dim3(C::THREADS), 0, s, a, tw, ntiles, nitems);
       return hipGetLastError();
@@ -710,7 +728,8 @@ __global__ __launch_bounds__(512) void gen_column_pair(FkPairArgs a, GenPlan g, 
   for (long long grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {
     const long long w = grp * L + l;
     const bool ok = w < a.nwork;
-    const PairItem it = pair_item(ok ? w : 0, a.Mx, a.My);
+    const uint2 e = pair_entry(a, ok ? w : 0);
+    const PairItem it = pair_of(a, e);
     const float2* in = static_cast<const float2*>(a.in) + (long long)it.ky * a.in_row + (long long)it.kx * a.nt;
     float2 x[EMAX];  // all loads in flight before any LDS write (EMAX * P >= N)
     static_for<EMAX>([&](auto k_) {
@@ -734,7 +753,7 @@ __global__ __launch_bounds__(512) void gen_column_pair(FkPairArgs a, GenPlan g, 
     const long long dst = (long long)it.ky * a.out_row + (long long)it.kx * a.nt;
     const long long dst2 = (long long)it.ky2 * a.out_row + (long long)it.kx2 * a.nt;
     const bool ok2 = ok && it.has_mirror;
-    for (int kz = p; kz < a.nt; kz += P) {
+    for (int kz = p; kz < (int)e.y; kz += P) {
       float2 xa, xb;
       stolt_pair(
           kz, half, A, a.norm, [&](int i) { return my[i]; }, [&](int i) { return my[i == 0 ? 0 : N - i]; }, xa,

@@ -44,26 +44,40 @@ int ilog2i(int v) {
 // 64-byte row segments share 128-byte lines, and the second finds the lines in that L2.
 __device__ __forceinline__ int gen_tile() {
   const int b = blockIdx.x;
-  return (gridDim.x % 16 == 0) ? ((b & ~15) | ((b & 7) << 1) | ((b >> 3) & 1)) : b;
+  return b < (int)(gridDim.x & ~15u) ? ((b & ~15) | ((b & 7) << 1) | ((b >> 3) & 1)) : b;
 }
 
 
-template <int EMAX, bool INV, int ST>
+// LIST: the tiles of a.items with their bounds (ST_C64)
+template <int EMAX, bool INV, int ST, bool LIST>
 __global__ __launch_bounds__(kGenMaxThreads) void gen_strided(StridedArgs a, GenPlan g, int lt) {
   extern __shared__ float2 glds[];
   const int n = g.n, T = 1 << lt, P = blockDim.x >> lt;
   const int tid = threadIdx.x;
   const int c = tid & (T - 1), p = tid >> lt;
-  const long long plane = blockIdx.y;
-  const int col = gen_tile() * T + c;
+  long long plane = blockIdx.y;
+  int col = gen_tile() * T + c, lim = n / 2;
+  if constexpr (LIST) {
+    const uint2 e = a.items[gen_tile()];
+    plane = item_plane(e);
+    lim = item_lim(e);
+    col = (int)e.y + c;
+  }
   const bool colok = col < a.ncols;
+  auto within = [&](int i) { return !LIST || i <= lim || i >= n - lim; };
   const float2* in = static_cast<const float2*>(a.in) + plane * a.in_plane + (colok ? col : 0);
+  const __amdgpu_buffer_rsrc_t inb = buf_view(static_cast<const float2*>(a.in) + plane * a.in_plane);
   // samples i = p + k P (k < EMAX cover the line): all loads in flight before any LDS write
   float2 x[EMAX];
   static_for<EMAX>([&](auto k_) {
     constexpr int k = decltype(k_)::value;
     const int i = p + k * P;
-    x[k] = (colok && i < a.n_in) ? in[(long long)i * a.in_line] : make_float2(0.f, 0.f);
+    if constexpr (LIST) {
+      const bool want = colok && i < a.n_in && (!INV || within(i));
+      x[k] = buf_ld<false>(inb, want ? 8u * ((unsigned)i * (unsigned)a.in_line + (unsigned)col) : kBufNone);
+    } else {
+      x[k] = (colok && i < a.n_in) ? in[(long long)i * a.in_line] : make_float2(0.f, 0.f);
+    }
   });
   static_for<EMAX>([&](auto k_) {
     constexpr int k = decltype(k_)::value;
@@ -76,7 +90,7 @@ __global__ __launch_bounds__(kGenMaxThreads) void gen_strided(StridedArgs a, Gen
   gen_fft<EMAX, INV>(glds + c, T, g, twl, p, P);
   static_for<EMAX>([&](auto k_) {
     const int i = p + decltype(k_)::value * P;
-    if (i >= a.n_out) return;
+    if (i >= a.n_out || (!INV && !within(i))) return;
     const float2 v = glds[i * T + c];
     if constexpr (ST == ST_C64 || ST == ST_C64_SCALED) {
       if (colok)
@@ -205,7 +219,7 @@ __global__ __launch_bounds__(kGenMaxThreads) void gen_xr2c(FkXArgs a, GenPlan g,
   gen_fft<EMAX, false>(glds + c, T, g, twl, p, P);
   if (!colok) return;
   float2* out = static_cast<float2*>(a.out) + y * a.out_plane + t0;
-  for (int k = p; k <= n / 2; k += P) {
+  for (int k = p; k <= a.kmax; k += P) {
     const float2 zk = glds[k * T + c];
     const float2 zm = glds[(k == 0 ? 0 : n - k) * T + c];
     // A = (Z[k] + conj Z[-k]) / 2, B = (Z[k] - conj Z[-k]) / (2i)
@@ -253,7 +267,15 @@ hipError_t gen_strided_st(const GenPlan& g, const StridedArgs& a, int nplanes, h
   const int T = gen_cols(g.n), P = gen_line_threads(g.n);
   const dim3 grid((a.ncols + T - 1) / T, nplanes);
   const size_t lds = (size_t)g.n * (T + 1) * sizeof(float2);
-  hipLaunchKernelGGL((gen_strided<kGenE, INV, ST>), grid, dim3(T * P), lds, s, a, g, ilog2i(T));
+  if (a.items != nullptr) {
+    if constexpr (ST == ST_C64)
+      hipLaunchKernelGGL((gen_strided<kGenE, INV, ST, true>), dim3((unsigned)a.nitems), dim3(T * P), lds, s, a, g,
+                         ilog2i(T));
+    else
+      return hipErrorInvalidValue;
+  } else {
+    hipLaunchKernelGGL((gen_strided<kGenE, INV, ST, false>), grid, dim3(T * P), lds, s, a, g, ilog2i(T));
+  }
   return hipGetLastError();
 }
 
@@ -279,9 +301,11 @@ hipError_t gen_contig_st(const GenPlan& g, const ContigArgs& a, hipStream_t s) {
 
 }  // namespace
 
+int gen_strided_cols(int n) { return gen_cols(n); }
+
 hipError_t launch_gen_strided(const GenPlan& g, bool inverse, int st, const StridedArgs& a, int nplanes,
                               hipStream_t s) {
-  if (a.ncols <= 0 || nplanes <= 0 || a.n_out > g.n) return hipErrorInvalidValue;
+  if (a.ncols <= 0 || nplanes <= 0 || a.n_out > g.n || (a.items != nullptr && a.nitems <= 0)) return hipErrorInvalidValue;
   switch (st) {
     case ST_C64: return inverse ? gen_strided_st<true, ST_C64>(g, a, nplanes, s)
                                 : gen_strided_st<false, ST_C64>(g, a, nplanes, s);

@@ -48,7 +48,8 @@ constexpr int kMfW = 8;    // waves per block
 // One tile (32 columns of one plane) per block.  The inputs n_in and outputs n_out are N
 // or N/2 (zero padding, crop) and the column count a multiple of 32 (checked on the host),
 // so no load or store needs a guard.
-template <int N, bool INV, int SP>
+// LIST: the tiles of a.items with their bounds.
+template <int N, bool INV, int SP, bool LIST>
 __global__ __launch_bounds__(64 * kMfW) void strided_fft_mfma(StridedArgs a, const mf_u4* __restrict__ t1,
                                                               const mf_u4* __restrict__ t3,
                                                               const float2* __restrict__ tw, int tiles_x) {
@@ -61,8 +62,15 @@ __global__ __launch_bounds__(64 * kMfW) void strided_fft_mfma(StridedArgs a, con
   __shared__ float2 twl[N];                // W_N^m
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int col = lane & 31, hl = lane >> 5;
-  const long long plane = blockIdx.x / tiles_x;
-  const int c0 = (blockIdx.x % tiles_x) * kMfT;
+  long long plane = blockIdx.x / tiles_x;
+  int c0 = (blockIdx.x % tiles_x) * kMfT, lim = N / 2;
+  if constexpr (LIST) {
+    const uint2 e = a.items[blockIdx.x];
+    plane = item_plane(e);
+    lim = item_lim(e);
+    c0 = (int)e.y;
+  }
+  auto within = [&](int n) { return !LIST || n <= lim || n >= N - lim; };
   for (int m = threadIdx.x; m < N; m += 64 * kMfW) twl[m] = tw[m * (kTwiddleN / N)];
   // inputs n2 >= 8 (n >= N/2) are all zero padding when n_in = N/2: one K step
   const bool upper = a.n_in > N / 2;
@@ -70,6 +78,7 @@ __global__ __launch_bounds__(64 * kMfW) void strided_fft_mfma(StridedArgs a, con
   // of the offset is (4 N1 hl) rows + its column, the rest is uniform
   const unsigned int* in = static_cast<const unsigned int*>(a.in) + plane * a.in_plane + c0;
   const long long lin = (long long)(4 * N1 * hl) * a.in_line + col;
+  const __amdgpu_buffer_rsrc_t inv = buf_view(in);
   unsigned int raw[IT1][2][4];
 #pragma unroll
   for (int it = 0; it < IT1; ++it)
@@ -77,8 +86,15 @@ __global__ __launch_bounds__(64 * kMfW) void strided_fft_mfma(StridedArgs a, con
     for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const unsigned int* row = in + (long long)((wv + kMfW * it) + N1 * (8 * q + r)) * a.in_line;
-        raw[it][q][r] = (q == 0 || upper) ? ld_u32_nt(row + lin) : 0u;
+        const int n = (wv + kMfW * it) + N1 * (8 * q + r);
+        const unsigned int* row = in + (long long)n * a.in_line;
+        if constexpr (INV && LIST) {  // beyond the item's bound zero, without a branch
+          const bool want = (q == 0 || upper) && within(n + 4 * N1 * hl);
+          raw[it][q][r] = __builtin_amdgcn_raw_buffer_load_b32(
+              inv, want ? 4u * ((unsigned)n * (unsigned)a.in_line + (unsigned)lin) : kBufNone, 0, 2);
+        } else {
+          raw[it][q][r] = (q == 0 || upper) ? ld_u32_nt(row + lin) : 0u;
+        }
       }
   const mf_u4 A1[2] = {t1[lane], t1[64 + lane]};
   mf_u4 A3[MB3][KS3];
@@ -123,7 +139,7 @@ __global__ __launch_bounds__(64 * kMfW) void strided_fft_mfma(StridedArgs a, con
       for (int j = 0; j < 8; ++j) {
         // n = k2 + N2 (16 b + (j < 4 ? 0 : 8) + (j & 3)) + N2 4 hl
         const int nu = k2 + N2 * (16 * b + (j < 4 ? 0 : 8) + (j & 3));
-        if (nu + N2 * 4 * hl < a.n_out) st_u32_nt(out + (long long)nu * a.out_line + lout, M::pack(d[j], d[j + 8]));
+        if (nu + N2 * 4 * hl < a.n_out && (INV || within(nu + N2 * 4 * hl))) st_u32_nt(out + (long long)nu * a.out_line + lout, M::pack(d[j], d[j + 8]));
       }
     }
   }
@@ -190,7 +206,7 @@ __global__ __launch_bounds__(256) void fk_column_pair_mfma(FkPairArgs a, const m
   using M = Mfma<SP>;
   __shared__ float2 spec[4][N + 2];  // a wave's column spectrum, natural order; bin N repeats bin 0
   __shared__ float2 tl[16 * 64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 31, hl = lane >> 5;
   col1024_twiddles(tl, twt, false);
   mf_u4 B1[2][2];
@@ -210,26 +226,36 @@ __global__ __launch_bounds__(256) void fk_column_pair_mfma(FkPairArgs a, const m
   // column, computes the same values and stores them to the same places, so that every
   // wave issues the same loads and stores and the wait for the next group's loads leaves
   // this group's stores in flight.
-  PairItem nitem[2];
+  uint2 nitem[2], after[2];  // list entries of the group that is loading, of the one after it
   unsigned int nraw[2][2][4];
-  auto fetch = [&](long long g) {
+  auto entries = [&](long long g) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const long long w = g * 8 + 4 * u + wv;
-      nitem[u] = pair_item(w < a.nwork ? w : g * 8, a.Mx, a.My);
-      const unsigned int* in = inb + (long long)nitem[u].ky * a.in_row + (long long)nitem[u].kx * a.nt + j;
+      after[u] = pair_entry_uniform(a, w < a.nwork ? w : g * 8);
+    }
+  };
+  auto fetch = [&]() {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      nitem[u] = after[u];
+      const unsigned int* in = inb + (long long)(nitem[u].x >> 16) * a.in_row + (long long)(nitem[u].x & 0xffffu) * a.nt + j;
 #pragma unroll
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) nraw[u][q][r] = ld_u32_nt(in + 32 * (8 * q + 4 * hl + r));
     }
   };
-  if ((long long)blockIdx.x < ngroups) fetch(blockIdx.x);
+  if ((long long)blockIdx.x < ngroups) {
+    entries(blockIdx.x);
+    fetch();
+  }
+  if ((long long)blockIdx.x + gridDim.x < ngroups) entries((long long)blockIdx.x + gridDim.x);
   // the tables and the first group arrive before the loop, whose one wait per group then
   // counts only the loop's own loads and stores
   __builtin_amdgcn_s_waitcnt(0);
   for (long long g = blockIdx.x; g < ngroups; g += gridDim.x) {
-    const PairItem item[2] = {nitem[0], nitem[1]};
+    const uint2 item[2] = {nitem[0], nitem[1]};
     unsigned int raw[2][2][4];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -237,7 +263,8 @@ __global__ __launch_bounds__(256) void fk_column_pair_mfma(FkPairArgs a, const m
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) raw[u][q][r] = nraw[u][q][r];
-    if (g + gridDim.x < ngroups) fetch(g + gridDim.x);
+    if (g + gridDim.x < ngroups) fetch();
+    if (g + 2LL * gridDim.x < ngroups) entries(g + 2LL * gridDim.x);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       mf_u4 B3[4];
@@ -260,7 +287,8 @@ __global__ __launch_bounds__(256) void fk_column_pair_mfma(FkPairArgs a, const m
       // half), sharing q = sqrt(A + kz^2) in t-bin units (FP32); zero beyond the last
       // frequency sample, the last sample itself at q = HALF - 1; Jacobian kz / q times
       // the output scale
-      const PairItem& it = item[u];
+      const PairItem it = pair_of(a, item[u]);
+      const int nz = (int)item[u].y;
       const int kxs = it.kx < a.Mx / 2 ? it.kx : it.kx - a.Mx;
       const int kys = it.ky < a.My / 2 ? it.ky : it.ky - a.My;
       const double ax = a.sxk * kxs, ay = a.syk * kys;
@@ -274,8 +302,10 @@ __global__ __launch_bounds__(256) void fk_column_pair_mfma(FkPairArgs a, const m
       if (double(kzmax + 1) * (kzmax + 1) <= rem) ++kzmax;
       // a column without a mirror (its own mirror) stores its own remap twice
       const bool mir = it.has_mirror;
-      unsigned int* o1 = outb + (long long)it.ky * a.out_row + (long long)it.kx * a.nt + lane;
-      unsigned int* o2 = mir ? outb + (long long)it.ky2 * a.out_row + (long long)it.kx2 * a.nt + lane : o1;
+      unsigned int* c1 = outb + (long long)it.ky * a.out_row + (long long)it.kx * a.nt;
+      const __amdgpu_buffer_rsrc_t o1 = buf_view(c1);
+      const __amdgpu_buffer_rsrc_t o2 =
+          buf_view(mir ? outb + (long long)it.ky2 * a.out_row + (long long)it.kx2 * a.nt : c1);
 #pragma unroll
       for (int i = 0; i < HALF / 64; ++i) {
         const float kz = (float)(lane + 64 * i);
@@ -296,8 +326,9 @@ __global__ __launch_bounds__(256) void fk_column_pair_mfma(FkPairArgs a, const m
         const float ar = fmaf(fr, s1.x - s0.x, s0.x) * jac, ai = fmaf(fr, s1.y - s0.y, s0.y) * jac;
         const float br = fmaf(fr, m1.x - m0.x, m0.x) * jac, bi = -fmaf(fr, m1.y - m0.y, m0.y) * jac;
         const unsigned int pa = M::pack(ar, ai);
-        st_u32_nt(o1 + 64 * i, pa);
-        st_u32_nt(o2 + 64 * i, mir ? M::pack(br, bi) : pa);
+        const unsigned int off = kzi < nz ? 4u * (unsigned)kzi : kBufNone;
+        __builtin_amdgcn_raw_buffer_store_b32(pa, o1, off, 0, 2);
+        __builtin_amdgcn_raw_buffer_store_b32(mir ? M::pack(br, bi) : pa, o2, off, 0, 2);
       }
     }
   }
@@ -399,17 +430,20 @@ hipError_t launch_strided_mfma(int n, bool inverse, const StridedArgs& a, int np
   const mf_u4* t1 = static_cast<const mf_u4*>(t.a16[inverse][scaled][bf]);
   const mf_u4* t3 = static_cast<const mf_u4*>(n == 512 ? t.a32[inverse][scaled][bf] : t.a16[inverse][scaled][bf]);
   const int tiles_x = a.ncols / kMfT;
-  const dim3 grid((unsigned)((long long)tiles_x * nplanes));
+  const dim3 grid((unsigned)(a.items != nullptr ? (long long)a.nitems : (long long)tiles_x * nplanes));
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, grid, dim3(64 * kMfW), 0, s, a, t1, t3, tw, tiles_x);
     return hipGetLastError();
   };
-  if (n == 512) {
-    if (sp == SP_F16) return inverse ? go(strided_fft_mfma<512, true, SP_F16>) : go(strided_fft_mfma<512, false, SP_F16>);
-    return inverse ? go(strided_fft_mfma<512, true, SP_BF16>) : go(strided_fft_mfma<512, false, SP_BF16>);
-  }
-  if (sp == SP_F16) return inverse ? go(strided_fft_mfma<256, true, SP_F16>) : go(strided_fft_mfma<256, false, SP_F16>);
-  return inverse ? go(strided_fft_mfma<256, true, SP_BF16>) : go(strided_fft_mfma<256, false, SP_BF16>);
+  auto pick = [&](auto n_, auto sp_) {
+    constexpr int N = decltype(n_)::value, SP = decltype(sp_)::value;
+    if (a.items != nullptr) return inverse ? go(strided_fft_mfma<N, true, SP, true>) : go(strided_fft_mfma<N, false, SP, true>);
+    return inverse ? go(strided_fft_mfma<N, true, SP, false>) : go(strided_fft_mfma<N, false, SP, false>);
+  };
+  const std::integral_constant<int, SP_F16> h{};
+  const std::integral_constant<int, SP_BF16> b{};
+  if (n == 512) return sp == SP_F16 ? pick(std::integral_constant<int, 512>{}, h) : pick(std::integral_constant<int, 512>{}, b);
+  return sp == SP_F16 ? pick(std::integral_constant<int, 256>{}, h) : pick(std::integral_constant<int, 256>{}, b);
 }
 
 bool mfma_column_ok(int mt, int nt, int sp, const FkPairArgs& a) {

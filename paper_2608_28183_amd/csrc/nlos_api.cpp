@@ -108,6 +108,13 @@ hipError_t gen_tables(int device, const int* m, const bool* use, nlos::GenPlan* 
 // memory channels at a power-of-two stride.  es is the bytes per complex element.
 size_t fk_row_stride(size_t Mx, size_t nt, size_t es) { return Mx * nt + 256 / es; }
 
+// An intermediate of at most this many bytes is kept in the 256 MB last-level cache for the
+// next pass (ordinary accesses); larger ones stream past it.
+constexpr size_t kCacheBytes = size_t(160) << 20;
+
+// Zeros of the remapped spectrum below which a plan does without work lists.
+constexpr size_t kMinZeroBytes = size_t(16) << 20;
+
 // log2 of a power of two (0 for n <= 1)
 int ilog2(int n) {
   int k = 0;
@@ -180,6 +187,13 @@ struct nlos_ctx {
 struct nlos_fk_plan {
   nlos_fk_desc d{};
   int device = 0;
+  // The work lists (fk_schedule) of the y pass, the column pass and the x- and y-IFFT: entries
+  // list[i] .. list[i + 1] of d_items (null: every item).  kmax: largest kx needed; nz: depth
+  // samples stored ahead of the z pass.
+  int list[5] = {0, 0, 0, 0, 0};
+  int kmax = 0, nz = 0;
+  size_t w4_bytes = 0;        // of W4 that the x-IFFT writes
+  uint2* d_items = nullptr;
   int Mx = 0, My = 0, Mt = 0;
   double sxk = 0, syk = 0;
   float norm = 0.f;
@@ -628,6 +642,90 @@ nlos_status nlos_fk_desc_workspace_bytes(const nlos_fk_desc* d, size_t* bytes) {
   return NLOS_OK;
 }
 
+// The work lists of a plan.  The Stolt remap of column (kx, ky) is zero where
+// A(kx, ky) + kz^2 > (Mt/2 - 1)^2 (A of stolt_pair): outside an ellipsoid of frequencies,
+// which fills 0.35 of the remapped half spectrum at 256 x 256 x 512 (1 m wall, 32 ps) and
+// all but its corners where bins are short against the pitch.  What the zeros feed is
+// neither stored nor read, and spectra that only feed zeros are not formed: a column ends
+// at nz(kx, ky) (rounded up to the inverse passes' tiles), the y pass keeps |ky| up to its
+// plane's bound, the x pass kx up to kmax.
+static hipError_t fk_schedule(nlos_fk_plan* p) {
+  const nlos_fk_desc& d = p->d;
+  const int nx = d.nx, nt = d.nt, Mx = p->Mx, My = p->My;
+  const int sp = fk_sp(d.prec), half = p->Mt / 2;
+  const int Ty = p->gen_y ? nlos::gen_strided_cols(My) : nlos::strided_cols(My, false, sp);
+  const int Tx_i = p->gen_x ? nlos::gen_strided_cols(Mx) : nlos::strided_cols(Mx, true, sp);
+  const int Ty_i = p->gen_y ? nlos::gen_strided_cols(My) : nlos::strided_cols(My, true, sp);
+  const int G = std::max(Tx_i, Ty_i);
+  const int hx = Mx / 2, hy = My / 2;
+  // depth samples of column (kx, |ky|) that may be non-zero, a hair beyond the kernels' own
+  // test (they write the exact zeros), in whole granules; 0: none
+  std::vector<int> nz((size_t)(hy + 1) * (hx + 1), 0);
+  const double lim2 = (double)(half - 1) * (half - 1) * (1.0 + 1e-9);
+  for (int j = 0; j <= hy; ++j)
+    for (int k = 0; k <= hx; ++k) {
+      const double ax = p->sxk * k, ay = p->syk * j, rem = lim2 - (ax * ax + ay * ay);
+      if (rem < 1.0 && (j > 0 || k > 0)) break;  // A grows with k; kz = 0 is zero anyway
+      const int z = std::min((int)std::sqrt(rem), half - 1) + 1;
+      nz[(size_t)j * (hx + 1) + k] = std::min(nt, (z + G - 1) / G * G);
+    }
+  auto NZ = [&](int j, int k) { return nz[(size_t)j * (hx + 1) + k]; };
+  // without lists where the zeros are too few to pay for reading them (a list costs a small
+  // pass about 1 us, 16 MB take 3 us to move)
+  size_t zeros = 0;
+  for (int j = 0; j <= hy; ++j)
+    for (int k = 0; k <= hx; ++k) zeros += (size_t)(nt - NZ(j, k)) * fk_elem_bytes(d.prec) * 4;
+  p->kmax = hx;
+  p->nz = nt;
+  p->w4_bytes = (size_t)My * nx * nt * fk_elem_bytes(d.prec);
+  if (zeros < kMinZeroBytes) return hipSuccess;
+  // the listed passes address a plane with 32-bit byte offsets
+  const FkLayout L = fk_layout(&d);
+  if (std::max((size_t)My * L.rs_half, (size_t)Mx * nt) * L.es > 0xf0000000u) return hipSuccess;
+  p->kmax = 0;
+  while (p->kmax < hx && NZ(0, p->kmax + 1) > 0) ++p->kmax;
+  p->nz = NZ(0, 0);
+  std::vector<uint2> it;
+  auto push = [&](int plane, int lim, int col) {
+    it.push_back(make_uint2((unsigned)plane | (unsigned)lim << 16, (unsigned)col));
+  };
+  // y pass: planes kx, outputs |ky| <= j
+  for (int k = 0; k <= p->kmax; ++k) {
+    int j = 0;
+    while (j < hy && NZ(j + 1, k) > 0) ++j;
+    for (int c = 0; c < nt; c += Ty) push(k, j, c);
+  }
+  p->list[1] = (int)it.size();
+  // column pairs; on the planes kx = 0 and Mx/2 the mirror stays on the plane (ky <= My/2)
+  auto columns = [&](int k, int ky) {
+    const int n = NZ(2 * ky > My ? My - ky : ky, k);
+    if (n > 0 && !(2 * ky > My && (k == 0 || k == hx))) it.push_back(make_uint2((unsigned)k | (unsigned)ky << 16, (unsigned)n));
+  };
+  for (int ky = 0; ky < My; ++ky)
+    for (int k = 0; k <= p->kmax; ++k) columns(k, ky);
+  p->list[2] = (int)it.size();
+  // x-IFFT: planes ky, tiles with a non-zero column, inputs |kx| <= k
+  for (int ky = 0; ky < My; ++ky) {
+    const int j = 2 * ky > My ? My - ky : ky;
+    for (int c = 0, k = hx; c < NZ(j, 0); c += Tx_i) {
+      while (NZ(j, k) <= c / G * G) --k;
+      push(ky, k, c);
+    }
+  }
+  p->list[3] = (int)it.size();
+  p->w4_bytes = (size_t)(p->list[3] - p->list[2]) * Tx_i * nx * fk_elem_bytes(d.prec);
+  // y-IFFT: planes x, inputs |ky| <= j
+  for (int x = 0; x < nx; ++x)
+    for (int c = 0, j = hy; c < p->nz; c += Ty_i) {
+      while (NZ(j, 0) <= c / G * G) --j;
+      push(x, j, c);
+    }
+  p->list[4] = (int)it.size();
+  hipError_t e = nlos::dev_alloc((void**)&p->d_items, it.size() * sizeof(uint2));
+  if (e == hipSuccess) e = hipMemcpy(p->d_items, it.data(), it.size() * sizeof(uint2), hipMemcpyHostToDevice);
+  return e;
+}
+
 nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_plan** out) {
   try {
     if (!ctx || !out) return fail(ctx, NLOS_ERR_INVALID_ARG, "fk_plan_create: NULL argument");
@@ -655,9 +753,11 @@ nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_pl
     const int m[3] = {p->Mx, p->My, p->Mt};
     const bool use[3] = {p->gen_xr2c, p->gen_y, p->gen_t};
     nlos::GenPlan* const g[3] = {&p->gx, &p->gy, &p->gt};
-    const hipError_t e = gen_tables(ctx->device, m, use, g, 3, &p->d_gtw);
+    hipError_t e = gen_tables(ctx->device, m, use, g, 3, &p->d_gtw);
+    if (e == hipSuccess) e = hipSetDevice(ctx->device);
+    if (e == hipSuccess) e = fk_schedule(p);
     if (e != hipSuccess) {
-      delete p;
+      nlos_fk_plan_destroy(p);
       return fail(ctx, e == hipErrorOutOfMemory ? NLOS_ERR_OUT_OF_MEMORY : NLOS_ERR_DEVICE,
                   "fk_plan_create: general-length twiddle tables: %s", hipGetErrorString(e));
     }
@@ -676,9 +776,10 @@ nlos_status nlos_fk_workspace_bytes(const nlos_fk_plan* p, size_t* bytes) {
 
 nlos_status nlos_fk_plan_destroy(nlos_fk_plan* p) {
   if (!p) return NLOS_OK;
-  if (p->d_gtw) {
+  if (p->d_gtw || p->d_items) {
     (void)hipSetDevice(p->device);
-    (void)hipFree(p->d_gtw);
+    if (p->d_gtw) (void)hipFree(p->d_gtw);
+    if (p->d_items) (void)hipFree(p->d_items);
   }
   delete p;
   return NLOS_OK;
@@ -696,7 +797,7 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   void* W2 = base + L.w2_off * L.es;        // [My][Mx/2+1][nt] half spectrum after the y pass
   void* W3 = base + L.b_off * L.es;         // [My][Mx][nt] after the column pass
   void* W4 = base;                          // [My][nx][nt] after the x-IFFT (W1, W2 are dead)
-  void* W5 = W3;                            // [ny][nx][nt] after the x-IFFT (W3 is dead)
+  void* W5 = W3;                            // [ny][nx][nt] after the y-IFFT (W3 is dead)
   // FP16 storage exponents: [0] W1 and W2, [1] W3, [2] W4, [3] W5
   int* ex = nullptr;
   float* partials = nullptr;
@@ -720,32 +821,46 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
                                     /*second inverse*/ l_my, s);
     }));
   }
-  // pass 1: x-FFT of tau * t/(nt-1), zero padded to Mx, kx in [0, Mx/2]
+  const bool mf = ctx->mfma && sp != nlos::SP_F32;
+  auto list = [&](StridedArgs& a, int i) {
+    a.items = p->d_items ? p->d_items + p->list[i] : nullptr;
+    a.nitems = p->list[i + 1] - p->list[i];
+  };
+  // Cached or streaming (ordinary or non-temporal): an intermediate that fits the last-level cache is read from it by the
+  // next pass (fk_y 98 -> 80 us at 128x128x1024, whose W1 is 135 MB), a larger one only
+  // displaces what could still be reused
+  const int w1_nt = (size_t)ny * (p->kmax + 1) * nt * L.es > kCacheBytes;
+  const int w5_nt = (size_t)ny * nx * p->nz * L.es > kCacheBytes;
+  // W4 is written in the cache up to a little beyond its size (268 MB at 128x128x1024: x-IFFT
+  // 152 -> 130 us, y-IFFT unchanged; 344 MB at 256x256x512: 172 both ways, y-IFFT 143 -> 168 us)
+  const int w4_nt = p->w4_bytes > 2 * kCacheBytes;
+  // pass 1: x-FFT of tau * t/(nt-1), zero padded to Mx, kx in [0, kmax]
   FkXArgs x{};
   x.tau = d_tau; x.out = W1; x.out_plane = RH; x.nx = (int)nx; x.nt = (int)nt;
   x.tscale = (float)(1.0 / (double)(nt - 1));
-  x.e_out = ex;
+  x.e_out = ex; x.kmax = p->kmax; x.nt_out = w1_nt;
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_X, [&] {
     return p->gen_xr2c ? nlos::launch_gen_xr2c(p->gx, x, (int)ny, s) : nlos::launch_fk_xr2c((int)Mx, x, (int)ny, tw, s, sp);
   }));
-  // pass 2: y-FFT of the Mx/2 + 1 planes, zero padded to My
+  // pass 2: y-FFT of the planes kx <= kmax, zero padded to My
   StridedArgs a{};
   a.in = W1; a.out = W2;
   a.in_plane = nt; a.in_line = RH; a.out_plane = nt; a.out_line = RH;
   a.ncols = (int)nt; a.n_in = (int)ny; a.n_out = (int)My;
-  a.e_in = ex; a.e_out = ex;
-  const bool mf = ctx->mfma && sp != nlos::SP_F32;
+  a.e_in = ex; a.e_out = ex; a.nt_in = w1_nt; a.nt_out = 1;
+  list(a, 0);
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_Y, [&] {
     if (mf && nlos::mfma_strided_ok((int)My, sp, a))
-      return nlos::launch_strided_mfma((int)My, false, a, (int)(Mx / 2 + 1), ctx->mt, tw, s, sp);
-    return p->gen_y ? nlos::launch_gen_strided(p->gy, false, nlos::ST_C64, a, (int)(Mx / 2 + 1), s)
-                    : nlos::launch_strided((int)My, false, nlos::LD_C64, nlos::ST_C64, a, (int)(Mx / 2 + 1), tw, s, sp, true);
+      return nlos::launch_strided_mfma((int)My, false, a, p->kmax + 1, ctx->mt, tw, s, sp);
+    return p->gen_y ? nlos::launch_gen_strided(p->gy, false, nlos::ST_C64, a, p->kmax + 1, s)
+                    : nlos::launch_strided((int)My, false, nlos::LD_C64, nlos::ST_C64, a, p->kmax + 1, tw, s, sp, true);
   }));
   // pass 3: per column of the half spectrum: t-FFT, Stolt + Jacobian + 1/(Mx My Mt) for the
   // column and its mirror; the remapped spectra (kz < nt) go to W3
   FkPairArgs c{};
   c.in = W2; c.out = W3; c.in_row = RH; c.out_row = RF;
-  c.nwork = (Mx / 2 - 1) * My + 2 * (My / 2 + 1);
+  c.items = p->d_items ? p->d_items + p->list[1] : nullptr;
+  c.nwork = p->d_items ? p->list[2] - p->list[1] : (Mx / 2 - 1) * My + 2 * (My / 2 + 1);
   c.nt = (int)nt; c.Mx = (int)Mx; c.My = (int)My;
   c.sxk = p->sxk; c.syk = p->syk; c.norm = p->norm;
   c.e_in = ex; c.e_out = ex ? ex + 1 : nullptr;
@@ -764,7 +879,8 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   a.in = W3; a.out = W4;
   a.in_plane = RF; a.in_line = nt; a.out_plane = RX; a.out_line = nt;
   a.ncols = (int)nt; a.n_in = (int)Mx; a.n_out = (int)nx;
-  a.e_in = ex ? ex + 1 : nullptr; a.e_out = ex ? ex + 2 : nullptr;
+  a.e_in = ex ? ex + 1 : nullptr; a.e_out = ex ? ex + 2 : nullptr; a.nt_in = 1; a.nt_out = w4_nt;
+  list(a, 2);
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_XI, [&] {
     if (mf && nlos::mfma_strided_ok((int)Mx, sp, a))
       return nlos::launch_strided_mfma((int)Mx, true, a, (int)My, ctx->mt, tw, s, sp);
@@ -776,18 +892,19 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   a.in = W4; a.out = W5;
   a.in_plane = nt; a.in_line = RX; a.out_plane = nt; a.out_line = nx * nt;
   a.ncols = (int)nt; a.n_in = (int)My; a.n_out = (int)ny;
-  a.e_in = ex ? ex + 2 : nullptr; a.e_out = ex ? ex + 3 : nullptr;
+  a.e_in = ex ? ex + 2 : nullptr; a.e_out = ex ? ex + 3 : nullptr; a.nt_in = 1; a.nt_out = w5_nt;
+  list(a, 3);
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_YI, [&] {
     if (mf && nlos::mfma_strided_ok((int)My, sp, a))
       return nlos::launch_strided_mfma((int)My, true, a, (int)nx, ctx->mt, tw, s, sp);
     return p->gen_y ? nlos::launch_gen_strided(p->gy, true, nlos::ST_C64, a, (int)nx, s)
                     : nlos::launch_strided((int)My, true, nlos::LD_C64, nlos::ST_C64, a, (int)nx, tw, s, sp, true);
   }));
-  // pass 6: z-IFFT of each (y, x) line (kz < nt stored, zero padded to Mt), keep z < nt,
+  // pass 6: z-IFFT of each (y, x) line (kz < nz stored, zero padded to Mt), keep z < nt,
   // |Psi|^2 and the max over depth
   ContigArgs z{};
   z.in = W5; z.out = d_vol; z.nlines = ny * nx; z.in_line = nt; z.out_line = nt;
-  z.n_in = (int)nt; z.n_out = (int)nt; z.oscale = 1.0f; z.img = d_img;
+  z.n_in = p->nz; z.n_out = (int)nt; z.oscale = 1.0f; z.img = d_img;
   z.e_in = ex ? ex + 3 : nullptr;
   if (d_psi) {  // the complex field Psi itself (FP32 path)
     z.out = d_psi; z.img = nullptr;
@@ -1726,11 +1843,12 @@ nlos_status nlos_moe(nlos_ctx* ctx, const nlos_moe_plan* p, const float* d_tau, 
   FkXArgs x{};
   x.tau = d_tau; x.out = W1; x.out_plane = RH; x.nx = (int)nx; x.nt = (int)nt;
   x.tscale = (float)(1.0 / (double)(nt - 1)); x.unscaled = 1;
+  x.kmax = (int)Mx / 2; x.nt_out = 1;
   HIP_TRY(ctx, timed(ctx, NLOS_PASS_FK_X, [&] { return nlos::launch_fk_xr2c((int)Mx, x, (int)ny, tw, s0); }));
   StridedArgs a{};
   a.in = W1; a.out = W2;
   a.in_plane = nt; a.in_line = RH; a.out_plane = nt; a.out_line = RH;
-  a.ncols = (int)nt; a.n_in = (int)ny; a.n_out = (int)My;
+  a.ncols = (int)nt; a.n_in = (int)ny; a.n_out = (int)My; a.nt_in = a.nt_out = 1;
   HIP_TRY(ctx, timed(ctx, NLOS_PASS_FK_Y, [&] { return nlos::launch_strided((int)My, false, nlos::LD_C64, nlos::ST_C64, a, (int)(Mx / 2 + 1), tw, s0, nlos::SP_F32, true); }));
   // fork: the RSD branch on the second stream
   HIP_TRY(ctx, hipEventRecord(ctx->fork[0], s0));
@@ -1769,12 +1887,12 @@ nlos_status nlos_moe(nlos_ctx* ctx, const nlos_moe_plan* p, const float* d_tau, 
   a = StridedArgs{};
   a.in = W3; a.out = W4;
   a.in_plane = nt; a.in_line = RF; a.out_plane = nt; a.out_line = RF;
-  a.ncols = (int)nt; a.n_in = (int)My; a.n_out = (int)ny;
+  a.ncols = (int)nt; a.n_in = (int)My; a.n_out = (int)ny; a.nt_in = a.nt_out = 1;
   HIP_TRY(ctx, timed(ctx, NLOS_PASS_FK_YI, [&] { return nlos::launch_strided((int)My, true, nlos::LD_C64, nlos::ST_C64, a, (int)Mx, tw, s0, nlos::SP_F32, true); }));
   a = StridedArgs{};
   a.in = W4; a.out = W5;
   a.in_plane = RF; a.in_line = nt; a.out_plane = nx * nt; a.out_line = nt;
-  a.ncols = (int)nt; a.n_in = (int)Mx; a.n_out = (int)nx;
+  a.ncols = (int)nt; a.n_in = (int)Mx; a.n_out = (int)nx; a.nt_in = a.nt_out = 1;
   HIP_TRY(ctx, timed(ctx, NLOS_PASS_FK_XI, [&] { return nlos::launch_strided((int)Mx, true, nlos::LD_C64, nlos::ST_C64, a, (int)ny, tw, s0, nlos::SP_F32, true); }));
   ContigArgs z{};
   z.in = W5; z.out = nullptr; z.nlines = ny * nx; z.in_line = nt; z.out_line = nt;

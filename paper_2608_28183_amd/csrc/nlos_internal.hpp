@@ -42,6 +42,13 @@ enum { ST_C64 = 0, ST_ABS2_IMG = 1, ST_ABS_IMG = 2, ST_C64_SCALED = 3 };
 enum { CL_C64 = 0, CL_REAL = 1, CL_REAL_PAIR = 2 };
 enum { CS_C64 = 0, CS_ABS_IMG = 1, CS_BINS = 2, CS_ABS2_MAX = 3 };
 
+// One (plane, column tile) of a strided pass, from a list the host builds: the tile's first
+// column and a bound on the signed index along the line, |n| <= lim (n <= lim or
+// n >= N - lim).  Samples beyond it are zero and are not read (inverse passes) or not
+// needed and not written (the forward pass).  x = plane | lim << 16, y = first column.
+__device__ __forceinline__ int item_plane(uint2 e) { return (int)(e.x & 0xffffu); }
+__device__ __forceinline__ int item_lim(uint2 e) { return (int)(e.x >> 16); }
+
 // Lines along a strided axis.  Element n of line `col` in plane `plane` is at
 // in[plane * in_plane + n * in_line + col]; n < n_in are read (the rest are the
 // zero padding), n < n_out are written.
@@ -61,6 +68,11 @@ struct StridedArgs {
   const int* e_in;
   const int* e_out;
   int e_per_col;
+  // the work items (null: every tile of every plane, lim = N/2); tiles as wide as
+  // strided_cols / gen_strided_cols say
+  const uint2* items;
+  int nitems;
+  int nt_in, nt_out;   // FP32 ST_C64: non-temporal loads / stores
 };
 
 // Lines along the contiguous axis: line `ln` is in[ln * in_line + n], n < n_in.
@@ -90,6 +102,8 @@ struct FkXArgs {
   float tscale;        // 1 / (nt - 1)
   const int* e_out;    // FP16 output: written as value * 2^(*e_out)
   int unscaled;        // 1: plain x-FFT of tau (no t/(nt-1) factor, which then comes later)
+  int kmax;            // rows kx <= kmax are written
+  int nt_out;          // FP32: non-temporal stores
 };
 
 // f-k pass 3: input half spectrum in[ky][kx <= Mx/2][nt] (row stride in_row), output full
@@ -104,6 +118,9 @@ struct FkPairArgs {
   const int* e_in;     // FP16: input holds value * 2^(*e_in), output is written
   const int* e_out;    // as value * 2^(*e_out)
   float tscale_in;     // non-zero: input sample t is first multiplied by t * tscale_in
+  // the nwork column pairs to do (null: all of them): x = kx | ky << 16, y = kz stored (the
+  // remap is zero beyond)
+  const uint2* items;
 };
 
 // Mixture of experts, phasors from the shared spatial half spectrum: for each column
@@ -148,7 +165,11 @@ struct RsdPropArgs {
                            // FP16 / BF16: one)
 };
 
-// stream: non-temporal loads and stores (FP32 LD_C64 -> ST_C64 only; ignored otherwise)
+// stream: the f-k passes (FP32 LD_C64 -> ST_C64), as resident blocks where the shape allows
+// Columns per tile of launch_strided (stream as below), launch_strided_mfma (32) and
+// launch_gen_strided for lines of n points: what an item list of theirs is cut into.
+int strided_cols(int n, bool inverse, int sp);
+int gen_strided_cols(int n);
 hipError_t launch_strided(int n, bool inverse, int ld, int st, const StridedArgs& a, int nplanes,
                           const float2* tw, hipStream_t s, int sp = 0, bool stream = false);
 hipError_t launch_contig(int n, bool inverse, int ld, int st, const ContigArgs& a,
