@@ -157,10 +157,11 @@ nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan *plan);
 /* Every valid event (as in nlos_bin) in bin b of its pixel adds
  * exp(-2 pi i freq_bin[f] b / nt) to d_phasor[pixel][f] (float re, im pairs,
  * [ny][nx][n_freq], 8-byte aligned; zeroed first unless desc->accumulate), which is the
- * DFT at those bins of the histogram nlos_bin would build, up to rounding: hardware
- * float atomics, one wave per event with its lanes over the frequencies, so the order of
- * the sums (and the last bits) varies from run to run.  Dropped events are counted as
- * in nlos_bin.  Feeds nlos_rsd_from_phasors. */
+ * DFT at those bins of the histogram nlos_bin would build, up to rounding.  Sorted by pixel
+ * tiles (workspace from the context pool, as in nlos_bin), or, for few events on a large plan,
+ * shapes without tiles and streams under capture, by hardware float atomics, where the
+ * order of the sums (and the last bits) varies from run to run.  Dropped events are counted
+ * as in nlos_bin.  Feeds nlos_rsd_from_phasors. */
 nlos_status nlos_phasor_bin(nlos_ctx *ctx, const nlos_phasor_plan *plan, const nlos_event *d_events,
                             uint64_t n_events, float *d_phasor, unsigned long long *d_dropped);
 

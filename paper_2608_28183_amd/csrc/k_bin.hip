@@ -1,6 +1,8 @@
 // Photon-event binning and small utility kernels (gfx950, wave64).
 #include "nlos_internal.hpp"
 
+#include <algorithm>
+
 namespace nlos {
 
 __global__ __launch_bounds__(256) void fill_u32(uint32_t* __restrict__ p, size_t n, uint32_t v) {
@@ -135,8 +137,6 @@ hipError_t launch_bin(const void* events, unsigned long long n, uint32_t* hist,
 // depend on the order in which the LDS atomics land.
 
 constexpr int kBinThreads = 256;
-constexpr int kBinPerThread = 32;
-constexpr int kBinChunk = kBinThreads * kBinPerThread;  // events per block in pass 1
 // tp nt <= kBinTileWords (codes fit 16 bits).  At 64 x 64 x 512 with 1e7 events, tiles of
 // 4096 words (512 tiles) measured 0.066 ms, of 8192 words 0.074 ms (the gather's time is
 // its busiest tile's: fewer, larger tiles balance worse) and of 2048 words 0.080 ms.
@@ -224,27 +224,29 @@ __device__ __forceinline__ void block_exclusive_scan(uint32_t* a, int m, uint32_
   }
 }
 
-// Pass 1: chunk blockIdx.x -> runs[chunk][kBinChunk] (16-bit codes, sorted by tile) and
-// start[tile][chunk]; invalid events are counted into *dropped.
+// Pass 1: chunk blockIdx.x of kBinThreads PT events -> runs[chunk][.] (16-bit codes
+// (pixel in tile) stride + bin, sorted by tile) and start[tile][chunk]; invalid events are
+// counted into *dropped.
+template <int PT>
 __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __restrict__ ev, unsigned long long n,
                                                              int npix, int nt, U32Div bin_ps, uint32_t t0, int tp,
-                                                             U32Div tp_div,
+                                                             int stride, U32Div tp_div,
                                                              int ntiles, int nchunks, uint16_t* __restrict__ runs,
                                                              uint16_t* __restrict__ start,
                                                              unsigned long long* __restrict__ dropped) {
   extern __shared__ uint32_t sh[];
   uint32_t* cnt = sh;  // ntiles + 1 counters, then their exclusive scan
-  uint16_t* sorted = reinterpret_cast<uint16_t*>(sh + ntiles + 1);  // kBinChunk codes
+  uint16_t* sorted = reinterpret_cast<uint16_t*>(sh + ntiles + 1);  // the codes
   __shared__ uint32_t wsum[kBinThreads / 64];
   for (int i = threadIdx.x; i <= ntiles; i += kBinThreads) cnt[i] = 0;
   __syncthreads();
-  const unsigned long long beg = (unsigned long long)blockIdx.x * kBinChunk;
-  uint32_t code[kBinPerThread];  // tile << 16 | (pixel in tile) nt + bin; ~0u: none
-  uint32_t pos[kBinPerThread];   // place in the tile's run
+  const unsigned long long beg = (unsigned long long)blockIdx.x * (kBinThreads * PT);
+  uint32_t code[PT];  // tile << 16 | (pixel in tile) nt + bin; ~0u: none
+  uint32_t pos[PT];   // place in the tile's run
   unsigned int drop = 0;
-  constexpr int kLoads = 16;  // loads in flight per lane
+  constexpr int kLoads = PT < 16 ? PT : 16;  // loads in flight per lane
 #pragma unroll
-  for (int r = 0; r < kBinPerThread; r += kLoads) {
+  for (int r = 0; r < PT; r += kLoads) {
     uint2 e[kLoads];
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
@@ -260,7 +262,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
         const int px = bin_event(e[j], npix, nt, bin_ps, t0, &b);
         if (px >= 0) {
           const int tile = (int)u32_quot((uint32_t)px, tp_div);
-          c = ((uint32_t)tile << 16) | (uint32_t)((px - tile * tp) * nt + b);
+          c = ((uint32_t)tile << 16) | (uint32_t)((px - tile * tp) * stride + b);
         } else {
           ++drop;
         }
@@ -275,11 +277,11 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
   for (int i = threadIdx.x; i <= ntiles; i += kBinThreads)
     start[(size_t)i * nchunks + blockIdx.x] = (uint16_t)cnt[i];
 #pragma unroll
-  for (int j = 0; j < kBinPerThread; ++j)
+  for (int j = 0; j < PT; ++j)
     if (code[j] != ~0u) sorted[cnt[code[j] >> 16] + pos[j]] = (uint16_t)(code[j] & 0xffffu);
   __syncthreads();
   const uint32_t nv = cnt[ntiles];
-  uint16_t* out = runs + (size_t)blockIdx.x * kBinChunk;
+  uint16_t* out = runs + (size_t)blockIdx.x * (kBinThreads * PT);
   for (uint32_t i = threadIdx.x; i < nv; i += kBinThreads) out[i] = sorted[i];
   if (dropped != nullptr) {
 #pragma unroll
@@ -288,19 +290,14 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
   }
 }
 
-// Pass 2: one block per tile.  Its runs from kBinGroup chunks at a time are laid end to
-// end (exclusive scan of their lengths); lane i of the flat range finds its chunk by
-// binary search and counts its code in the tile's LDS histogram.
-__global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint16_t* __restrict__ runs,
-                                                                    const uint16_t* __restrict__ start,
-                                                                    int nchunks, int npix, int nt, int tp,
-                                                                    uint32_t* __restrict__ hist, int accumulate) {
-  extern __shared__ uint32_t h[];  // tp nt counters
+// Pass 2 for one tile and a block: its runs from kBinGroup chunks at a time are laid end to
+// end (exclusive scan of their lengths); lane i of the flat range finds its chunk by binary
+// search and counts its code in the tile's histogram h (`words` counters in LDS, cleared here).
+__device__ __forceinline__ void gather_tile(const uint16_t* __restrict__ runs, const uint16_t* __restrict__ start,
+                                            int nchunks, int chunk, int t, uint32_t* h, int words) {
   __shared__ uint32_t rbeg[kBinGroup];
   __shared__ uint32_t rpre[kBinGroup + 1];
   __shared__ uint32_t wsum[kBinGatherThreads / 64];
-  const int t = blockIdx.x;
-  const int words = tp * nt;
   for (int i = threadIdx.x; i < words; i += kBinGatherThreads) h[i] = 0;
   for (int c0 = 0; c0 < nchunks; c0 += kBinGroup) {
     const int g = nchunks - c0 < kBinGroup ? nchunks - c0 : kBinGroup;
@@ -338,7 +335,7 @@ __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint1
           // elements only grow with j: walk on to the run that holds i (rpre[g] = total > i
           // stops the walk at k = g - 1 at the latest)
           while (rpre[k + 1] <= i) ++k;
-          v[j] = runs[(size_t)(c0 + k) * kBinChunk + rbeg[k] + (i - rpre[k])];
+          v[j] = runs[(size_t)(c0 + k) * chunk + rbeg[k] + (i - rpre[k])];
         }
       }
 #pragma unroll
@@ -346,7 +343,16 @@ __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint1
     }
   }
   __syncthreads();
-  const long long first = (long long)t * tp * nt;
+}
+
+__global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint16_t* __restrict__ runs,
+                                                                    const uint16_t* __restrict__ start,
+                                                                    int nchunks, int chunk, int npix, int nt, int tp,
+                                                                    uint32_t* __restrict__ hist, int accumulate) {
+  extern __shared__ uint32_t h[];  // tp nt counters
+  const int words = tp * nt;
+  gather_tile(runs, start, nchunks, chunk, blockIdx.x, h, words);
+  const long long first = (long long)blockIdx.x * tp * nt;
   const long long last = (long long)npix * nt;
   for (int i = threadIdx.x; i < words && first + i < last; i += kBinGatherThreads) {
     uint32_t* g = hist + first + i;
@@ -354,40 +360,165 @@ __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint1
   }
 }
 
-// Tile layout of a binning job: tp pixels per tile (tp nt <= kBinTileWords), or false when
-// the tiled path does not apply (then the per-event atomic kernel runs).
-bool bin_tiles(int npix, int nt, unsigned long long n, int* tp, int* ntiles) {
-  if (nt > kBinTileWords || n >= (1ull << 31)) return false;
-  *tp = kBinTileWords / nt;
+// Pass 2 of phasor binning: the tile's histogram as above, which stays in LDS, then its DFT at
+// the nf bins on the matrix cores (FP32): rows are the (re, im) parts of the frequencies in
+// blocks of 16, columns the tile's pixels in blocks of 16, the contraction runs over the time
+// bins, 4 a step.  The twiddles come as operands from the plan's table
+// tab[row block][step][lane] (lane l: part (l % 16) of the block at bin 4 step + l / 16), the
+// counts from the histogram, whose rows are `stride` = 4 mod 64 words apart so that 16 pixels
+// x 4 bins fall on 64 banks.  Few blocks split the bins over the waves and add up in LDS.
+// Every sum has a fixed order.  The same DFT on the vector units took 45 us of 61 at
+// 64 x 64 x 512 with 39 frequencies (7 instructions per count and frequency).
+typedef float bin_f4 __attribute__((ext_vector_type(4)));
+constexpr int kPhasorWaves = kBinGatherThreads / 64;
+__global__ __launch_bounds__(kBinGatherThreads) void bin_tile_phasor(const uint16_t* __restrict__ runs,
+                                                                    const uint16_t* __restrict__ start,
+                                                                    int nchunks, int chunk, int npix, int nt, int tp,
+                                                                    int stride, const float* __restrict__ tab, int nf,
+                                                                    float* __restrict__ P, int accumulate) {
+  extern __shared__ uint32_t h[];  // tp stride counters, later the partial sums [wave][256]
+  const int words = tp * stride;
+  float* red = reinterpret_cast<float*>(h);
+  gather_tile(runs, start, nchunks, chunk, blockIdx.x, h, words);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c16 = lane & 15, kq = lane >> 4;
+  const int pix0 = blockIdx.x * tp;
+  const int npx = npix - pix0 < tp ? npix - pix0 : tp;
+  const int nsteps = (nt + 3) / 4;
+  const int nrb = (2 * nf + 15) / 16;
+  const int units = nrb * ((npx + 15) / 16);
+  const int ks = units >= kPhasorWaves ? 1 : kPhasorWaves / units;  // parts of the contraction
+  const int per = (nsteps + ks - 1) / ks;
+  auto put = [&](int u, bin_f4 d) {  // lane: rows 4 kq + v, column c16
+    const int px = (u / nrb) * 16 + c16, row = (u % nrb) * 16 + 4 * kq;
+    if (px >= npx) return;
+    float* o = P + (long long)(pix0 + px) * 2 * nf + row;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (row + v < 2 * nf) o[v] = accumulate ? o[v] + d[v] : d[v];
+  };
+  bin_f4 d;
+  for (int s0 = 0; s0 < units * ks; s0 += kPhasorWaves) {
+    const int slot = s0 + wv;
+    d = bin_f4{0.f, 0.f, 0.f, 0.f};
+    if (slot < units * ks) {
+      const int u = slot / ks, q0 = (slot % ks) * per;
+      const int q1 = q0 + per < nsteps ? q0 + per : nsteps;
+      const int px = (u / nrb) * 16 + c16;
+      const uint32_t* row = h + (px < tp ? px : tp - 1) * stride + kq;
+      const float* t = tab + (long long)(u % nrb) * nsteps * 64 + lane;
+#pragma unroll 8
+      for (int q = q0; q < q1; ++q) d = __builtin_amdgcn_mfma_f32_16x16x4f32(t[q * 64], (float)row[4 * q], d, 0, 0, 0);
+      if (ks == 1) put(u, d);
+    }
+  }
+  if (ks == 1) return;
+  // one slot per wave (units ks <= kPhasorWaves); every histogram read is done
+  __syncthreads();
+  *reinterpret_cast<bin_f4*>(red + wv * 256 + 4 * lane) = d;
+  __syncthreads();
+  if (wv < units) {
+    d = *reinterpret_cast<const bin_f4*>(red + wv * ks * 256 + 4 * lane);
+    for (int i = 1; i < ks; ++i) d += *reinterpret_cast<const bin_f4*>(red + (wv * ks + i) * 256 + 4 * lane);
+    put(wv, d);
+  }
+}
+
+// Events per thread of pass 1 (a chunk is kBinThreads times as many): short jobs of few tiles
+// want more blocks (1e4 events 15 us against 23 at 64 x 64 x 512); from there on the gather's
+// cost is its number of runs (1e6 events 36 us against 56)
+int bin_per_thread(unsigned long long n, int ntiles) { return n >= (1ull << 18) || ntiles > 1024 ? 32 : 8; }
+
+// Tile layout of a binning job: tp pixels of `stride` words per tile (tp stride <= words), or
+// false when the tiled path does not apply (then the per-event atomic kernel runs).
+bool bin_tiles(int npix, int stride, unsigned long long n, int words, int* tp, int* ntiles) {
+  if (stride > words || n >= (1ull << 31)) return false;
+  *tp = words / stride;
   if (*tp > npix) *tp = npix;
   *ntiles = (npix + *tp - 1) / *tp;
   return *ntiles <= kBinMaxTiles;
 }
+// Phasor binning: 16 pixels a tile (the columns of a matrix product) up to 1024 bins, fewer
+// beyond (two blocks of 66 KB of LDS per CU), more below 512; and the row stride of
+// bin_tile_phasor
+int phasor_words(int stride) { return std::min(std::max(16 * 516, 16 * stride), 16 * 1028); }
+int phasor_stride(int nt) { return (nt + 59) / 64 * 64 + 4; }
 
-size_t bin_workspace_bytes(int npix, int nt, unsigned long long n) {
-  int tp = 0, nti = 0;
-  if (!bin_tiles(npix, nt, n, &tp, &nti)) return 0;
-  const size_t nchunks = (size_t)((n + kBinChunk - 1) / kBinChunk);
-  const size_t bytes = 2 * nchunks * kBinChunk + 2 * (size_t)(nti + 1) * nchunks;
+size_t bin_runs_bytes(unsigned long long n, int ntiles) {
+  const size_t chunk = (size_t)kBinThreads * bin_per_thread(n, ntiles);
+  const size_t nchunks = (size_t)((n + chunk - 1) / chunk);
+  const size_t bytes = 2 * nchunks * chunk + 2 * (size_t)(ntiles + 1) * nchunks;
   return bytes > 0 ? bytes : 256;  // never zero: zero means "not tiled"
 }
+size_t bin_workspace_bytes(int npix, int nt, unsigned long long n) {
+  int tp = 0, nti = 0;
+  return bin_tiles(npix, nt, n, kBinTileWords, &tp, &nti) ? bin_runs_bytes(n, nti) : 0;
+}
+size_t phasor_workspace_bytes(int npix, int nt, unsigned long long n) {
+  int tp = 0, nti = 0;
+  return bin_tiles(npix, phasor_stride(nt), n, phasor_words(phasor_stride(nt)), &tp, &nti) ? bin_runs_bytes(n, nti) : 0;
+}
+
+namespace {
+// The tiles of a job and its sorted runs in ws (pass 1 launched)
+struct BinRuns {
+  int tp, ntiles, nchunks, chunk;
+  uint16_t* runs;   // [chunk][.]
+  uint16_t* start;  // [tile][chunk], ntiles + 1 rows
+};
+hipError_t bin_sort(const void* events, unsigned long long n, unsigned long long* dropped, int npix, int nt,
+                    int stride, int words, uint32_t bin_ps, uint32_t t0, void* ws, hipStream_t s, BinRuns* r) {
+  if (!bin_tiles(npix, stride, n, words, &r->tp, &r->ntiles)) return hipErrorInvalidValue;
+  const int pt = bin_per_thread(n, r->ntiles);
+  r->chunk = kBinThreads * pt;
+  r->nchunks = (int)((n + r->chunk - 1) / r->chunk);
+  r->runs = static_cast<uint16_t*>(ws);
+  r->start = r->runs + (size_t)r->nchunks * r->chunk;
+  if (r->nchunks == 0) return hipSuccess;
+  auto go = [&](auto k) {
+    hipLaunchKernelGGL(k, dim3((unsigned)r->nchunks), dim3(kBinThreads),
+                       (size_t)4 * (r->ntiles + 1) + (size_t)2 * r->chunk, s, static_cast<const uint2*>(events), n,
+                       npix, nt, u32_div(bin_ps), t0, r->tp, stride, u32_div((uint32_t)r->tp), r->ntiles, r->nchunks, r->runs,
+                       r->start, dropped);
+    return hipGetLastError();
+  };
+  return pt == 32 ? go(bin_chunk_sort<32>) : go(bin_chunk_sort<8>);
+}
+}  // namespace
 
 hipError_t launch_bin_tiled(const void* events, unsigned long long n, uint32_t* hist, unsigned long long* dropped,
                             int npix, int nt, uint32_t bin_ps, uint32_t t0, int accumulate, void* ws, hipStream_t s) {
-  int tp = 0, nti = 0;
-  if (!bin_tiles(npix, nt, n, &tp, &nti)) return hipErrorInvalidValue;
-  const int nchunks = (int)((n + kBinChunk - 1) / kBinChunk);
-  uint16_t* runs = static_cast<uint16_t*>(ws);                // [chunk][kBinChunk]
-  uint16_t* start = runs + (size_t)nchunks * kBinChunk;        // [tile][chunk], ntiles + 1 rows
-  hipError_t e;
-  if (nchunks > 0) {
-    hipLaunchKernelGGL(bin_chunk_sort, dim3((unsigned)nchunks), dim3(kBinThreads),
-                       (size_t)4 * (nti + 1) + (size_t)2 * kBinChunk, s, static_cast<const uint2*>(events), n, npix,
-                       nt, u32_div(bin_ps), t0, tp, u32_div((uint32_t)tp), nti, nchunks, runs, start, dropped);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(bin_tile_gather, dim3((unsigned)nti), dim3(kBinGatherThreads), (size_t)4 * tp * nt, s, runs,
-                     start, nchunks, npix, nt, tp, hist, accumulate);
+  BinRuns r;
+  const hipError_t e = bin_sort(events, n, dropped, npix, nt, nt, kBinTileWords, bin_ps, t0, ws, s, &r);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(bin_tile_gather, dim3((unsigned)r.ntiles), dim3(kBinGatherThreads), (size_t)4 * r.tp * nt, s,
+                     r.runs, r.start, r.nchunks, r.chunk, npix, nt, r.tp, hist, accumulate);
+  return hipGetLastError();
+}
+
+size_t phasor_table(int nt, int nf, const int* bins, const float2* lut, float* tab) {
+  const int nsteps = (nt + 3) / 4, nrb = (2 * nf + 15) / 16;
+  if (tab != nullptr)
+    for (int rb = 0; rb < nrb; ++rb)
+      for (int q = 0; q < nsteps; ++q)
+        for (int l = 0; l < 64; ++l) {
+          const int c = rb * 16 + l % 16, b = 4 * q + l / 16;
+          const float2 w = c < 2 * nf && b < nt ? lut[((long long)bins[c / 2] * b) % nt] : make_float2(0.f, 0.f);
+          *tab++ = c % 2 ? w.y : w.x;
+        }
+  return (size_t)nrb * nsteps * 64;
+}
+
+hipError_t launch_phasor_tiled(const void* events, unsigned long long n, float2* P, unsigned long long* dropped,
+                               int npix, int nt, uint32_t bin_ps, uint32_t t0, const float* tab, int nf,
+                               int accumulate, void* ws, hipStream_t s) {
+  const int stride = phasor_stride(nt);
+  BinRuns r;
+  const hipError_t e = bin_sort(events, n, dropped, npix, nt, stride, phasor_words(stride), bin_ps, t0, ws, s, &r);
+  if (e != hipSuccess) return e;
+  const size_t lds = std::max((size_t)4 * r.tp * stride, (size_t)1024 * kPhasorWaves);
+  hipLaunchKernelGGL(bin_tile_phasor, dim3((unsigned)r.ntiles), dim3(kBinGatherThreads), lds, s, r.runs, r.start,
+                     r.nchunks, r.chunk, npix, nt, r.tp, stride, tab, nf, reinterpret_cast<float*>(P), accumulate);
   return hipGetLastError();
 }
 

@@ -451,6 +451,20 @@ static nlos_status get_workspace(nlos_ctx* ctx, void* d_ws, size_t ws_bytes, siz
   return NLOS_OK;
 }
 
+// The context pool with room for `need` bytes, for a path that has another to fall back on:
+// false (no error) while the stream is captured (a graph must not hold the pool's address) or
+// when the pool cannot grow.
+static bool pool_at_hand(nlos_ctx* ctx, size_t need, void** out) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const std::string err = ctx->err;
+  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+      get_workspace(ctx, nullptr, 0, need, out) == NLOS_OK)
+    return true;
+  (void)hipGetLastError();
+  ctx->err = err;
+  return false;
+}
+
 // ---------------------------------------------------------------------------
 // binning
 // ---------------------------------------------------------------------------
@@ -524,12 +538,16 @@ nlos_status nlos_counts_to_float(nlos_ctx* ctx, const uint32_t* d_hist, float* d
 // phasor binning (Section 4.1)
 // ---------------------------------------------------------------------------
 
+// Floats of the largest operand table a phasor plan holds (16 MB: 1024 frequencies of 2048 bins)
+constexpr size_t kMaxPhasorTable = size_t(4) << 20;
+
 struct nlos_phasor_plan {
   nlos_bin_desc d{};
   int device = 0;
   int nf = 0;
   float2* d_lut = nullptr;  // W_nt^m, m < nt (FP64-generated)
   int* d_bins = nullptr;
+  float* d_tab = nullptr;   // operands of the tiled path (null: too many bins, never taken)
 };
 
 nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan* p) {
@@ -537,6 +555,7 @@ nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan* p) {
   (void)hipSetDevice(p->device);
   if (p->d_lut) (void)hipFree(p->d_lut);
   if (p->d_bins) (void)hipFree(p->d_bins);
+  if (p->d_tab) (void)hipFree(p->d_tab);
   delete p;
   return NLOS_OK;
 }
@@ -568,6 +587,13 @@ nlos_status nlos_phasor_plan_create(nlos_ctx* ctx, const nlos_bin_desc* d, int n
     if (e == hipSuccess) e = nlos::dev_alloc((void**)&p->d_bins, n_freq * sizeof(int));
     if (e == hipSuccess) e = hipMemcpy(p->d_lut, lut.data(), lut.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_bins, freq_bin, n_freq * sizeof(int), hipMemcpyHostToDevice);
+    const size_t ntab = nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), nullptr);
+    if (e == hipSuccess && ntab <= kMaxPhasorTable) {
+      std::vector<float> tab(ntab);
+      nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), tab.data());
+      e = nlos::dev_alloc((void**)&p->d_tab, ntab * sizeof(float));
+      if (e == hipSuccess) e = hipMemcpy(p->d_tab, tab.data(), ntab * sizeof(float), hipMemcpyHostToDevice);
+    }
     if (e != hipSuccess) {
       nlos_phasor_plan_destroy(p);
       return fail(ctx, NLOS_ERR_DEVICE, "phasor_plan_create: %s", hipGetErrorString(e));
@@ -590,6 +616,27 @@ nlos_status nlos_phasor_bin(nlos_ctx* ctx, const nlos_phasor_plan* p, const nlos
   HIP_TRY(ctx, hipSetDevice(ctx->device));
   const nlos_bin_desc& d = p->d;
   const size_t nval = 2 * (size_t)d.nx * d.ny * p->nf;
+  // By pixel tiles (nlos_bin's runs, then each tile's DFT) except for few events on a large
+  // plan: the tiles cost their DFT, about 1.3e13 (pixel, bin, frequency) products a second,
+  // the events' float atomics 1.34e11 adds a second (97 products each) and 20 us more to
+  // start (2.6e8 products).  Measured: 1e6 events at 64x64x512 with 39 frequencies 39 us by
+  // tiles, 590 by atomics; 3e4 events 22 and 41; 1e4 events at 128x128x1024 with 129
+  // frequencies 190 and 103.
+  const double products = (double)d.nx * d.ny * d.nt * p->nf;
+  const bool tiles = products <= 2.6e8 + 97.0 * (double)n_events * p->nf;
+  const size_t wsb = p->d_tab ? nlos::phasor_workspace_bytes(d.nx * d.ny, d.nt, n_events) : 0;
+  void* ws = nullptr;
+  if (wsb > 0 && tiles && pool_at_hand(ctx, wsb, &ws)) {
+    if (d_dropped && !d.accumulate)
+      HIP_TRY(ctx, timed(ctx, NLOS_PASS_FILL, [&] {
+        return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(d_dropped), 2, 0u, ctx->stream);
+      }));
+    HIP_TRY(ctx, timed(ctx, NLOS_PASS_PHASOR_BIN, [&] {
+      return nlos::launch_phasor_tiled(d_events, n_events, reinterpret_cast<float2*>(d_phasor), d_dropped, d.nx * d.ny,
+                                       d.nt, d.bin_ps, d.t0_ps, p->d_tab, p->nf, d.accumulate, ws, ctx->stream);
+    }));
+    return NLOS_OK;
+  }
   if (!d.accumulate) {
     HIP_TRY(ctx, timed(ctx, NLOS_PASS_FILL, [&] { return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(d_phasor), nval, 0u, ctx->stream); }));
     if (d_dropped)

@@ -277,6 +277,15 @@ hipError_t launch_bin(const void* events, unsigned long long n, uint32_t* hist,
 size_t bin_workspace_bytes(int npix, int nt, unsigned long long n);
 hipError_t launch_bin_tiled(const void* events, unsigned long long n, uint32_t* hist, unsigned long long* dropped,
                             int npix, int nt, uint32_t bin_ps, uint32_t t0, int accumulate, void* ws, hipStream_t s);
+// The same runs, then per tile the DFT of its histogram at the plan's nf bins (nt <= 2048; tab
+// from phasor_table): every P[pixel][f] is written (added to when accumulate).  Workspace ws
+// of phasor_workspace_bytes (0: does not apply to this shape).
+size_t phasor_workspace_bytes(int npix, int nt, unsigned long long n);
+// host: the DFT operands of the bins from lut = W_nt^m (tab null: their number of floats only)
+size_t phasor_table(int nt, int nf, const int* bins, const float2* lut, float* tab);
+hipError_t launch_phasor_tiled(const void* events, unsigned long long n, float2* P, unsigned long long* dropped,
+                               int npix, int nt, uint32_t bin_ps, uint32_t t0, const float* tab, int nf,
+                               int accumulate, void* ws, hipStream_t s);
 // P[pixel][f] += W_nt^(bins[f] b) per valid event (nt <= 2048, lut = W_nt^m, m < nt)
 hipError_t launch_phasor_bin(const void* events, unsigned long long n, float2* P, unsigned long long* dropped,
                              int npix, int nt, uint32_t bin_ps, uint32_t t0, const float2* lut, const int* bins,
