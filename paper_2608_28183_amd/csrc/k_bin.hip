@@ -127,24 +127,25 @@ hipError_t launch_bin(const void* events, unsigned long long n, uint32_t* hist,
 // The histogram (8 MiB at 64 x 64 x 512) is far larger than LDS, and device-scope atomics
 // each reach the memory side, so the counters are privatised per tile of tp pixels (tp nt
 // counters, at most 16 KB of LDS), in two passes with no global atomics:
-// (1) each block takes a chunk of kBinChunk events and sorts it by tile in LDS (per-tile
-//     counts, their scan, placement), then writes it back as runs of 16-bit codes
-//     (pixel in tile) nt + bin, one run per tile, with the start of every run in a table
-//     start[tile][chunk] (start[ntiles][chunk]: the chunk's valid events);
+// (1) each block takes a chunk of events and sorts it by tile in LDS (per-tile counts, their
+//     scan, placement), then writes it back as runs of 16-bit codes (pixel in tile) nt + bin,
+//     one run per tile, with the start of every run in a table start[chunk][tile]
+//     (start[chunk][ntiles]: the chunk's valid events);
 // (2) one block per tile gathers its runs from every chunk, histograms them in LDS and
 //     writes the tile's rows with plain stores (all of them, so no clearing pass).
 // Events are read once; all adds are integer adds, so the histogram is exact and does not
-// depend on the order in which the LDS atomics land.
+// depend on the order in which the LDS atomics land.  Both passes wait on latency (the loads,
+// the LDS atomics) more than on the 108 MB they move at 1e7 events and 64 x 64 x 512: 31 and
+// 24 us, 54 in all against 104 before with scattered reflecting points (the gather searched
+// and walked a flat range of all runs per element; see also count_dropped).
 
 constexpr int kBinThreads = 256;
 // tp nt <= kBinTileWords (codes fit 16 bits).  At 64 x 64 x 512 with 1e7 events, tiles of
-// 4096 words (512 tiles) measured 0.066 ms, of 8192 words 0.074 ms (the gather's time is
-// its busiest tile's: fewer, larger tiles balance worse) and of 2048 words 0.080 ms.
+// 4096 words (512 tiles) measured faster than 8192 words (0.066 to 0.074 ms; the gather's time is
+// its busiest tile's: fewer, larger tiles balance worse) and 2048 words (0.080 ms).
 constexpr int kBinTileWords = 4096;
 constexpr int kBinMaxTiles = 8192;
 constexpr int kBinGatherThreads = 1024;
-constexpr int kBinGroup = 2048;  // chunks whose runs pass 2 gathers per round
-constexpr int kBinBatch = 8;     // loads in flight per lane
 
 // Quotient of a u32 by a divisor fixed for the launch: a multiply-high and two shifts with
 // constants computed on the host (Granlund and Montgomery's division by invariant integers,
@@ -186,12 +187,12 @@ __device__ __forceinline__ uint32_t lds_count(uint32_t* cnt, int key) {
   const int lane = threadIdx.x & 63;
   const unsigned long long act = __ballot(key >= 0);
   if (act == 0ull) return 0;
-  const int leader = __ffsll((long long)act) - 1;
-  const int lk = __shfl(key, leader);
+  const int leader = __builtin_amdgcn_readfirstlane(__ffsll((long long)act) - 1);
+  const int lk = __builtin_amdgcn_readlane(key, leader);
   if (__ballot(key >= 0 && key == lk) == act) {
     uint32_t base = 0;
     if (lane == leader) base = atomicAdd(cnt + lk, (uint32_t)__popcll(act));
-    base = __shfl(base, leader);
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
     return base + (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
   }
   return key >= 0 ? atomicAdd(cnt + key, 1u) : 0u;
@@ -225,15 +226,13 @@ __device__ __forceinline__ void block_exclusive_scan(uint32_t* a, int m, uint32_
 }
 
 // Pass 1: chunk blockIdx.x of kBinThreads PT events -> runs[chunk][.] (16-bit codes
-// (pixel in tile) stride + bin, sorted by tile) and start[tile][chunk]; invalid events are
-// counted into *dropped.
+// (pixel in tile) stride + bin, sorted by tile) and start[chunk][tile].
 template <int PT>
 __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __restrict__ ev, unsigned long long n,
                                                              int npix, int nt, U32Div bin_ps, uint32_t t0, int tp,
                                                              int stride, U32Div tp_div,
-                                                             int ntiles, int nchunks, uint16_t* __restrict__ runs,
-                                                             uint16_t* __restrict__ start,
-                                                             unsigned long long* __restrict__ dropped) {
+                                                             int ntiles, uint16_t* __restrict__ runs,
+                                                             uint16_t* __restrict__ start) {
   extern __shared__ uint32_t sh[];
   uint32_t* cnt = sh;  // ntiles + 1 counters, then their exclusive scan
   uint16_t* sorted = reinterpret_cast<uint16_t*>(sh + ntiles + 1);  // the codes
@@ -243,7 +242,6 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
   const unsigned long long beg = (unsigned long long)blockIdx.x * (kBinThreads * PT);
   uint32_t code[PT];  // tile << 16 | (pixel in tile) nt + bin; ~0u: none
   uint32_t pos[PT];   // place in the tile's run
-  unsigned int drop = 0;
   constexpr int kLoads = PT < 16 ? PT : 16;  // loads in flight per lane
 #pragma unroll
   for (int r = 0; r < PT; r += kLoads) {
@@ -251,21 +249,16 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
       const unsigned long long k = beg + (unsigned long long)(r + j) * kBinThreads + threadIdx.x;
-      e[j] = k < n ? ev[k] : make_uint2(0u, 0u);
+      e[j] = k < n ? ev[k] : make_uint2(0xffffffffu, 0u);  // (pixel -1: no event)
     }
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-      const unsigned long long k = beg + (unsigned long long)(r + j) * kBinThreads + threadIdx.x;
       uint32_t c = ~0u;
-      if (k < n) {
-        int b = 0;
-        const int px = bin_event(e[j], npix, nt, bin_ps, t0, &b);
-        if (px >= 0) {
-          const int tile = (int)u32_quot((uint32_t)px, tp_div);
-          c = ((uint32_t)tile << 16) | (uint32_t)((px - tile * tp) * stride + b);
-        } else {
-          ++drop;
-        }
+      int b = 0;
+      const int px = bin_event(e[j], npix, nt, bin_ps, t0, &b);
+      if (px >= 0) {
+        const int tile = (int)u32_quot((uint32_t)px, tp_div);
+        c = ((uint32_t)tile << 16) | (uint32_t)((px - tile * tp) * stride + b);
       }
       code[r + j] = c;
       pos[r + j] = lds_count(cnt, c == ~0u ? -1 : (int)(c >> 16));
@@ -275,7 +268,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
   block_exclusive_scan<kBinThreads>(cnt, ntiles + 1, wsum);
   __syncthreads();
   for (int i = threadIdx.x; i <= ntiles; i += kBinThreads)
-    start[(size_t)i * nchunks + blockIdx.x] = (uint16_t)cnt[i];
+    start[(size_t)blockIdx.x * (ntiles + 1) + i] = (uint16_t)cnt[i];
 #pragma unroll
   for (int j = 0; j < PT; ++j)
     if (code[j] != ~0u) sorted[cnt[code[j] >> 16] + pos[j]] = (uint16_t)(code[j] & 0xffffu);
@@ -283,78 +276,81 @@ __global__ __launch_bounds__(kBinThreads) void bin_chunk_sort(const uint2* __res
   const uint32_t nv = cnt[ntiles];
   uint16_t* out = runs + (size_t)blockIdx.x * (kBinThreads * PT);
   for (uint32_t i = threadIdx.x; i < nv; i += kBinThreads) out[i] = sorted[i];
-  if (dropped != nullptr) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) drop += __shfl_xor(drop, off, 64);
-    if ((threadIdx.x & 63) == 0 && drop != 0) atomicAdd(dropped, (unsigned long long)drop);
-  }
 }
 
-// Pass 2 for one tile and a block: its runs from kBinGroup chunks at a time are laid end to
-// end (exclusive scan of their lengths); lane i of the flat range finds its chunk by binary
-// search and counts its code in the tile's histogram h (`words` counters in LDS, cleared here).
+// Pass 2 for one tile and a block of NT threads: counts its codes of every chunk's run in the
+// tile's histogram h (`words` counters in LDS, cleared here).  Groups of 1 << lw lanes take a
+// run each, kBinRuns runs in flight: their bounds, then their codes, then the counts.
+constexpr int kBinRuns = 4;
+template <int NT>
 __device__ __forceinline__ void gather_tile(const uint16_t* __restrict__ runs, const uint16_t* __restrict__ start,
-                                            int nchunks, int chunk, int t, uint32_t* h, int words) {
-  __shared__ uint32_t rbeg[kBinGroup];
-  __shared__ uint32_t rpre[kBinGroup + 1];
-  __shared__ uint32_t wsum[kBinGatherThreads / 64];
-  for (int i = threadIdx.x; i < words; i += kBinGatherThreads) h[i] = 0;
-  for (int c0 = 0; c0 < nchunks; c0 += kBinGroup) {
-    const int g = nchunks - c0 < kBinGroup ? nchunks - c0 : kBinGroup;
-    __syncthreads();  // h cleared, the previous round's readers of rbeg / rpre done
-    for (int k = threadIdx.x; k < g; k += kBinGatherThreads) {
-      const uint32_t b = start[(size_t)t * nchunks + c0 + k];
-      rbeg[k] = b;
-      rpre[k] = (uint32_t)start[(size_t)(t + 1) * nchunks + c0 + k] - b;
+                                            int ntiles, int nchunks, int chunk, int t, uint32_t* h, int words, int lw) {
+  for (int i = threadIdx.x; i < words; i += NT) h[i] = 0;
+  __syncthreads();
+  const int W = 1 << lw, groups = NT >> lw;
+  const int g = threadIdx.x >> lw, l = threadIdx.x & (W - 1);
+  for (int k0 = 0; k0 < nchunks; k0 += groups * kBinRuns) {
+    uint32_t i[kBinRuns], e[kBinRuns];
+    const uint16_t* run[kBinRuns];
+#pragma unroll
+    for (int u = 0; u < kBinRuns; ++u) {
+      const int k = k0 + u * groups + g;
+      const int kc = k < nchunks ? k : 0;
+      const uint16_t* st = start + (size_t)kc * (ntiles + 1) + t;
+      i[u] = st[0] + l;
+      e[u] = k < nchunks ? st[1] : 0;
+      run[u] = runs + (size_t)kc * chunk;
     }
-    if (threadIdx.x == 0) rpre[g] = 0;
-    __syncthreads();
-    block_exclusive_scan<kBinGatherThreads>(rpre, g + 1, wsum);
-    __syncthreads();
-    const uint32_t total = rpre[g];
-    int top = 1;  // largest power of two below g (g >= 1)
-    while (2 * top < g) top <<= 1;
-    // a batch covers kBinGatherThreads kBinBatch flat elements; wave w takes the 64 kBinBatch
-    // of them from ew on, lane l element ew + 64 j + l at step j
-    const int lane = threadIdx.x & 63;
-    for (uint32_t b0 = 0; b0 < total; b0 += kBinGatherThreads * kBinBatch) {
-      const uint32_t ew = b0 + (uint32_t)(threadIdx.x >> 6) * (64 * kBinBatch);
-      // the chunk whose run holds element ew (the last k with rpre[k] <= ew): one search
-      // per wave, on wave-uniform values
-      int k = 0;
-      for (int step = top; step > 0; step >>= 1) {
-        const int m = k + step;
-        if (m < g && (uint32_t)__builtin_amdgcn_readfirstlane((int)rpre[m]) <= ew) k = m;
-      }
-      uint32_t v[kBinBatch];
+    bool more = true;
+    while (more) {  // (the wave's longest run)
+      uint32_t v[kBinRuns];
+      more = false;
 #pragma unroll
-      for (int j = 0; j < kBinBatch; ++j) {
-        const uint32_t i = ew + (uint32_t)(64 * j + lane);
-        v[j] = 0xffffu;
-        if (i < total) {
-          // elements only grow with j: walk on to the run that holds i (rpre[g] = total > i
-          // stops the walk at k = g - 1 at the latest)
-          while (rpre[k + 1] <= i) ++k;
-          v[j] = runs[(size_t)(c0 + k) * chunk + rbeg[k] + (i - rpre[k])];
-        }
+      for (int u = 0; u < kBinRuns; ++u) {
+        v[u] = i[u] < e[u] ? run[u][i[u]] : 0xffffu;
+        i[u] += W;
+        more |= i[u] < e[u];
       }
 #pragma unroll
-      for (int j = 0; j < kBinBatch; ++j) lds_count(h, v[j] == 0xffffu ? -1 : (int)v[j]);
+      for (int u = 0; u < kBinRuns; ++u) lds_count(h, v[u] == 0xffffu ? -1 : (int)v[u]);
+      more = __ballot(more) != 0ull;
     }
   }
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint16_t* __restrict__ runs,
-                                                                    const uint16_t* __restrict__ start,
-                                                                    int nchunks, int chunk, int npix, int nt, int tp,
-                                                                    uint32_t* __restrict__ hist, int accumulate) {
+// Invalid events: n less the chunks' valid ones, by the block of tile 0 (an atomic per wave of
+// pass 1 on the one counter took 45 us of 1e7 events).
+template <int NT>
+__device__ __forceinline__ void count_dropped(const uint16_t* __restrict__ start, int ntiles, int nchunks,
+                                              unsigned long long n, unsigned long long* dropped, int accumulate) {
+  if (blockIdx.x != 0 || dropped == nullptr) return;
+  __shared__ unsigned int part[NT / 64];
+  unsigned int v = 0;  // n < 2^31
+  for (int k = threadIdx.x; k < nchunks; k += NT) v += start[(size_t)k * (ntiles + 1) + ntiles];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  unsigned long long d = n;
+  for (int w = 0; w < NT / 64; ++w) d -= part[w];
+  *dropped = accumulate ? *dropped + d : d;
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void bin_tile_gather(const uint16_t* __restrict__ runs,
+                                                      const uint16_t* __restrict__ start, int ntiles, int nchunks,
+                                                      int chunk, int npix, int nt, int tp, int lw,
+                                                      uint32_t* __restrict__ hist, int accumulate,
+                                                      unsigned long long n, unsigned long long* dropped) {
   extern __shared__ uint32_t h[];  // tp nt counters
   const int words = tp * nt;
-  gather_tile(runs, start, nchunks, chunk, blockIdx.x, h, words);
+  count_dropped<NT>(start, ntiles, nchunks, n, dropped, accumulate);
+  gather_tile<NT>(runs, start, ntiles, nchunks, chunk, blockIdx.x, h, words, lw);
   const long long first = (long long)blockIdx.x * tp * nt;
   const long long last = (long long)npix * nt;
-  for (int i = threadIdx.x; i < words && first + i < last; i += kBinGatherThreads) {
+  for (int i = threadIdx.x; i < words && first + i < last; i += NT) {
     uint32_t* g = hist + first + i;
     *g = accumulate ? *g + h[i] : h[i];
   }
@@ -372,14 +368,17 @@ __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_gather(const uint1
 typedef float bin_f4 __attribute__((ext_vector_type(4)));
 constexpr int kPhasorWaves = kBinGatherThreads / 64;
 __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_phasor(const uint16_t* __restrict__ runs,
-                                                                    const uint16_t* __restrict__ start,
+                                                                    const uint16_t* __restrict__ start, int ntiles,
                                                                     int nchunks, int chunk, int npix, int nt, int tp,
-                                                                    int stride, const float* __restrict__ tab, int nf,
-                                                                    float* __restrict__ P, int accumulate) {
+                                                                    int lw, int stride, const float* __restrict__ tab,
+                                                                    int nf, float* __restrict__ P, int accumulate,
+                                                                    unsigned long long n,
+                                                                    unsigned long long* dropped) {
   extern __shared__ uint32_t h[];  // tp stride counters, later the partial sums [wave][256]
   const int words = tp * stride;
   float* red = reinterpret_cast<float*>(h);
-  gather_tile(runs, start, nchunks, chunk, blockIdx.x, h, words);
+  count_dropped<kBinGatherThreads>(start, ntiles, nchunks, n, dropped, accumulate);
+  gather_tile<kBinGatherThreads>(runs, start, ntiles, nchunks, chunk, blockIdx.x, h, words, lw);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c16 = lane & 15, kq = lane >> 4;
   const int pix0 = blockIdx.x * tp;
@@ -424,16 +423,17 @@ __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_phasor(const uint1
   }
 }
 
-// Events per thread of pass 1 (a chunk is kBinThreads times as many): short jobs of few tiles
-// want more blocks (1e4 events 15 us against 23 at 64 x 64 x 512); from there on the gather's
-// cost is its number of runs (1e6 events 36 us against 56)
-int bin_per_thread(unsigned long long n, int ntiles) { return n >= (1ull << 18) || ntiles > 1024 ? 32 : 8; }
+// Events per thread of pass 1 (a chunk is kBinThreads times as many): short jobs want more blocks
+// (1e4 events at 64 x 64 x 512: 11, 13 and 18 us with 8, 16 and 32), long ones longer runs
+// (1e7: 72, 58 and 54; 3e6 at 200 x 200 x 512: 85, 61 and 52)
+int bin_per_thread(unsigned long long n) { return n < 400000 ? 8 : n < 1500000 ? 16 : 32; }
 
 // Tile layout of a binning job: tp pixels of `stride` words per tile (tp stride <= words), or
 // false when the tiled path does not apply (then the per-event atomic kernel runs).
-bool bin_tiles(int npix, int stride, unsigned long long n, int words, int* tp, int* ntiles) {
+// Small images keep at least `least` pixels a tile, for blocks enough to fill the device.
+bool bin_tiles(int npix, int stride, unsigned long long n, int words, int least, int* tp, int* ntiles) {
   if (stride > words || n >= (1ull << 31)) return false;
-  *tp = words / stride;
+  *tp = std::min(words / stride, std::max(npix / 512, least));
   if (*tp > npix) *tp = npix;
   *ntiles = (npix + *tp - 1) / *tp;
   return *ntiles <= kBinMaxTiles;
@@ -445,55 +445,61 @@ int phasor_words(int stride) { return std::min(std::max(16 * 516, 16 * stride), 
 int phasor_stride(int nt) { return (nt + 59) / 64 * 64 + 4; }
 
 size_t bin_runs_bytes(unsigned long long n, int ntiles) {
-  const size_t chunk = (size_t)kBinThreads * bin_per_thread(n, ntiles);
+  const size_t chunk = (size_t)kBinThreads * bin_per_thread(n);
   const size_t nchunks = (size_t)((n + chunk - 1) / chunk);
   const size_t bytes = 2 * nchunks * chunk + 2 * (size_t)(ntiles + 1) * nchunks;
   return bytes > 0 ? bytes : 256;  // never zero: zero means "not tiled"
 }
 size_t bin_workspace_bytes(int npix, int nt, unsigned long long n) {
   int tp = 0, nti = 0;
-  return bin_tiles(npix, nt, n, kBinTileWords, &tp, &nti) ? bin_runs_bytes(n, nti) : 0;
+  return bin_tiles(npix, nt, n, kBinTileWords, 1, &tp, &nti) ? bin_runs_bytes(n, nti) : 0;
 }
 size_t phasor_workspace_bytes(int npix, int nt, unsigned long long n) {
   int tp = 0, nti = 0;
-  return bin_tiles(npix, phasor_stride(nt), n, phasor_words(phasor_stride(nt)), &tp, &nti) ? bin_runs_bytes(n, nti) : 0;
+  return bin_tiles(npix, phasor_stride(nt), n, phasor_words(phasor_stride(nt)), 16, &tp, &nti) ? bin_runs_bytes(n, nti) : 0;
 }
 
 namespace {
 // The tiles of a job and its sorted runs in ws (pass 1 launched)
 struct BinRuns {
   int tp, ntiles, nchunks, chunk;
+  int lw;           // log2 of the lanes that gather a run: about its mean length, 4 .. 64
   uint16_t* runs;   // [chunk][.]
-  uint16_t* start;  // [tile][chunk], ntiles + 1 rows
+  uint16_t* start;  // [chunk][tile], ntiles + 1 a row
 };
-hipError_t bin_sort(const void* events, unsigned long long n, unsigned long long* dropped, int npix, int nt,
-                    int stride, int words, uint32_t bin_ps, uint32_t t0, void* ws, hipStream_t s, BinRuns* r) {
-  if (!bin_tiles(npix, stride, n, words, &r->tp, &r->ntiles)) return hipErrorInvalidValue;
-  const int pt = bin_per_thread(n, r->ntiles);
+hipError_t bin_sort(const void* events, unsigned long long n, int npix, int nt,
+                    int stride, int words, int least, uint32_t bin_ps, uint32_t t0, void* ws, hipStream_t s,
+                    BinRuns* r) {
+  if (!bin_tiles(npix, stride, n, words, least, &r->tp, &r->ntiles)) return hipErrorInvalidValue;
+  const int pt = bin_per_thread(n);
   r->chunk = kBinThreads * pt;
   r->nchunks = (int)((n + r->chunk - 1) / r->chunk);
   r->runs = static_cast<uint16_t*>(ws);
   r->start = r->runs + (size_t)r->nchunks * r->chunk;
+  r->lw = 2;
+  while (r->lw < 6 && r->chunk / r->ntiles >= (2 << r->lw)) ++r->lw;
   if (r->nchunks == 0) return hipSuccess;
   auto go = [&](auto k) {
     hipLaunchKernelGGL(k, dim3((unsigned)r->nchunks), dim3(kBinThreads),
                        (size_t)4 * (r->ntiles + 1) + (size_t)2 * r->chunk, s, static_cast<const uint2*>(events), n,
-                       npix, nt, u32_div(bin_ps), t0, r->tp, stride, u32_div((uint32_t)r->tp), r->ntiles, r->nchunks, r->runs,
-                       r->start, dropped);
+                       npix, nt, u32_div(bin_ps), t0, r->tp, stride, u32_div((uint32_t)r->tp), r->ntiles, r->runs, r->start);
     return hipGetLastError();
   };
-  return pt == 32 ? go(bin_chunk_sort<32>) : go(bin_chunk_sort<8>);
+  return pt == 32 ? go(bin_chunk_sort<32>) : pt == 16 ? go(bin_chunk_sort<16>) : go(bin_chunk_sort<8>);
 }
 }  // namespace
 
 hipError_t launch_bin_tiled(const void* events, unsigned long long n, uint32_t* hist, unsigned long long* dropped,
                             int npix, int nt, uint32_t bin_ps, uint32_t t0, int accumulate, void* ws, hipStream_t s) {
   BinRuns r;
-  const hipError_t e = bin_sort(events, n, dropped, npix, nt, nt, kBinTileWords, bin_ps, t0, ws, s, &r);
+  const hipError_t e = bin_sort(events, n, npix, nt, nt, kBinTileWords, 1, bin_ps, t0, ws, s, &r);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(bin_tile_gather, dim3((unsigned)r.ntiles), dim3(kBinGatherThreads), (size_t)4 * r.tp * nt, s,
-                     r.runs, r.start, r.nchunks, r.chunk, npix, nt, r.tp, hist, accumulate);
-  return hipGetLastError();
+  auto go = [&](auto k, int threads) {
+    hipLaunchKernelGGL(k, dim3((unsigned)r.ntiles), dim3(threads), (size_t)4 * r.tp * nt, s, r.runs, r.start, r.ntiles,
+                       r.nchunks, r.chunk, npix, nt, r.tp, r.lw, hist, accumulate, n, dropped);
+    return hipGetLastError();
+  };
+  return r.ntiles >= 1024 && n / r.ntiles < 4096 ? go(bin_tile_gather<256>, 256) : go(bin_tile_gather<kBinGatherThreads>, kBinGatherThreads);
 }
 
 size_t phasor_table(int nt, int nf, const int* bins, const float2* lut, float* tab) {
@@ -514,11 +520,12 @@ hipError_t launch_phasor_tiled(const void* events, unsigned long long n, float2*
                                int accumulate, void* ws, hipStream_t s) {
   const int stride = phasor_stride(nt);
   BinRuns r;
-  const hipError_t e = bin_sort(events, n, dropped, npix, nt, stride, phasor_words(stride), bin_ps, t0, ws, s, &r);
+  const hipError_t e = bin_sort(events, n, npix, nt, stride, phasor_words(stride), 16, bin_ps, t0, ws, s, &r);
   if (e != hipSuccess) return e;
   const size_t lds = std::max((size_t)4 * r.tp * stride, (size_t)1024 * kPhasorWaves);
   hipLaunchKernelGGL(bin_tile_phasor, dim3((unsigned)r.ntiles), dim3(kBinGatherThreads), lds, s, r.runs, r.start,
-                     r.nchunks, r.chunk, npix, nt, r.tp, stride, tab, nf, reinterpret_cast<float*>(P), accumulate);
+                     r.ntiles, r.nchunks, r.chunk, npix, nt, r.tp, r.lw, stride, tab, nf, reinterpret_cast<float*>(P), accumulate,
+                     n, dropped);
   return hipGetLastError();
 }
 

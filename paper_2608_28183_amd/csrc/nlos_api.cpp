@@ -500,10 +500,6 @@ nlos_status nlos_bin(nlos_ctx* ctx, const nlos_bin_desc* d, const nlos_event* d_
     void* ws = nullptr;
     nlos_status st2 = get_workspace(ctx, nullptr, 0, wsb, &ws);
     if (st2 != NLOS_OK) return st2;
-    if (d_dropped && !d->accumulate)
-      HIP_TRY(ctx, timed(ctx, NLOS_PASS_FILL, [&] {
-        return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(d_dropped), 2, 0u, ctx->stream);
-      }));
     HIP_TRY(ctx, timed(ctx, NLOS_PASS_BIN, [&] {
       return nlos::launch_bin_tiled(d_events, n_events, d_hist, d_dropped, npix, d->nt, d->bin_ps, d->t0_ps,
                                     d->accumulate, ws, ctx->stream);
@@ -627,10 +623,6 @@ nlos_status nlos_phasor_bin(nlos_ctx* ctx, const nlos_phasor_plan* p, const nlos
   const size_t wsb = p->d_tab ? nlos::phasor_workspace_bytes(d.nx * d.ny, d.nt, n_events) : 0;
   void* ws = nullptr;
   if (wsb > 0 && tiles && pool_at_hand(ctx, wsb, &ws)) {
-    if (d_dropped && !d.accumulate)
-      HIP_TRY(ctx, timed(ctx, NLOS_PASS_FILL, [&] {
-        return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(d_dropped), 2, 0u, ctx->stream);
-      }));
     HIP_TRY(ctx, timed(ctx, NLOS_PASS_PHASOR_BIN, [&] {
       return nlos::launch_phasor_tiled(d_events, n_events, reinterpret_cast<float2*>(d_phasor), d_dropped, d.nx * d.ny,
                                        d.nt, d.bin_ps, d.t0_ps, p->d_tab, p->nf, d.accumulate, ws, ctx->stream);
