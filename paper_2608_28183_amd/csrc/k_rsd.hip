@@ -10,9 +10,11 @@
 // are the same for the whole wave, so they come in through the scalar unit and enter the
 // FMAs as scalar operands, and each kernel value is loaded once per 64 pixels.  The
 // lane's own phasor P^[pix][f] is read from its contiguous frequency row.  Every C
-// element is produced by one lane in a fixed frequency order.
+// element is produced by one lane in a fixed frequency order.  This form (FP32 FMAs) runs
+// on request only; the matrix cores below are the default.
 #include <hip/hip_fp16.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "mfma_fft.hpp"
@@ -24,12 +26,20 @@ constexpr int kGroupPix = 64;   // pixels per chunk (one per lane; matches the p
 constexpr int kDepths = 8;      // depths per wave
 constexpr int kWavesPerBlock = 4;
 
+// K_r[i][f][d] from the plan's table (see RsdPropArgs::Kr); FP32 is the exact sum of its three
+// bfloat16 planes
 template <int SP>
-__device__ __forceinline__ float2 load_kr(const void* __restrict__ kr, long long i) {
+__device__ __forceinline__ float2 load_kr(const RsdPropArgs& a, int i, int f, int d) {
+  constexpr int FL = SP == SP_F32 ? 4 : 2;
+  const int ng = 8 / FL * ((a.Nf + 7) / 8);
+  const long long o = (((long long)i * ng + f / FL) * a.Nd + d) * FL + f % FL;
+  const unsigned int* kr = static_cast<const unsigned int*>(a.Kr);
   if constexpr (SP == SP_F32) {
-    return static_cast<const float2*>(kr)[i];
+    using M = Mfma<SP_BF16>;
+    const float2 k0 = M::unpack(kr[o]), k1 = M::unpack(kr[o + a.kr_plane]), k2 = M::unpack(kr[o + 2 * a.kr_plane]);
+    return make_float2((k2.x + k1.x) + k0.x, (k2.y + k1.y) + k0.y);
   } else {
-    return Mfma<SP>::unpack(static_cast<const unsigned int*>(kr)[i]);
+    return Mfma<SP>::unpack(kr[o]);
   }
 }
 
@@ -42,13 +52,14 @@ __device__ __forceinline__ void cmac2(float2& acc, float2 pa, float2 k0, float2 
 // One frequency f of the lane's pixel: tap-weighted phasors, then the ND depths of the
 // wave's slice (kernel rows o0, o1 are wave-uniform).
 template <int SP, int ND>
-__device__ __forceinline__ void rsd_freq(float2* acc, float2 p, float2 wf, float wa, float wb, const void* kr,
-                                         long long o0, long long o1) {
+__device__ __forceinline__ void rsd_freq(float2* acc, float2 p, float2 wf, float wa, float wb, const RsdPropArgs& a,
+                                         int i0, int i1, int f, int d0) {
   const float2 pw = make_float2(p.x * wf.x - p.y * wf.y, p.x * wf.y + p.y * wf.x);
   const float2 pa = make_float2(pw.x * wa, pw.y * wa);
   const float2 pb = make_float2(pw.x * wb, pw.y * wb);
 #pragma unroll
-  for (int j = 0; j < ND; ++j) cmac2(acc[j], pa, load_kr<SP>(kr, o0 + j), pb, load_kr<SP>(kr, o1 + j));
+  for (int j = 0; j < ND; ++j) 
+    cmac2(acc[j], pa, load_kr<SP>(a, i0, f, d0 + j), pb, load_kr<SP>(a, i1, f, d0 + j));
 }
 
 template <int SP>
@@ -73,8 +84,6 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
     const float wa = a.chunk_wa[g * kGroupPix + lane];
     const float wb = a.chunk_wb[g * kGroupPix + lane];
     const float2* __restrict__ ph = static_cast<const float2*>(a.Ph) + (long long)(pix >= 0 ? pix : 0) * a.ph_stride;
-    long long o0 = (long long)i0 * Nf * Nd + d0;
-    long long o1 = (long long)i1 * Nf * Nd + d0;
     if (d0 + kDepths <= Nd) {
       int f = 0;
       // eight phasor loads in flight per lane
@@ -84,15 +93,11 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
         for (int u = 0; u < 8; ++u) p[u] = ph[f + u];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          rsd_freq<SP, kDepths>(acc, p[u], a.w[f + u], wa, wb, a.Kr, o0, o1);
-          o0 += Nd;
-          o1 += Nd;
+          rsd_freq<SP, kDepths>(acc, p[u], a.w[f + u], wa, wb, a, i0, i1, f + u, d0);
         }
       }
       for (; f < Nf; ++f) {
-        rsd_freq<SP, kDepths>(acc, ph[f], a.w[f], wa, wb, a.Kr, o0, o1);
-        o0 += Nd;
-        o1 += Nd;
+        rsd_freq<SP, kDepths>(acc, ph[f], a.w[f], wa, wb, a, i0, i1, f, d0);
       }
     } else {
       // last, partial depth slice
@@ -104,9 +109,7 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
         const float2 pb = make_float2(pw.x * wb, pw.y * wb);
 #pragma unroll
         for (int j = 0; j < kDepths; ++j)
-          if (j < nd) cmac2(acc[j], pa, load_kr<SP>(a.Kr, o0 + j), pb, load_kr<SP>(a.Kr, o1 + j));
-        o0 += Nd;
-        o1 += Nd;
+          if (j < nd) cmac2(acc[j], pa, load_kr<SP>(a, i0, f, d0 + j), pb, load_kr<SP>(a, i1, f, d0 + j));
       }
     }
   }
@@ -118,313 +121,272 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// matrix-core propagation (FP16 / BF16 radial kernel)
+// matrix-core propagation
 // ---------------------------------------------------------------------------
 //
-// For one chunk the sum is a complex matrix product: rows = the chunk's 64 pixels, the
-// contraction runs over (frequency, tap) with the tap-weighted phasors A[p][f, tap] =
-// w_f P^[p][f] (wa | wb)[p] on one side and the kernel rows K_r[i0 | i1][f][d] on the
-// other, columns = depths.  As a real product on (re, im) pairs it maps onto
-// v_mfma_f32_32x32x16 (FP32 accumulate): one 16-wide K step covers 4 frequencies x 2
-// taps x (re, im), lane l holding frequencies 4s + 2(l/32) + {0, 1}.  B comes straight
-// from the stored kernel pairs: (re, -im) for the real part of the output, (im, re) for
-// the imaginary part.  A is rounded to the kernel's format after scaling by a power of two
-// 2^e chosen per chunk from the largest |w_f P^| (wa | wb) of its pixels (a first pass
-// over their rows), so that every component stays below 2^14; the FP32 result is
-// multiplied by 2^-e.  A wave takes one chunk and DT 32-depth tiles.  DATA4: P^ and C are
-// stored in the kernel's four-byte format too (FP16 P^ times 2^e_ph, FP16 C at depth d
-// written times 2^e_c[d]); the chunk scale is then chosen on the stored values and the
-// exponents are folded into one final ldexp.
+// For one chunk the sum is a complex matrix product: rows = the chunk's pixels, the
+// contraction runs over (tap, frequency), columns = depths.  As a real product on (re, im)
+// pairs it maps onto v_mfma_f32_32x32x16 (FP32 accumulation): a 16-wide K step is 8
+// frequencies of one tap (FP32 kernels; lane l holds frequencies 8 s + 4 (l / 32) + 0..3 of
+// row or column l % 32) or 4 frequencies x 2 taps (FP16 / BF16; 4 s + 2 (l / 32) + 0..1).  The
+// kernel operands come as stored pairs from the plan's table, one 16- or 8-byte load a tap and
+// step; the phasors enter as (re, -im) for the real part of the output and (im, re) for the
+// imaginary.
+// A wave takes half a chunk (32 pixels) and DT 32-depth tiles; the loads of the next step are
+// in flight during a step (unconditional, clamped: a frequency beyond Nf has a zero weight, a
+// depth beyond Nd only feeds columns that are not stored).
+//
+// FP16 / BF16 kernels: the phasors w_f P^ (wa | wb) of each tap are rounded to the kernel's
+// format, FP16 after scaling by 2^e, e per half chunk from the largest |w_f P^| max(wa, wb)
+// of its pixels (a first pass over their rows) so that every component stays below 2^14; the
+// FP32 result is multiplied by 2^-e.  BF16 has FP32's exponent range and takes no scale.
+// DATA4: P^ and C are stored in the kernel's four-byte format too (FP16 P^ times 2^e_ph, FP16
+// C at depth d written times 2^e_c[d]), the exponents folded into one final ldexp.
+//
+// FP32 kernels: every FP32 value is the exact sum of three bfloat16 values x0 + x1 + x2 (each
+// the rounded remainder of the previous; 3 x 8 bits), so the product is the sum of the six
+// bfloat16 products of order below 2^-24: a0 b0, a0 b1, a1 b0, a0 b2, a1 b1, a2 b0 (the dropped
+// a1 b2 + a2 b1 are about 2^-26 of it, of random sign).  The kernel's planes come with the
+// plan, the phasors are split in registers; each tap has its own accumulators and the tap
+// weights come last, so the split is paid once.  The sums take 3/8 of the time of FP32 matrix
+// instructions and round less often (once per 16-wide product sum instead of per 2-wide):
+// over the volume within the error of the FP32 instructions against 64 bits.
+//
+// 128 x 128 x 1024 (129 frequencies, 64 depths; 8.7 GFLOP): FP32 131 -> 76 us, BF16 77 -> 47 us
+// against one 64-pixel chunk per wave with FP32 matrix instructions and scattered operand
+// loads.  The matrix cores are busy 38 % and the vector units (the splits) 32 % of it.
+template <int KSP>
+struct PropFmt {  // matrix-core format and planes of a kernel's storage
+  static constexpr int SP = KSP == SP_F32 ? (int)SP_BF16 : KSP;
+  static constexpr int NPL = KSP == SP_F32 ? 3 : 1;
+  static constexpr int NT = KSP == SP_F32 ? 2 : 1;  // accumulator sets: one per tap
+  static constexpr int FL = KSP == SP_F32 ? 4 : 2;  // frequencies per lane and step
+};
 
-template <int SP, int DT, bool DATA4>
-__global__ __launch_bounds__(256) void rsd_propagate_mfma(RsdPropArgs a) {
-  using M = Mfma<SP>;
+// (re, im) pairs of one K step as the A operands of the real and the imaginary part
+__device__ __forceinline__ mf_u4 prop_re(mf_u4 a) { return a ^ 0x80000000u; }
+__device__ __forceinline__ mf_u4 prop_im(mf_u4 a) {
+  return mf_u4{__builtin_amdgcn_alignbit(a[0], a[0], 16), __builtin_amdgcn_alignbit(a[1], a[1], 16),
+               __builtin_amdgcn_alignbit(a[2], a[2], 16), __builtin_amdgcn_alignbit(a[3], a[3], 16)};
+}
+
+template <int KSP, int DT, bool DATA4>
+__global__ __launch_bounds__(256, KSP == SP_F32 && DT == 1 ? 3 : 1) void rsd_propagate_mfma(RsdPropArgs a) {
+  using F = PropFmt<KSP>;
+  using M = Mfma<F::SP>;
+  constexpr int NPL = F::NPL, NT = F::NT, FL = F::FL, FS = 2 * FL;
+  extern __shared__ float2 ws[];  // weights w_f, zero from Nf to the last step's end
   const int lane = threadIdx.x & 63;
   const int hl = lane >> 5, c32 = lane & 31;
   const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nds = (a.Nd + 32 * DT - 1) / (32 * DT);
-  const long long w = (long long)blockIdx.x * kWavesPerBlock + wib;
-  if (w >= a.nchunks * nds) return;
-  const long long g = w / nds;
-  const int d0 = (int)(w % nds) * 32 * DT;
   const int Nf = a.Nf, Nd = a.Nd;
-  const int i0 = a.chunk_i0[g];
-  // the lane's own pixel (first pass, stores) and the two rows it feeds into A
-  const int pix = a.chunk_pix[g * kGroupPix + lane];
-  const int pr0 = a.chunk_pix[g * kGroupPix + c32], pr1 = a.chunk_pix[g * kGroupPix + 32 + c32];
-  mf_acc acc[2][DT][2];  // [row tile][depth tile][re | im]
+  const int ns = (Nf + FS - 1) / FS;
+  for (int f = threadIdx.x; f < FS * ns; f += 256) ws[f] = f < Nf ? a.w[f] : make_float2(0.f, 0.f);
+  __syncthreads();
+  const int nds = (Nd + 32 * DT - 1) / (32 * DT);
+  // blocks go round-robin over the 8 XCDs: those of the active chunks (the first nactive) are
+  // dealt so that an XCD's L2 sees neighbouring chunks, which share kernel rows
+  unsigned b = blockIdx.x;
+  const unsigned nb8 = (unsigned)(2 * a.nactive * nds / kWavesPerBlock) & ~7u;
+  if (b < nb8) b = (b & 7u) * (nb8 >> 3) + (b >> 3);
+  const long long w = (long long)b * kWavesPerBlock + wib;
+  if (w >= 2 * a.nchunks * nds) return;
+  const long long gh = w / nds;  // half chunk
+  const int d0 = (int)(w % nds) * 32 * DT;
+  const int i0 = a.chunk_i0[gh >> 1];
+  const int* pixs = a.chunk_pix + gh * 32;
+  if (pixs[0] < 0) return;  // slots fill in order: an empty half
+  const int pix = pixs[c32];
+  const float wa = a.chunk_wa[gh * 32 + c32], wb = a.chunk_wb[gh * 32 + c32];
+  mf_acc acc[NT][DT][2];  // [tap][depth tile][re | im]
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+  for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int q = 0; q < DT; ++q)
 #pragma unroll
       for (int o = 0; o < 2; ++o)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[r][q][o][v] = 0.f;
+        for (int v = 0; v < 16; ++v) acc[t][q][o][v] = 0.f;
   int out_exp = 0;  // C = acc 2^out_exp (before its own storage scale)
   if (i0 >= 0) {
     const int i1 = i0 + 1 < a.cut_idx ? i0 + 1 : a.cut_idx;
-    // pass 1: the largest component of w_f P^ times the larger tap weight
-    float m = 0.f;
-    {
-      const float tw = fmaxf(a.chunk_wa[g * kGroupPix + lane], a.chunk_wb[g * kGroupPix + lane]);
-      const long long row = (long long)(pix >= 0 ? pix : 0) * a.ph_stride;
-      constexpr int U = 16;  // loads in flight per lane (unconditional, clamped indices:
-                             // a repeated last frequency does not change the maximum)
-      for (int f0 = 0; f0 < Nf; f0 += U) {
-        float2 p[U], wf[U];
-        if constexpr (DATA4) {
-          unsigned int raw[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int f = min(f0 + u, Nf - 1);
-            raw[u] = static_cast<const unsigned int*>(a.Ph)[row + f];
-            wf[u] = a.w[f];
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) p[u] = M::unpack(raw[u]);
-        } else {
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int f = min(f0 + u, Nf - 1);
-            p[u] = static_cast<const float2*>(a.Ph)[row + f];
-            wf[u] = a.w[f];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float re = p[u].x * wf[u].x - p[u].y * wf[u].y, im = p[u].x * wf[u].y + p[u].y * wf[u].x;
-          m = fmaxf(m, fmaxf(fabsf(re), fabsf(im)));
-        }
-      }
-      m *= tw;
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    }
-    int ex = 0;
-    if (m > 0.f) (void)frexpf(m, &ex);  // m < 2^ex
-    // clamped so that the scaled tap weights (<= 1) and 2^-e stay finite normal floats
-    const int e = min(max(14 - ex, -100), 100);
-    out_exp = -e;
-    const float wa0 = ldexpf(a.chunk_wa[g * kGroupPix + c32], e), wb0 = ldexpf(a.chunk_wb[g * kGroupPix + c32], e);
-    const float wa1 = ldexpf(a.chunk_wa[g * kGroupPix + 32 + c32], e);
-    const float wb1 = ldexpf(a.chunk_wb[g * kGroupPix + 32 + c32], e);
-    const long long row0 = (long long)(pr0 >= 0 ? pr0 : 0) * a.ph_stride;
-    const long long row1 = (long long)(pr1 >= 0 ? pr1 : 0) * a.ph_stride;
-    // the phasors of rows 0 and 1 at frequency f, loaded as stored
     using PRaw = typename std::conditional<DATA4, unsigned int, float2>::type;
-    auto ldp = [&](long long row, int f) { return static_cast<const PRaw*>(a.Ph)[row + f]; };
+    const PRaw* row = static_cast<const PRaw*>(a.Ph) + (long long)(pix >= 0 ? pix : 0) * a.ph_stride;
     auto cvp = [&](PRaw r) {
       if constexpr (DATA4) return M::unpack(r);
       else return r;
     };
-    const unsigned int* kr = static_cast<const unsigned int*>(a.Kr);
-    const long long k0 = (long long)i0 * Nf * Nd, k1 = (long long)i1 * Nf * Nd;
-    // one K step: this lane's frequencies fa = f0, fb = f0 + 1.  Every load is
-    // unconditional, from clamped (valid) indices, so that the loads of several steps stay
-    // in flight: a frequency beyond Nf is zeroed by its multiplier ma / mb on w_f P^ (its
-    // A entries are then 0, whatever kernel value it meets), and a depth beyond Nd only
-    // feeds output columns that are never stored.
-    struct Step {
-      float2 wfa, wfb;
-      PRaw pa0, pb0, pa1, pb1;
-      float ma, mb;
-      unsigned int kv[DT][4];  // [depth tile][K0a, K1a, K0b, K1b]
-    };
-    auto load = [&](int f0) {
-      Step t;
-      const int fa = min(f0, Nf - 1), fb = min(f0 + 1, Nf - 1);
-      t.ma = f0 < Nf ? 1.f : 0.f;
-      t.mb = f0 + 1 < Nf ? 1.f : 0.f;
-      t.wfa = a.w[fa];
-      t.wfb = a.w[fb];
-      t.pa0 = ldp(row0, fa);
-      t.pb0 = ldp(row0, fb);
-      t.pa1 = ldp(row1, fa);
-      t.pb1 = ldp(row1, fb);
+    auto cm = [](float2 p, float2 wf) { return make_float2(p.x * wf.x - p.y * wf.y, p.x * wf.y + p.y * wf.x); };
+    float ta = wa, tb = wb;  // tap weights ahead of the rounding (times 2^e)
+    if constexpr (KSP == SP_F16) {
+      float m = 0.f;
+      constexpr int U = 8;  // loads in flight per lane (a repeated last frequency does not change
+                            // the maximum); the two lane halves take a part of the row each
+      for (int f0 = hl * U; f0 < Nf; f0 += 2 * U) {
+        PRaw p[U];
 #pragma unroll
-      for (int q = 0; q < DT; ++q) {
-        const int d = min(d0 + 32 * q + c32, Nd - 1);
-        t.kv[q][0] = kr[k0 + (long long)fa * Nd + d];
-        t.kv[q][1] = kr[k1 + (long long)fa * Nd + d];
-        t.kv[q][2] = kr[k0 + (long long)fb * Nd + d];
-        t.kv[q][3] = kr[k1 + (long long)fb * Nd + d];
+        for (int u = 0; u < U; ++u) p[u] = row[min(f0 + u, Nf - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float2 z = cm(cvp(p[u]), ws[min(f0 + u, Nf - 1)]);
+          m = fmaxf(m, fmaxf(fabsf(z.x), fabsf(z.y)));
+        }
       }
+      m *= fmaxf(wa, wb);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+      int ex = 0;
+      if (m > 0.f) (void)frexpf(m, &ex);  // m < 2^ex
+      // clamped so that the scaled tap weights (<= 1) and 2^-e stay finite normal floats
+      const int e = min(max(14 - ex, -100), 100);
+      out_exp = -e;
+      ta = ldexpf(wa, e);
+      tb = ldexpf(wb, e);
+    }
+    // the lane's kernel operands (groups of FL frequencies): plane pl, depth tile q
+    typedef unsigned int bv __attribute__((ext_vector_type(FL)));
+    const bv* kr = static_cast<const bv*>(a.Kr);
+    const long long npl = a.kr_plane / FL;
+    const int ng = 2 * ((Nf + 7) / 8) * (4 / FL);  // groups in a row of the table
+    const long long k0 = ((long long)i0 * ng + hl) * Nd, k1 = ((long long)i1 * ng + hl) * Nd;
+    int dq[DT];
+#pragma unroll
+    for (int q = 0; q < DT; ++q) dq[q] = min(d0 + 32 * q + c32, Nd - 1);
+    struct Step {
+      PRaw p[FL];
+      bv b[2][NPL][DT];  // [tap][plane][depth tile]
+    };
+    auto load = [&](int s) {
+      Step t;
+      s = min(s, ns - 1);
+#pragma unroll
+      for (int j = 0; j < FL; ++j) t.p[j] = row[min(FS * s + FL * hl + j, Nf - 1)];
+#pragma unroll
+      for (int pl = 0; pl < NPL; ++pl)
+#pragma unroll
+        for (int q = 0; q < DT; ++q) {
+          t.b[0][pl][q] = kr[pl * npl + k0 + (long long)(2 * s) * Nd + dq[q]];
+          t.b[1][pl][q] = kr[pl * npl + k1 + (long long)(2 * s) * Nd + dq[q]];
+        }
       return t;
     };
-    auto cm = [](float2 p, float2 wf) { return make_float2(p.x * wf.x - p.y * wf.y, p.x * wf.y + p.y * wf.x); };
-    auto step = [&](const Step& t) {
-      const float2 wa_ = make_float2(t.wfa.x * t.ma, t.wfa.y * t.ma), wb_ = make_float2(t.wfb.x * t.mb, t.wfb.y * t.mb);
-      const float2 za0 = cm(cvp(t.pa0), wa_), zb0 = cm(cvp(t.pb0), wb_), za1 = cm(cvp(t.pa1), wa_),
-                   zb1 = cm(cvp(t.pb1), wb_);
-      mf_u4 A[2];
-      A[0] = mf_u4{M::pack(za0.x * wa0, za0.y * wa0), M::pack(za0.x * wb0, za0.y * wb0),
-                   M::pack(zb0.x * wa0, zb0.y * wa0), M::pack(zb0.x * wb0, zb0.y * wb0)};
-      A[1] = mf_u4{M::pack(za1.x * wa1, za1.y * wa1), M::pack(za1.x * wb1, za1.y * wb1),
-                   M::pack(zb1.x * wa1, zb1.y * wa1), M::pack(zb1.x * wb1, zb1.y * wb1)};
+    auto mul = [&](mf_u4 A, mf_u4 B, mf_acc* c) {
+      c[0] = M::mma(prop_re(A), B, c[0]);
+      c[1] = M::mma(prop_im(A), B, c[1]);
+    };
+    auto step = [&](const Step& t, int s) {
+      float2 z[FL];
 #pragma unroll
-      for (int q = 0; q < DT; ++q) {
-        // (re, -im): flip the sign of the upper half; (im, re): swap the halves
-        const unsigned int* kq = t.kv[q];
-        const mf_u4 Bre = mf_u4{kq[0] ^ 0x80000000u, kq[1] ^ 0x80000000u, kq[2] ^ 0x80000000u, kq[3] ^ 0x80000000u};
-        const mf_u4 Bim = mf_u4{(kq[0] >> 16) | (kq[0] << 16), (kq[1] >> 16) | (kq[1] << 16),
-                                (kq[2] >> 16) | (kq[2] << 16), (kq[3] >> 16) | (kq[3] << 16)};
+      for (int j = 0; j < FL; ++j) z[j] = cm(cvp(t.p[j]), ws[FS * s + FL * hl + j]);
+      if constexpr (NPL == 3) {
+        mf_u4 A[3];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          acc[r][q][0] = M::mma(A[r], Bre, acc[r][q][0]);
-          acc[r][q][1] = M::mma(A[r], Bim, acc[r][q][1]);
+        for (int pl = 0; pl < 3; ++pl)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            A[pl][j] = M::pack(z[j].x, z[j].y);
+            if (pl < 2) {
+              const float2 r = M::unpack(A[pl][j]);
+              z[j] = make_float2(z[j].x - r.x, z[j].y - r.y);
+            }
+          }
+        constexpr int pa[6] = {2, 1, 0, 1, 0, 0}, pb[6] = {0, 1, 2, 0, 1, 0};  // the small products first
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+#pragma unroll
+          for (int tap = 0; tap < 2; ++tap)
+#pragma unroll
+            for (int q = 0; q < DT; ++q) mul(A[pa[i]], t.b[tap][pb[i]][q], acc[tap][q]);
+      } else {
+        const mf_u4 A = {M::pack(z[0].x * ta, z[0].y * ta), M::pack(z[0].x * tb, z[0].y * tb),
+                         M::pack(z[1].x * ta, z[1].y * ta), M::pack(z[1].x * tb, z[1].y * tb)};
+#pragma unroll
+        for (int q = 0; q < DT; ++q) {
+          const bv b0 = t.b[0][0][q], b1 = t.b[1][0][q];
+          mul(A, mf_u4{b0[0], b1[0], b0[1], b1[1]}, acc[0][q]);
         }
       }
     };
-    // K steps s = 0 .. ns-1 (frequencies 4s + 2hl + {0, 1}); the loads of step s + 4 are
-    // issued right after step s is consumed, so four steps of loads are in flight
-    const int ns = (Nf + 3) / 4;
-    const int fl = 2 * hl;
-    Step b0 = load(fl), b1 = load(fl + 4), b2 = load(fl + 8), b3 = load(fl + 12);
-    for (int s0 = 0; s0 < ns; s0 += 4) {
-      step(b0);
-      b0 = load(fl + 4 * (s0 + 4));
-      if (s0 + 1 < ns) step(b1);
-      b1 = load(fl + 4 * (s0 + 5));
-      if (s0 + 2 < ns) step(b2);
-      b2 = load(fl + 4 * (s0 + 6));
-      if (s0 + 3 < ns) step(b3);
-      b3 = load(fl + 4 * (s0 + 7));
+    Step b0 = load(0), b1 = load(1);
+    // (both steps of a round unconditional: loads that feed a conditional step are moved into
+    // it, next to their use)
+    for (int s = 0; s + 1 < ns; s += 2) {
+      step(b0, s);
+      b0 = load(s + 2);
+      __builtin_amdgcn_sched_barrier(0);  // (the loads stay ahead of the step they overlap)
+      step(b1, s + 1);
+      b1 = load(s + 3);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    if (ns & 1) step(b0, ns - 1);
   }
   // D lane layout: rows 8(v/4) + 4 hl + v%4 of the tile, column c32
-  int qexp[DT];  // final exponent per depth tile column: the chunk scale, and for FP16
+  int qexp[DT];  // final exponent per depth tile column: the half chunk's scale, and for FP16
                  // data the stored P^ scale (undone) and C's storage scale at that depth
 #pragma unroll
   for (int q = 0; q < DT; ++q) {
     const int d = min(d0 + 32 * q + c32, Nd - 1);
     qexp[q] = out_exp;
-    if constexpr (DATA4 && SP == SP_F16) qexp[q] += a.e_c[d] - a.e_ph[0];
+    if constexpr (DATA4 && KSP == SP_F16) qexp[q] += a.e_c[d] - a.e_ph[0];
   }
 #pragma unroll
-  for (int r = 0; r < 2; ++r)
+  for (int v = 0; v < 16; ++v) {
+    const int r = 8 * (v >> 2) + 4 * hl + (v & 3);
+    const int pp = __shfl(pix, r, 64);
+    const float ra = NT == 2 ? __shfl(wa, r, 64) : 0.f, rb = NT == 2 ? __shfl(wb, r, 64) : 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = 32 * r + 8 * (v >> 2) + 4 * hl + (v & 3);
-      const int pp = __shfl(pix, row, 64);
-#pragma unroll
-      for (int q = 0; q < DT; ++q) {
-        const int d = d0 + 32 * q + c32;
-        if (pp >= 0 && d < Nd) {
-          const float re = ldexpf(acc[r][q][0][v], qexp[q]), im = ldexpf(acc[r][q][1][v], qexp[q]);
-          const long long o = (long long)pp * a.c_stride + d;
-          if constexpr (DATA4) static_cast<unsigned int*>(a.C)[o] = M::pack(re, im);
-          else static_cast<float2*>(a.C)[o] = make_float2(re, im);
-        }
+    for (int q = 0; q < DT; ++q) {
+      const int d = d0 + 32 * q + c32;
+      float re = acc[0][q][0][v], im = acc[0][q][1][v];
+      if constexpr (NT == 2) {
+        re = fmaf(ra, re, rb * acc[1][q][0][v]);
+        im = fmaf(ra, im, rb * acc[1][q][1][v]);
+      } else if constexpr (KSP == SP_F16) {
+        re = ldexpf(re, qexp[q]);
+        im = ldexpf(im, qexp[q]);
+      }
+      if (pp >= 0 && d < Nd) {
+        const long long o = (long long)pp * a.c_stride + d;
+        if constexpr (DATA4) static_cast<unsigned int*>(a.C)[o] = M::pack(re, im);
+        else static_cast<float2*>(a.C)[o] = make_float2(re, im);
       }
     }
+  }
 }
 
-// FP32 kernels on the matrix cores: the same product on v_mfma_f32_32x32x2f32 (FP32
-// operands, FP32 accumulation).  A K step is one (frequency, tap): lane l holds part
-// l/32 (re or im) of the tap-weighted phasor of its row, and the kernel value of its depth
-// column as (re, -im) for the real part of the output and (im, re) for the imaginary part,
-// the half l/32 selecting the entry.  A wave takes one chunk and DT 32-depth tiles; the
-// loads of four frequencies ahead are in flight (unconditional, clamped indices as above).
-typedef float rsd_f16v __attribute__((ext_vector_type(16)));
-
-template <int DT>
-__global__ __launch_bounds__(256) void rsd_propagate_mfma32(RsdPropArgs a) {
-  const int lane = threadIdx.x & 63;
-  const int hl = lane >> 5, c32 = lane & 31;
-  const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nds = (a.Nd + 32 * DT - 1) / (32 * DT);
-  const long long w = (long long)blockIdx.x * kWavesPerBlock + wib;
-  if (w >= a.nchunks * nds) return;
-  const long long g = w / nds;
-  const int d0 = (int)(w % nds) * 32 * DT;
-  const int Nf = a.Nf, Nd = a.Nd;
-  const int i0 = a.chunk_i0[g];
-  const int pix = a.chunk_pix[g * kGroupPix + lane];
-  const int pr0 = a.chunk_pix[g * kGroupPix + c32], pr1 = a.chunk_pix[g * kGroupPix + 32 + c32];
-  rsd_f16v acc[2][DT][2];  // [row tile][depth tile][re | im]
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int q = 0; q < DT; ++q)
-#pragma unroll
-      for (int o = 0; o < 2; ++o)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[r][q][o][v] = 0.f;
-  if (i0 >= 0) {
-    const int i1 = i0 + 1 < a.cut_idx ? i0 + 1 : a.cut_idx;
-    const float wa0 = a.chunk_wa[g * kGroupPix + c32], wb0 = a.chunk_wb[g * kGroupPix + c32];
-    const float wa1 = a.chunk_wa[g * kGroupPix + 32 + c32], wb1 = a.chunk_wb[g * kGroupPix + 32 + c32];
-    const float2* ph = static_cast<const float2*>(a.Ph);
-    const long long row0 = (long long)(pr0 >= 0 ? pr0 : 0) * a.ph_stride;
-    const long long row1 = (long long)(pr1 >= 0 ? pr1 : 0) * a.ph_stride;
-    const float2* kr = static_cast<const float2*>(a.Kr);
-    const long long k0 = (long long)i0 * Nf * Nd, k1 = (long long)i1 * Nf * Nd;
-    struct Step {
-      float2 wf, p0, p1;
-      float m;
-      float2 kv[DT][2];  // [depth tile][tap]
-    };
-    auto load = [&](int f) {
-      Step t;
-      const int fc = min(f, Nf - 1);
-      t.m = f < Nf ? 1.f : 0.f;
-      t.wf = a.w[fc];
-      t.p0 = ph[row0 + fc];
-      t.p1 = ph[row1 + fc];
-#pragma unroll
-      for (int q = 0; q < DT; ++q) {
-        const int d = min(d0 + 32 * q + c32, Nd - 1);
-        t.kv[q][0] = kr[k0 + (long long)fc * Nd + d];
-        t.kv[q][1] = kr[k1 + (long long)fc * Nd + d];
-      }
-      return t;
-    };
-    auto step = [&](const Step& t) {
-      const float2 wf = make_float2(t.wf.x * t.m, t.wf.y * t.m);
-      const float2 z0 = make_float2(t.p0.x * wf.x - t.p0.y * wf.y, t.p0.x * wf.y + t.p0.y * wf.x);
-      const float2 z1 = make_float2(t.p1.x * wf.x - t.p1.y * wf.y, t.p1.x * wf.y + t.p1.y * wf.x);
-      const float c0 = hl ? z0.y : z0.x, c1 = hl ? z1.y : z1.x;
-      const float A[2][2] = {{wa0 * c0, wb0 * c0}, {wa1 * c1, wb1 * c1}};  // [row tile][tap]
-#pragma unroll
-      for (int q = 0; q < DT; ++q)
-#pragma unroll
-        for (int tap = 0; tap < 2; ++tap) {
-          const float2 K = t.kv[q][tap];
-          const float bre = hl ? -K.y : K.x, bim = hl ? K.x : K.y;
-#pragma unroll
-          for (int r = 0; r < 2; ++r) {
-            acc[r][q][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[r][tap], bre, acc[r][q][0], 0, 0, 0);
-            acc[r][q][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[r][tap], bim, acc[r][q][1], 0, 0, 0);
-          }
-        }
-    };
-    Step b0 = load(0), b1 = load(1), b2 = load(2), b3 = load(3);
-    for (int f0 = 0; f0 < Nf; f0 += 4) {
-      step(b0);
-      b0 = load(f0 + 4);
-      if (f0 + 1 < Nf) step(b1);
-      b1 = load(f0 + 5);
-      if (f0 + 2 < Nf) step(b2);
-      b2 = load(f0 + 6);
-      if (f0 + 3 < Nf) step(b3);
-      b3 = load(f0 + 7);
+// The plan's kernel table (RsdPropArgs::Kr) from K_r[i][f][d] in its natural order: float2
+// (SP_F32, split in three planes) or (re, im) FP16 / BF16 pairs.
+__global__ __launch_bounds__(256) void rsd_kr_table(const void* __restrict__ in, unsigned int* __restrict__ out,
+                                                    long long n, long long plane, int Nf, int Nd, int split) {
+  using M = Mfma<SP_BF16>;
+  const int FL = split ? 4 : 2, ng = 8 / FL * ((Nf + 7) / 8);
+  for (long long o = (long long)blockIdx.x * 256 + threadIdx.x; o < n; o += (long long)gridDim.x * 256) {
+    const long long r = o / FL / Nd;
+    const int d = (int)(o / FL % Nd), f = (int)(r % ng) * FL + (int)(o % FL);
+    const long long src = ((r / ng) * Nf + f) * Nd + d;
+    if (!split) {
+      out[o] = f < Nf ? static_cast<const unsigned int*>(in)[src] : 0u;
+      continue;
+    }
+    float2 k = f < Nf ? static_cast<const float2*>(in)[src] : make_float2(0.f, 0.f);
+    for (int pl = 0; pl < 3; ++pl) {
+      const unsigned int h = M::pack(k.x, k.y);
+      const float2 v = M::unpack(h);
+      out[pl * plane + o] = h;
+      k = make_float2(k.x - v.x, k.y - v.y);
     }
   }
-  // D lane layout: rows 8(v/4) + 4 hl + v%4 of the tile, column c32
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = 32 * r + 8 * (v >> 2) + 4 * hl + (v & 3);
-      const int pp = __shfl(pix, row, 64);
-#pragma unroll
-      for (int q = 0; q < DT; ++q) {
-        const int d = d0 + 32 * q + c32;
-        if (pp >= 0 && d < Nd)
-          static_cast<float2*>(a.C)[(long long)pp * a.c_stride + d] = make_float2(acc[r][q][0][v], acc[r][q][1][v]);
-      }
-    }
+}
+
+size_t rsd_kr_plane(int nrho, int nf, int nd) { return (size_t)nrho * (8 * ((nf + 7) / 8)) * nd; }
+
+hipError_t launch_rsd_kr_table(const void* in, void* out, int nrho, int nf, int nd, int sp, hipStream_t s) {
+  const long long n = (long long)rsd_kr_plane(nrho, nf, nd);
+  if (n <= 0) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 16384);
+  hipLaunchKernelGGL(rsd_kr_table, dim3(blocks), dim3(256), 0, s, in, static_cast<unsigned int*>(out), n, n, nf, nd,
+                     sp == SP_F32 ? 1 : 0);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -497,38 +459,29 @@ hipError_t launch_rsd_scales(const float* tau, long long n, float* partials, con
 
 hipError_t launch_rsd_propagate(const RsdPropArgs& a, hipStream_t s) {
   if (a.data_sp != SP_F32 && (a.data_sp != a.kernel_sp || !a.mfma)) return hipErrorInvalidValue;
-  if (a.mfma && (a.kernel_sp == SP_F16 || a.kernel_sp == SP_BF16)) {
-    // FP16 / BF16: two depth tiles per wave by default (0.079 against 0.114 ms with one);
-    // a.mfma == 2 asks for the other tiling
-    const int dt = (a.mfma == 2 || a.Nd <= 32) ? 1 : 2;
-    const long long waves = a.nchunks * ((a.Nd + 32 * dt - 1) / (32 * dt));
+  if (a.mfma) {
+    // 32-depth tiles per wave: FP32 kernels 1 (three waves per SIMD; 76 us against 80 with two at
+    // 128 x 128 x 1024), FP16 / BF16 2 (47 against 53)
+    int dt = a.kernel_sp == SP_F32 ? 1 : 2;
+    if (a.mfma == 2) dt = 3 - dt;
+    if (a.Nd <= 32) dt = 1;
+    const long long waves = 2 * a.nchunks * ((a.Nd + 32 * dt - 1) / (32 * dt));
     const long long blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks <= 0) return hipSuccess;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)blocks);
+    const size_t lds = sizeof(float2) * 8 * (size_t)((a.Nf + 7) / 8);
+    auto go = [&](auto k) {
+      hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), lds, s, a);
+      return hipGetLastError();
+    };
     const bool d4 = a.data_sp != SP_F32;
-#define NLOS_PROP(SPV, DTV, D4V) hipLaunchKernelGGL((rsd_propagate_mfma<SPV, DTV, D4V>), grid, dim3(256), 0, s, a)
+    if (a.kernel_sp == SP_F32) return dt == 1 ? go(rsd_propagate_mfma<SP_F32, 1, false>) : go(rsd_propagate_mfma<SP_F32, 2, false>);
     if (a.kernel_sp == SP_F16) {
-      if (d4) { if (dt == 1) NLOS_PROP(SP_F16, 1, true); else NLOS_PROP(SP_F16, 2, true); }
-      else { if (dt == 1) NLOS_PROP(SP_F16, 1, false); else NLOS_PROP(SP_F16, 2, false); }
-    } else {
-      if (d4) { if (dt == 1) NLOS_PROP(SP_BF16, 1, true); else NLOS_PROP(SP_BF16, 2, true); }
-      else { if (dt == 1) NLOS_PROP(SP_BF16, 1, false); else NLOS_PROP(SP_BF16, 2, false); }
+      if (d4) return dt == 1 ? go(rsd_propagate_mfma<SP_F16, 1, true>) : go(rsd_propagate_mfma<SP_F16, 2, true>);
+      return dt == 1 ? go(rsd_propagate_mfma<SP_F16, 1, false>) : go(rsd_propagate_mfma<SP_F16, 2, false>);
     }
-#undef NLOS_PROP
-    return hipGetLastError();
-  }
-  if (a.mfma && a.kernel_sp == SP_F32) {
-    // FP32: one depth tile per wave by default (two waves per SIMD: 0.133 against 0.165 ms
-    // with two tiles at 128 x 128 x 1024, 64 depths); a.mfma == 2 asks for the other tiling
-    const int dt = (a.mfma == 2 && a.Nd > 32) ? 2 : 1;
-    const long long waves = a.nchunks * ((a.Nd + 32 * dt - 1) / (32 * dt));
-    const long long blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks <= 0) return hipSuccess;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (dt == 1) hipLaunchKernelGGL(rsd_propagate_mfma32<1>, dim3((unsigned)blocks), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(rsd_propagate_mfma32<2>, dim3((unsigned)blocks), dim3(256), 0, s, a);
-    return hipGetLastError();
+    if (d4) return dt == 1 ? go(rsd_propagate_mfma<SP_BF16, 1, true>) : go(rsd_propagate_mfma<SP_BF16, 2, true>);
+    return dt == 1 ? go(rsd_propagate_mfma<SP_BF16, 1, false>) : go(rsd_propagate_mfma<SP_BF16, 2, false>);
   }
   const long long nds = (a.Nd + kDepths - 1) / kDepths;
   const long long waves = a.nchunks * nds;

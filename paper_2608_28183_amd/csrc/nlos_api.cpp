@@ -210,7 +210,8 @@ struct nlos_rsd_plan {
   int device = 0;
   int Mx = 0, My = 0;
   nlos::RsdGeometry g{};
-  void* d_kr = nullptr;       // [Nrho][Nf][Nd] float2 or (re, im) FP16 / BF16 pairs
+  void* d_kr = nullptr;       // kernel table (RsdPropArgs::Kr), kr_plane pairs a plane
+  long long kr_plane = 0;
   float* d_kappa = nullptr;   // [Nd] sum_f |w_f| max_i |K_r[i][f][d]| (four-byte data: scales)
   float2* d_w = nullptr;      // [Nf]
   int* d_bins = nullptr;      // [Nf]
@@ -218,7 +219,7 @@ struct nlos_rsd_plan {
   int* d_chunk_pix = nullptr;
   float* d_chunk_wa = nullptr;
   float* d_chunk_wb = nullptr;
-  long long nchunks = 0;
+  long long nchunks = 0, nactive = 0;
   // general (not power-of-two) lengths of the x, y and phasor t transforms: radix plans
   // and W_m^k tables (in d_gtw)
   bool gen_x = false, gen_y = false, gen_t = false;
@@ -1197,6 +1198,19 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
                   hipGetErrorString(e));
     };
     hipError_t e;
+    // the device's kernel table from the host's K_r (through a device copy in its own order)
+    auto kr_table = [&](const void* k, size_t bytes) -> hipError_t {
+      const int nrho = (int)(nk / ((size_t)d->n_freq * d->n_depth)), sp = fk_sp(d->kernel_prec);
+      p->kr_plane = (long long)nlos::rsd_kr_plane(nrho, d->n_freq, d->n_depth);
+      void* tmp = nullptr;
+      hipError_t r = nlos::dev_alloc(&p->d_kr, (size_t)p->kr_plane * (sp == nlos::SP_F32 ? 12 : 4));
+      if (r == hipSuccess) r = nlos::dev_alloc(&tmp, bytes);
+      if (r == hipSuccess) r = hipMemcpy(tmp, k, bytes, hipMemcpyHostToDevice);
+      if (r == hipSuccess) r = nlos::launch_rsd_kr_table(tmp, p->d_kr, nrho, d->n_freq, d->n_depth, sp, ctx->stream);
+      if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
+      if (tmp) (void)hipFree(tmp);
+      return r;
+    };
     if (d->kernel_prec == NLOS_FP16 || d->kernel_prec == NLOS_BF16) {
       // FP64 accumulation, a single rounding (to nearest even) to binary16 or bfloat16 on
       // store; (re, im) pairs, re in the lower half
@@ -1206,15 +1220,11 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
         kh[2 * i] = bf ? nlos::to_bf16_bits(kre[i]) : nlos::to_f16_bits(kre[i]);
         kh[2 * i + 1] = bf ? nlos::to_bf16_bits(kim[i]) : nlos::to_f16_bits(kim[i]);
       }
-      if ((e = nlos::dev_alloc((void**)&p->d_kr, nk * 4)) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
-      if ((e = hipMemcpy(p->d_kr, kh.data(), nk * 4, hipMemcpyHostToDevice)) != hipSuccess)
-        return cleanup(NLOS_ERR_DEVICE, "K_r upload", e);
+      if ((e = kr_table(kh.data(), nk * 4)) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
     } else {
       std::vector<float2> kf(nk);
       for (size_t i = 0; i < nk; ++i) kf[i] = make_float2((float)kre[i], (float)kim[i]);
-      if ((e = nlos::dev_alloc((void**)&p->d_kr, nk * sizeof(float2))) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
-      if ((e = hipMemcpy(p->d_kr, kf.data(), nk * sizeof(float2), hipMemcpyHostToDevice)) != hipSuccess)
-        return cleanup(NLOS_ERR_DEVICE, "K_r upload", e);
+      if ((e = kr_table(kf.data(), nk * sizeof(float2))) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
     }
     if (d->data_prec != NLOS_FP32) {
       // kappa_d = sum_f |w_f| max_i |K_r[i][f][d]|: with L = sum |tau| it bounds the
@@ -1240,6 +1250,7 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
         return cleanup(NLOS_ERR_DEVICE, "kappa upload", e);
     }
     p->nchunks = ch.count();
+    while (p->nactive < p->nchunks && ch.i0[p->nactive] >= 0) ++p->nactive;
     auto upload = [&](void** dst, const void* src, size_t bytes) -> hipError_t {
       hipError_t r = nlos::dev_alloc((void**)dst, bytes);
       if (r == hipSuccess) r = hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice);
@@ -1343,9 +1354,9 @@ static nlos_status rsd_run(nlos_ctx* ctx, const nlos_rsd_plan* p, hipStream_t s,
   }));
   // 4. radial propagation over pixel chunks: P^ -> C[pix][d]
   nlos::RsdPropArgs r{};
-  r.Ph = Ph; r.Kr = p->d_kr; r.w = p->d_w; r.C = C;
+  r.Ph = Ph; r.Kr = p->d_kr; r.kr_plane = p->kr_plane; r.w = p->d_w; r.C = C;
   r.chunk_i0 = p->d_chunk_i0; r.chunk_pix = p->d_chunk_pix; r.chunk_wa = p->d_chunk_wa;
-  r.chunk_wb = p->d_chunk_wb; r.nchunks = p->nchunks;
+  r.chunk_wb = p->d_chunk_wb; r.nchunks = p->nchunks; r.nactive = p->nactive;
   r.Nf = (int)Nf; r.Nd = (int)Nd; r.ph_stride = (int)Nfs; r.c_stride = (int)Nds;
   r.cut_idx = p->g.cut_idx; r.kernel_sp = fk_sp(d.kernel_prec);
   // four-byte data exist only on the matrix cores
@@ -1899,9 +1910,9 @@ nlos_status nlos_moe(nlos_ctx* ctx, const nlos_moe_plan* p, const float* d_tau, 
   HIP_TRY(ctx, timed_on(ctx, s1, NLOS_PASS_MOE_PHASOR, [&] { return nlos::launch_moe_phasor_pair(ph, tw, s1); }));
   HIP_TRY(ctx, hipEventRecord(ctx->fork[1], s1));  // W2 no longer read by the RSD branch
   nlos::RsdPropArgs r{};
-  r.Ph = Ph; r.Kr = p->rsd->d_kr; r.w = p->rsd->d_w; r.C = Cr;
+  r.Ph = Ph; r.Kr = p->rsd->d_kr; r.kr_plane = p->rsd->kr_plane; r.w = p->rsd->d_w; r.C = Cr;
   r.chunk_i0 = p->rsd->d_chunk_i0; r.chunk_pix = p->rsd->d_chunk_pix; r.chunk_wa = p->rsd->d_chunk_wa;
-  r.chunk_wb = p->rsd->d_chunk_wb; r.nchunks = p->rsd->nchunks;
+  r.chunk_wb = p->rsd->d_chunk_wb; r.nchunks = p->rsd->nchunks; r.nactive = p->rsd->nactive;
   r.Nf = (int)Nf; r.Nd = (int)Nd; r.ph_stride = (int)Nf; r.c_stride = (int)Nd;
   r.cut_idx = p->rsd->g.cut_idx; r.kernel_sp = fk_sp(rd.kernel_prec); r.mfma = ctx->rsd_mfma;
   HIP_TRY(ctx, timed_on(ctx, s1, NLOS_PASS_RSD_PROPAGATE, [&] { return nlos::launch_rsd_propagate(r, s1); }));

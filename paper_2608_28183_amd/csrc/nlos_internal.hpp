@@ -143,7 +143,11 @@ uint16_t to_bf16_bits(double v);
 struct RsdPropArgs {
   const void* Ph;          // [npix][Nf] spectra of the padded phasor planes (float2, or
                            // four-byte pairs when data_sp != SP_F32)
-  const void* Kr;          // [Nrho][Nf][Nd] radial kernel, float2 or (re, im) FP16 / BF16 pairs
+  // radial kernel: planes of kr_plane four-byte (re, im) pairs, f zero-padded to a multiple of
+  // 8.  FP16 / BF16: one plane [Nrho][f / 2][Nd][f % 2]; FP32: three bfloat16 planes that add
+  // up to it exactly, [Nrho][f / 4][Nd][f % 4]
+  const void* Kr;
+  long long kr_plane;
   const float2* w;         // [Nf] complex frequency weights
   void* C;                 // [npix][Nd] propagated spectra (float2 or four-byte pairs)
   const int* chunk_i0;     // [nchunks] lower radial bin (-1: all-zero chunk)
@@ -151,6 +155,7 @@ struct RsdPropArgs {
   const float* chunk_wa;   // [nchunks][64] a (1 - alpha), 0 in unused slots
   const float* chunk_wb;   // [nchunks][64] a alpha, 0 in unused slots
   long long nchunks;
+  long long nactive;       // the chunks with chunk_i0 >= 0 come first
   int Nf, Nd;
   int ph_stride, c_stride;  // elements between the pixel rows of Ph and of C
   int cut_idx;
@@ -161,8 +166,7 @@ struct RsdPropArgs {
   const int* e_ph;
   const int* e_c;
   int mfma;                // propagation on the matrix cores: 0 no (FP32 FMAs), 1 yes, 2 yes
-                           // with the other depth tiling (FP32: two 32-depth tiles per wave,
-                           // FP16 / BF16: one)
+                           // with the other depth tiling
 };
 
 // stream: the f-k passes (FP32 LD_C64 -> ST_C64), as resident blocks where the shape allows
@@ -219,6 +223,10 @@ constexpr int kScaleBlocks = 1024;
 hipError_t launch_fk_scales(const float* tau, long long n, int nt, float* partials, int* exps,
                             int l_norm, int l_first_inv, int l_second_inv, hipStream_t s);
 hipError_t launch_rsd_propagate(const RsdPropArgs& a, hipStream_t s);
+// the kernel table from K_r[Nrho][Nf][Nd] as float2 (sp SP_F32) or four-byte pairs (device
+// buffers); pairs per plane
+size_t rsd_kr_plane(int nrho, int nf, int nd);
+hipError_t launch_rsd_kr_table(const void* in, void* out, int nrho, int nf, int nd, int sp, hipStream_t s);
 // FP16 storage scales of the RSD intermediates from L = sum |tau| (n values, n even):
 // exps[0] for P, X and P^ (bound L), exps[1 + d] for C at depth d (bound L kappa[d]) and
 // exps[1 + nd + d] for D (bound My L kappa[d], l_my = log2 My); partials[kScaleBlocks].
