@@ -106,12 +106,24 @@ __device__ __forceinline__ void apply_stage(float2* v, int p, const TwLds<S>& tw
   });
 }
 
+// Orders the LDS accesses of the threads that share a line: block barrier, or, WAVE (every line
+// within one wave), only that wave's own accesses, which the LDS serves in order.
+template <bool WAVE>
+__device__ __forceinline__ void line_sync() {
+  if constexpr (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
 // v holds the stage-0 inputs (element stage_in_index<N, R0, E>(p, b, r) at v[b*R0 + r]).
 // Runs every stage; the last stage's outputs stay in v in the order emit_last visits.
 // SPLIT (two- and three-stage plans): each exchange moves the real parts, then the
 // imaginary parts, through a float buffer of half the size (lds is then a float array in
 // disguise).
-template <class S, bool INV, bool SPLIT = false, class Idx, class TW>
+template <class S, bool INV, bool SPLIT = false, bool WAVE = false, class Idx, class TW>
 __device__ __forceinline__ void fft_stages(float2* v, int p, float2* lds, Idx idx, const TW& tw) {
   constexpr int N = S::R0 * S::R1 * S::R2;
   constexpr int E = S::E;
@@ -122,11 +134,11 @@ __device__ __forceinline__ void fft_stages(float2* v, int p, float2* lds, Idx id
     {
       float re[E], im[E];
       write_lds_part<N, S::R0, 1, E, 0>(v, p, f, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       read_lds_part<N, S::R1, E>(re, p, f, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       write_lds_part<N, S::R0, 1, E, 1>(v, p, f, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       read_lds_part<N, S::R1, E>(im, p, f, idx);
 #pragma unroll
       for (int j = 0; j < E; ++j) v[j] = make_float2(re[j], im[j]);
@@ -134,13 +146,13 @@ __device__ __forceinline__ void fft_stages(float2* v, int p, float2* lds, Idx id
     apply_stage<S, 1, INV>(v, p, tw);
     if constexpr (S::NSTAGE == 3) {
       float re[E], im[E];
-      __syncthreads();  // every read of the first exchange before the second's writes
+      line_sync<WAVE>();  // every read of the first exchange before the second's writes
       write_lds_part<N, S::R1, S::R0, E, 0>(v, p, f, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       read_lds_part<N, S::R2, E>(re, p, f, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       write_lds_part<N, S::R1, S::R0, E, 1>(v, p, f, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       read_lds_part<N, S::R2, E>(im, p, f, idx);
 #pragma unroll
       for (int j = 0; j < E; ++j) v[j] = make_float2(re[j], im[j]);
@@ -150,15 +162,15 @@ __device__ __forceinline__ void fft_stages(float2* v, int p, float2* lds, Idx id
   }
   if constexpr (S::NSTAGE >= 2) {
     write_lds<N, S::R0, 1, E>(v, p, lds, idx);
-    __syncthreads();
+    line_sync<WAVE>();
     read_lds<N, S::R1, E>(v, p, lds, idx);
     if constexpr (S::NSTAGE == 2) {
       apply_stage<S, 1, INV>(v, p, tw);
     } else {
-      __syncthreads();
+      line_sync<WAVE>();
       apply_stage<S, 1, INV>(v, p, tw);
       write_lds<N, S::R1, S::R0, E>(v, p, lds, idx);
-      __syncthreads();
+      line_sync<WAVE>();
       read_lds<N, S::R2, E>(v, p, lds, idx);
       apply_stage<S, 2, INV>(v, p, tw);
     }
@@ -176,12 +188,13 @@ __device__ __forceinline__ void emit_last(const float2* v, int p, Store store) {
 }
 
 // All stages, then store(n, value) for every output.  SYNC_BEFORE_STORE puts a
-// barrier between the last LDS read and the stores (for stores into LDS).
-template <class S, bool INV, bool SYNC_BEFORE_STORE, bool SPLIT = false, class Idx, class TW, class Store>
+// line_sync between the last LDS read and the stores (for stores into LDS).
+template <class S, bool INV, bool SYNC_BEFORE_STORE, bool SPLIT = false, bool WAVE = false, class Idx, class TW,
+          class Store>
 __device__ __forceinline__ void fft_run(float2* v, int p, float2* lds, Idx idx, const TW& tw,
                                         Store store) {
-  fft_stages<S, INV, SPLIT>(v, p, lds, idx, tw);
-  if constexpr (SYNC_BEFORE_STORE) __syncthreads();
+  fft_stages<S, INV, SPLIT, WAVE>(v, p, lds, idx, tw);
+  if constexpr (SYNC_BEFORE_STORE) line_sync<WAVE>();
   emit_last<S>(v, p, store);
 }
 
@@ -235,6 +248,7 @@ struct ContigCfg {
   static constexpr int P = S::P;
   static constexpr int L = 256 / P < 1 ? 1 : 256 / P;
   static constexpr int THREADS = L * P;
+  static constexpr bool WAVE = P <= 64;  // a line's threads are one wave's
   static constexpr int LSTRIDE = N + (N >= 32 ? N / 32 : 1);
   static constexpr int LDS_ELEMS = L * LSTRIDE;
 };

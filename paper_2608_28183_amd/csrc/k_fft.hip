@@ -311,7 +311,7 @@ __global__ __launch_bounds__((ContigCfg<N, ContigTune<N>::E>::THREADS)) void con
     // natural-order spectrum into LDS, then gather the requested bins (four-byte output
     // for SP_F16 / SP_BF16, FP16 times 2^(*e_out))
     auto store = [&](int n, float2 val) { my[swz(n)] = val; };
-    fft_run<S, INV, true>(v, p, my, idx, tw, store);
+    fft_run<S, INV, true, false, C::WAVE>(v, p, my, idx, tw, store);
     __syncthreads();
     const long long line0 = (long long)blockIdx.x * C::L;
     const int eo = SP == SP_F16 ? *a.e_out : 0;
@@ -353,13 +353,12 @@ __global__ __launch_bounds__((ContigCfg<N, ContigTune<N>::E>::THREADS)) void con
       if (wr) orow[n] = e;
       m = fmaxf(m, e);
     };
-    fft_run<S, INV, false, SPLIT>(v, p, my, idx, tw, store);
-    if (a.img != nullptr) {
-      constexpr int W = P < 64 ? P : 64;
+    fft_run<S, INV, false, SPLIT, C::WAVE>(v, p, my, idx, tw, store);
+    if (a.img != nullptr) {  // the line's lanes are one wave's: its maximum is complete here
+      static_assert(P <= 64, "a line within a wave");
 #pragma unroll
-      for (int off = 1; off < W; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, W));
-      if (lineok && (p % W) == 0)
-        atomicMax(reinterpret_cast<unsigned int*>(a.img) + line, __float_as_uint(m));
+      for (int off = 1; off < P; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, P));
+      if (lineok && p == 0) a.img[line] = m;
     }
   } else {
     auto store = [&](int n, float2 val) {
@@ -374,7 +373,7 @@ __global__ __launch_bounds__((ContigCfg<N, ContigTune<N>::E>::THREADS)) void con
                     __float_as_uint(m));
       }
     };
-    fft_run<S, INV, false>(v, p, my, idx, tw, store);
+    fft_run<S, INV, false, false, C::WAVE>(v, p, my, idx, tw, store);
   }
 }
 
@@ -418,6 +417,7 @@ __global__ __launch_bounds__((ContigCfg<N, ContigTune<N>::E>::THREADS)) void zif
   auto idx = [&](int n) { return swz(n); };
   long long g = blockIdx.x;
   if (g < ngroups) fetch(g);
+  __syncthreads();  // the tables; from here on the waves keep to themselves
   for (; g < ngroups; g += gridDim.x) {
     float2 v[E];
 #pragma unroll
@@ -436,14 +436,14 @@ __global__ __launch_bounds__((ContigCfg<N, ContigTune<N>::E>::THREADS)) void zif
       orow[n] = e;
       m = fmaxf(m, e);
     };
-    fft_run<S, true, false, true>(v, p, my, idx, TwLds<S>{wt, wt2}, store);
-    if (a.img != nullptr) {
-      constexpr int W = P < 64 ? P : 64;
+    fft_run<S, true, false, true, C::WAVE>(v, p, my, idx, TwLds<S>{wt, wt2}, store);
+    if (a.img != nullptr) {  // the line's lanes are one wave's: its maximum is complete here
+      static_assert(P <= 64, "a line within a wave");
 #pragma unroll
-      for (int off = 1; off < W; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, W));
-      if ((p % W) == 0) atomicMax(reinterpret_cast<unsigned int*>(a.img) + line, __float_as_uint(m));
+      for (int off = 1; off < P; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, P));
+      if (p == 0) a.img[line] = m;
     }
-    __syncthreads();  // every read of this group's exchange before the next group's writes
+    line_sync<C::WAVE>();  // every read of this group's exchange before the next group's writes
   }
 }
 

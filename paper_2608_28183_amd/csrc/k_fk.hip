@@ -201,14 +201,14 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair(Fk
         for (int j = 0; j < E; ++j) v[j] = cscale(v[j], float(p + j * P) * a.tscale_in);
       }
     }
-    __syncthreads();  // the previous item's last LDS reads are done
+    line_sync<C::WAVE>();  // the previous item's last LDS reads are done
     // the spectrum in natural order (the line stride leaves room for the repeated bin 0)
     static_assert(C::LSTRIDE > N, "room for bin N");
-    fft_run<S, false, true>(v, p, my, idx, tw, [&](int n, float2 val) {
+    fft_run<S, false, true, false, C::WAVE>(v, p, my, idx, tw, [&](int n, float2 val) {
       my[n] = val;
       if (n == 0) my[N] = val;
     });
-    __syncthreads();
+    line_sync<C::WAVE>();
 
     // Stolt (shared by the pair): q = sqrt(A + kz^2) in t-bin units; lerp weight,
     // Jacobian kz/q, 1/(Mx My Mt).
@@ -285,6 +285,7 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair_st
   uint2 cur = entry(g < ngroups ? g : 0), nxt = entry(g + step < ngroups ? g + step : 0);
   if (g < ngroups) fetch(cur);
   __builtin_amdgcn_s_waitcnt(0);  // tables and the first group before the loop
+  __syncthreads();
   for (; g < ngroups; g += step) {
     const uint2 e = cur;
     float2 v[E];
@@ -295,14 +296,14 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair_st
     cur = nxt;
     if (g + 2 * step < ngroups) nxt = entry(g + 2 * step);
     if (g + step < ngroups) fetch(cur);
-    __syncthreads();  // the previous item's LDS reads (and, first, the tables) are done
+    line_sync<C::WAVE>();  // the previous item's LDS reads are done
     // the spectrum in natural order (the line stride leaves room for the repeated bin 0)
     static_assert(C::LSTRIDE > N, "room for bin N");
-    fft_run<S, false, true>(v, p, my, idx, TwLds<S>{wt, wt2}, [&](int n, float2 val) {
+    fft_run<S, false, true, false, C::WAVE>(v, p, my, idx, TwLds<S>{wt, wt2}, [&](int n, float2 val) {
       my[n] = val;
       if (n == 0) my[N] = val;
     });
-    __syncthreads();
+    line_sync<C::WAVE>();
     const PairItem it = pair_of(a, e);
     const int kxs = it.kx < a.Mx / 2 ? it.kx : it.kx - a.Mx;
     const int kys = it.ky < a.My / 2 ? it.ky : it.ky - a.My;
@@ -314,7 +315,9 @@ __global__ __launch_bounds__((ContigCfg<N, E_>::THREADS)) void fk_column_pair_st
     const __amdgpu_buffer_rsrc_t o2 = buf_view(outp + (long long)(mir ? it.ky2 : it.ky) * a.out_row +
                                                (long long)(mir ? it.kx2 : it.kx) * a.nt);
     const int nz = (int)e.y;
-#pragma unroll
+    // (1024 points: 116 registers instead of 154 whole, no change in time; 2048 points: whole
+    // measured 152 us against 156 at 128 x 128 x 1024)
+#pragma unroll (N == 1024 ? 4 : HALF / P)
     for (int i = 0; i < HALF / P; ++i) {
       const int kz = p + i * P;
       float2 xa = make_float2(0.f, 0.f), xb = xa;
@@ -662,6 +665,19 @@ constexpr long long column_blocks(int n) { return n >= 2048 ? 2048 : 4096; }
 
 template <int N, int SP>
 static hipError_t launch_pair_n(const FkPairArgs& a, const float2* tw, hipStream_t s) {
+  if constexpr (SP == SP_F32 && N >= 512) {
+    if (a.tscale_in == 0.f && 2 * a.nt == N) {
+      // 512-point columns take 8 samples per thread here, a wave per column (32 per thread and
+      // 16 columns per block before: 16 -> 11 us at 32 x 32 x 256, 61 -> 40 at 128 x 128 x 256)
+      constexpr int E = N == 512 ? 8 : 16;
+      using C = ContigCfg<N, E>;
+      const long long groups = (a.nwork + C::L - 1) / C::L;
+      const long long res = resident_blocks<fk_column_pair_stream<N, E>>(C::THREADS);
+      const long long nb = res > 0 && res < groups ? res : groups;
+      hipLaunchKernelGGL((fk_column_pair_stream<N, E>), dim3((unsigned)nb), dim3(C::THREADS), 0, s, a, tw);
+      return hipGetLastError();
+    }
+  }
   constexpr int E = (N >= 1024) ? 16 : default_e(N);
   using C = ContigCfg<N, E>;
   const long long groups = (a.nwork + C::L - 1) / C::L;
@@ -670,14 +686,6 @@ static hipError_t launch_pair_n(const FkPairArgs& a, const float2* tw, hipStream
   // padded volume, four-byte storage (FP32 keeps its guarded loads: the folded form
   // raised its registers from 157 to 173 and its occupancy from 3 to 2)
   const bool half = SP != SP_F32 && 2 * a.nt == N;
-  if constexpr (SP == SP_F32 && FftShape<N, E>::NSTAGE == 3) {
-    if (a.tscale_in == 0.f && 2 * a.nt == N) {
-      const long long res = resident_blocks<fk_column_pair_stream<N, E>>(C::THREADS);
-      const long long nb = res > 0 && res < groups ? res : groups;
-      hipLaunchKernelGGL((fk_column_pair_stream<N, E>), dim3((unsigned)nb), dim3(C::THREADS), 0, s, a, tw);
-      return hipGetLastError();
-    }
-  }
   if (SP == SP_F32 && a.tscale_in != 0.f)
     hipLaunchKernelGGL((fk_column_pair<N, E, SP_F32, true>), grid, dim3(C::THREADS), 0, s, a, tw);
   else if (a.tscale_in != 0.f)

@@ -162,8 +162,14 @@ __global__ __launch_bounds__(kGenMaxThreads) void gen_contig(ContigArgs a, GenPl
     if (a.img != nullptr) {
       const int W = P < 64 ? P : 64;  // lanes of one line within a wave
       for (int off = 1; off < W; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, W));
-      if (lineok && (p % W) == 0)
-        atomicMax(reinterpret_cast<unsigned int*>(a.img) + line, __float_as_uint(m));
+      if (P > 64) {  // a line over several waves (one line per block from 256 threads)
+        __shared__ float part[kGenMaxThreads / 64];
+        if ((tid & 63) == 0) part[tid >> 6] = m;
+        __syncthreads();
+        if (p == 0)
+          for (int w = 1; w < P / 64; ++w) m = fmaxf(m, part[(tid >> 6) + w]);
+      }
+      if (lineok && p == 0) a.img[line] = m;
     }
   } else {
     if (!lineok) return;

@@ -407,7 +407,7 @@ __global__ __launch_bounds__(256, 3) void zfft_abs2_mfma(ContigArgs a, const mf_
       if (a.img != nullptr) {
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-        if (lane == 0) atomicMax(reinterpret_cast<unsigned int*>(a.img) + line[u], __float_as_uint(mx));
+        if (lane == 0) a.img[line[u]] = mx;
       }
     }
   }

@@ -62,8 +62,16 @@ __device__ __forceinline__ void rsd_freq(float2* acc, float2 p, float2 wf, float
     cmac2(acc[j], pa, load_kr<SP>(a, i0, f, d0 + j), pb, load_kr<SP>(a, i1, f, d0 + j));
 }
 
+// The last pass takes its maxima over several blocks of a pixel: the image is cleared here,
+// one value per thread (a launch less).
+__device__ __forceinline__ void clear_image(const RsdPropArgs& a) {
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t < a.img_n) a.img[t] = 0.f;
+}
+
 template <int SP>
 __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
+  clear_image(a);
   const int lane = threadIdx.x & 63;
   // wave-uniform work index: chunk g, depth slice starting at d0
   const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -176,6 +184,7 @@ __global__ __launch_bounds__(256, KSP == SP_F32 && DT == 1 ? 3 : 1) void rsd_pro
   using M = Mfma<F::SP>;
   constexpr int NPL = F::NPL, NT = F::NT, FL = F::FL, FS = 2 * FL;
   extern __shared__ float2 ws[];  // weights w_f, zero from Nf to the last step's end
+  clear_image(a);
   const int lane = threadIdx.x & 63;
   const int hl = lane >> 5, c32 = lane & 31;
   const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

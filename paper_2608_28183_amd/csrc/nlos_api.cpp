@@ -847,10 +847,6 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   }
   const long long RH = (long long)L.rs_half, RF = (long long)L.rs_full;
   const float2* tw = ctx->d_tw;
-  if (d_img)
-    HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FILL, [&] {
-      return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(d_img), (size_t)nx * ny, 0u, s);
-    }));
 
   if (ex) {
     // FP16: power-of-two storage scales from the bound sum |tau| t/(nt-1)
@@ -1304,10 +1300,6 @@ static nlos_status rsd_run(nlos_ctx* ctx, const nlos_rsd_plan* p, hipStream_t s,
   void* C = base + L.b_off * es;    // [My][Mx][Nds]
   void* D = base;                   // [ny][Mx][Nds]
   const float2* tw = ctx->d_tw;
-  if (d_img)
-    HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FILL, [&] {
-      return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(d_img), (size_t)nx * ny, 0u, s);
-    }));
   // FP16 storage exponents: [0] P, X, P^; [1 + d] C at depth d; [1 + Nd + d] D at depth d
   int* ex = nullptr;
   if (sp == nlos::SP_F16) {
@@ -1362,6 +1354,7 @@ static nlos_status rsd_run(nlos_ctx* ctx, const nlos_rsd_plan* p, hipStream_t s,
   // four-byte data exist only on the matrix cores
   r.mfma = sp != nlos::SP_F32 && ctx->rsd_mfma == 0 ? 1 : ctx->rsd_mfma;
   r.data_sp = sp; r.e_ph = ex; r.e_c = e_pc;
+  if (d_img && !d_field) { r.img = d_img; r.img_n = nx * ny; }
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_RSD_PROPAGATE, [&] { return nlos::launch_rsd_propagate(r, s); }));
   // 5. y-IFFT per depth column, keep y < ny: C -> D[y][kx][d] (FP16: per-depth exponents)
   a = StridedArgs{};
@@ -1886,8 +1879,7 @@ nlos_status nlos_moe(nlos_ctx* ctx, const nlos_moe_plan* p, const float* d_tau, 
     s1 = ctx->aux;
   }
   HIP_TRY(ctx, timed(ctx, NLOS_PASS_FILL, [&] {
-    hipError_t e = nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(img_fk), (size_t)nx * ny, 0u, s0);
-    return e != hipSuccess ? e : nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(img_rsd), (size_t)nx * ny, 0u, s0);
+    return nlos::launch_fill_u32(reinterpret_cast<uint32_t*>(img_rsd), (size_t)nx * ny, 0u, s0);
   }));
   // shared: x and y FFTs of the (unscaled) transient -> W2
   FkXArgs x{};

@@ -83,7 +83,7 @@ struct ContigArgs {
   int n_in, n_out;
   float oscale;        // CS_ABS_IMG: output = |v| * oscale; CS_ABS2_MAX: |v|^2 * oscale
   float* img;          // CS_ABS_IMG: img[(ln % img_lines) * out_line + n] = max over lines;
-                       // CS_ABS2_MAX: img[ln] = max over the line
+                       // (img zero beforehand); CS_ABS2_MAX: img[ln] = max over the line
   long long img_lines;
   const int* bins;     // CS_BINS: out[ln * out_line + f] = X[bins[f]], f < nbins
   int nbins;
@@ -165,6 +165,8 @@ struct RsdPropArgs {
                            // written as value * 2^e_c[d]
   const int* e_ph;
   const int* e_c;
+  float* img;              // image of img_n values the propagation clears for the last pass (or null)
+  long long img_n;         // at most one value per padded pixel
   int mfma;                // propagation on the matrix cores: 0 no (FP32 FMAs), 1 yes, 2 yes
                            // with the other depth tiling
 };
