@@ -159,8 +159,20 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_c64_s
   const int tid = threadIdx.x;
   const int c = tid % T;
   const int p = tid / T;
+  // the twiddles of three-stage plans in LDS, of two-stage plans in registers
+  constexpr bool TWL = S::NSTAGE == 3 && E_ == 8;
+  constexpr int NW1 = TWL ? S::R1 * S::R0 : 1, NW2 = TWL ? (S::R2 - 1) * S::R0 * S::R1 : 1;
+  __shared__ float2 wt[NW1];
+  __shared__ float2 wt2[NW2];
   TwRegs<S> twr;
-  twr.load(p, tw);
+  if constexpr (TWL) {
+    for (int k = tid; k < NW1; k += C::THREADS) wt[k] = tw[(k % S::R0) * (k / S::R0) * (kTwiddleN / (S::R0 * S::R1))];
+    for (int k = tid; k < NW2; k += C::THREADS)
+      wt2[k] = tw[(k % (S::R0 * S::R1)) * (1 + k / (S::R0 * S::R1)) * (kTwiddleN / N)];
+    __syncthreads();
+  } else {
+    twr.load(p, tw);
+  }
   // the twiddles arrive before the first item's loads are issued: the waits of the loop
   // then count only that loop's own loads and stores
   __builtin_amdgcn_s_waitcnt(0);
@@ -211,7 +223,8 @@ __global__ __launch_bounds__((StridedCfg<N, E, T_>::THREADS)) void strided_c64_s
     if (it + 2 * step < nitems) nxt = item(it + 2 * step);
     if (it + step < nitems) fetch(cur);
 
-    fft_stages<S, INV>(v, p, lds, idx, twr);
+    if constexpr (TWL) fft_stages<S, INV>(v, p, lds, idx, TwLds<S>{wt, wt2});
+    else fft_stages<S, INV>(v, p, lds, idx, twr);
     // last stage: butterfly b of thread p holds outputs n = p + b P + r (N / RL); the
     // lower half is r < RL / 2
     const __amdgpu_buffer_rsrc_t out = buf_view(static_cast<float2*>(a.out) + item_plane(e) * a.out_plane);
@@ -463,15 +476,18 @@ static hipError_t launch_zifft_stream(const ContigArgs& a, const float2* tw, hip
 }
 
 // (samples per thread, columns per block) of the strided passes, from timing sweeps at
-// 512-point lines (256x256x512 f-k): forward y pass E=16 T=16, inverse passes E=8 T=16;
-// 256-point lines use 32 columns (256-byte rows).  With four-byte storage the 512-point
-// passes double their columns so that a row segment stays 128 bytes (a whole cache line:
-// 64-byte segments fetch every line twice); 256-point lines keep 32 columns, already
-// 128 bytes at four bytes, since 64 would need 128 KB of LDS per block (one block per CU).
+// 512-point lines (256x256x512 f-k): E=8 T=16, three stages whose twiddles sit in LDS: 61
+// registers, so that two blocks of 1024 threads and their loads in flight share a CU (x-IFFT
+// 185 -> 171 us, y-IFFT 147 -> 134 against the twiddles in registers, 83 of them and one
+// block; forward E=16 108.5 us, E=8 106.5); 256-point lines use 32 columns (256-byte rows).
+// With four-byte storage the 512-point passes double their columns so that a row segment
+// stays 128 bytes (a whole cache line: 64-byte segments fetch every line twice); 256-point
+// lines keep 32 columns, already 128 bytes at four bytes, since 64 would need 128 KB of LDS
+// per block (one block per CU).
 template <int N, bool INV, int LD, int ST, int SP = SP_F32>
 struct StridedTune {
   static constexpr bool WIDE = SP != SP_F32;
-  static constexpr int E = (N == 512) ? (INV && !WIDE ? 8 : 16) : default_e(N);
+  static constexpr int E = (N == 512) ? (WIDE ? 16 : 8) : default_e(N);
   static constexpr int T = (N == 512) ? (WIDE ? 32 : 16) : (N == 256 ? 32 : default_t(N));
 };
 
