@@ -4,7 +4,7 @@
 Default workload: f-k migration of a 256 x 256 x 512 confocal transient
 (32 ps bins, 1 m wall, seeded scene of 5 planar patches and 3 spheres), zero
 padded to 512 x 512 x 1024, FP32, input resident in HBM.  One step is one
-complete nlos_fk call (5 kernel passes + the image clear).  Prints one JSON
+complete nlos_fk call (6 kernel passes).  Prints one JSON
 line with volumes/s, the HBM roofline of the dominant kernel and the FP64
 oracle's CPU throughput on a bounded sample of the same workload.
 
@@ -27,21 +27,51 @@ F32_VALU_PEAK_TFLOPS = 157.3
 MFMA_F16_PEAK_TFLOPS = 2500.0  # dense FP16 / BF16 matrix cores
 
 
-def fk_pass_bytes(ny, nx, nt, pad, c=8, xfirst=True):
+def fk_support(ny, nx, nt, pad, wall_w, wall_h, bin_ps):
+    """Depth samples kz < nt of every column of the remapped spectrum that can be non-zero,
+    [My][Mx] in signed-frequency order: the Stolt remap of column (kx, ky) vanishes where
+    A(kx, ky) + kz^2 > (Mt/2 - 1)^2."""
+    import numpy as np
+    Mx, My, Mt = pad * nx, pad * ny, pad * nt
+    half = 0.5 * 299792458.0 * bin_ps * 1e-12
+    ax = half * nx / wall_w * Mt / Mx * np.abs(np.fft.fftfreq(Mx, 1.0 / Mx))
+    ay = half * ny / wall_h * Mt / My * np.abs(np.fft.fftfreq(My, 1.0 / My))
+    rem = (Mt // 2 - 1.0) ** 2 - (ay[:, None] ** 2 + ax[None, :] ** 2)
+    n = np.minimum(np.floor(np.sqrt(np.maximum(rem, 0.0))).astype(np.int64), Mt // 2 - 1) + 1
+    return np.minimum(np.where(rem >= 1.0, n, 0), nt)
+
+
+def fk_pass_bytes(ny, nx, nt, pad, c=8, xfirst=True, geom=None):
     """Algorithmic HBM bytes of each f-k pass of the schedule: every pruned intermediate
     written once and read once as c-byte complex values (8: FP32; 4: FP16 / BF16) -- half spectra
     kx <= Mx/2 up to the column pass, the z-IFFT last on the cropped ny x nx columns --
     tau read and vol written as float32.  The schedule (xfirst) runs the x-IFFT before the
-    y-IFFT; the shared-spectrum mixture runs the y-IFFT first."""
+    y-IFFT; the shared-spectrum mixture runs the y-IFFT first.  With geom = (wall_w, wall_h,
+    bin_ps) the zeros of the remapped spectrum (fk_support) and the spectra that only feed
+    them are left out, as nlos_fk does; the mixture's own passes move every sample."""
     Mx, My = pad * nx, pad * ny
     Mh = Mx // 2 + 1
+    if xfirst and geom is not None:
+        n = fk_support(ny, nx, nt, pad, *geom)
+        nh = n[:, :Mh]
+        kept = int((nh > 0).any(axis=0).sum())  # kx = 0 .. kmax
+        rows = int((nh > 0).sum())              # (kx, ky) the column pass reads
+        line0 = int(n[:, 0].sum())              # samples with any kx
+        nz = int(n.max())
+        return {
+            "fk_x": 4 * ny * nx * nt + c * ny * kept * nt,
+            "fk_y": c * ny * kept * nt + c * rows * nt,
+            "fk_column": c * rows * nt + c * int(n.sum()),
+            "fk_xi": c * int(n.sum()) + c * nx * line0,
+            "fk_yi": c * nx * line0 + c * ny * nx * nz,
+            "fk_zi": c * ny * nx * nz + 4 * ny * nx * nt + 4 * ny * nx,
+        }
     nwork = (Mx // 2 - 1) * My + 2 * (My // 2 + 1)
     out = {
         "fk_x": 4 * ny * nx * nt + c * ny * Mh * nt,
         "fk_y": c * ny * Mh * nt + c * My * Mh * nt,
         "fk_column": c * nwork * nt + c * My * Mx * nt,
         "fk_zi": c * ny * nx * nt + 4 * ny * nx * nt + 4 * ny * nx,
-        "fill": 4 * ny * nx,
     }
     if xfirst:
         out["fk_xi"] = c * My * Mx * nt + c * My * nx * nt
@@ -75,18 +105,17 @@ def rsd_pass_bytes(ny, nx, nt, pad, nf, nd, nrho, nchunks=0, kernel_bytes=8, dat
         + c * My * Mx * nd,
         "rsd_yi": c * My * Mx * nd + c * ny * Mx * nd,
         "rsd_xi": c * ny * Mx * nd + 4 * ny * nx * nd + 4 * ny * nx,
-        "fill": 4 * ny * nx,
     }
 
 
-def moe_pass_bytes(ny, nx, nt, pad, nf, nd, nrho, shared=False):
+def moe_pass_bytes(ny, nx, nt, pad, nf, nd, nrho, shared=False, geom=None):
     """Algorithmic bytes of the mixture-of-experts passes: the f-k passes (images only,
     no volume), the RSD phasors -- from the shared half spectrum (shared schedule) or the
     transient followed by the x and y passes (branches in sequence) -- the RSD
     propagation and inverse passes (image only) and the mixture."""
     Mx, My = pad * nx, pad * ny
-    fk = fk_pass_bytes(ny, nx, nt, pad, xfirst=not shared)
-    fk["fk_zi"] = 8 * ny * nx * nt + 4 * ny * nx
+    fk = fk_pass_bytes(ny, nx, nt, pad, xfirst=not shared, geom=geom)
+    fk["fk_zi"] -= 4 * ny * nx * nt
     rsd = rsd_pass_bytes(ny, nx, nt, pad, nf, nd, nrho)
     out = {k: fk[k] for k in ("fk_x", "fk_y", "fk_column", "fk_yi", "fk_xi", "fk_zi")}
     if shared:
@@ -98,7 +127,7 @@ def moe_pass_bytes(ny, nx, nt, pad, nf, nd, nrho, shared=False):
     out["rsd_yi"] = rsd["rsd_yi"]
     out["rsd_xi"] = 8 * ny * Mx * nd + 4 * ny * nx
     out["moe_mix"] = 4 * 4 * ny * nx
-    out["fill"] = 8 * ny * nx
+    out["fill"] = 4 * ny * nx
     return out
 
 
@@ -295,7 +324,8 @@ def main():
         vol = torch.empty((ny, nx, nt), device=dev)
         img = torch.empty((ny, nx), device=dev)
         step = lambda: plan(tau, vol, img, ws)  # noqa: E731
-        pass_bytes = fk_pass_bytes(ny, nx, nt, cfg.pad, 8 if args.prec == "fp32" else 4)
+        pass_bytes = fk_pass_bytes(ny, nx, nt, cfg.pad, 8 if args.prec == "fp32" else 4,
+                                   geom=(cfg.wall_w, cfg.wall_h, cfg.bin_ps))
         if args.prec == "fp16":
             pass_bytes["fk_scale"] = 4 * ny * nx * nt  # the bound's read of tau
         metric, unit = "fk_volumes_per_s", "volumes/s"
@@ -340,7 +370,8 @@ def main():
         step = lambda: plan(tau, img, None, None, ws)  # noqa: E731
         g = nlos.nlos_rsd_geometry_get(plan.rsd_desc)
         nf = len(p.freq_bins)
-        pass_bytes = moe_pass_bytes(ny, nx, nt, cfg.pad, nf, p.n_depth, g["n_rho"])
+        pass_bytes = moe_pass_bytes(ny, nx, nt, cfg.pad, nf, p.n_depth, g["n_rho"],
+                                    geom=(cfg.wall_w, cfg.wall_h, cfg.bin_ps))
         metric, unit = "moe_images_per_s", "images/s"
         units_per_step = 1
         workload = {"workload": f"mixture of experts f-k x RSD (Eq. 10, beta 0.3) on {ny}x{nx}x{nt} "
@@ -381,7 +412,7 @@ def main():
             nlos.nlos_fk_complex(ctx.handle, plan.handle, taus[counter[0] & 1], psi, ws)
             nlos.nlos_merge_push(ctx.handle, mstate, psi, merged, coh)
             counter[0] += 1
-        pass_bytes = fk_pass_bytes(ny, nx, nt, cfg.pad)
+        pass_bytes = fk_pass_bytes(ny, nx, nt, cfg.pad, geom=(cfg.wall_w, cfg.wall_h, cfg.bin_ps))
         pass_bytes["fk_zi"] = 16 * ny * nx * nt
         pass_bytes["merge"] = (8 + 8 + 8 * (window - 1) + 8) * ny * nx * nt
         metric, unit = "merged_fk_volumes_per_s", "volumes/s"
@@ -504,12 +535,14 @@ def main():
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "algorithmic_bytes": pass_bytes[dom], "avg_ms": round(avg_ms[dom], 4)}
     if kind == "rsd" and dom == "rsd_propagate":
-        # the propagation is a contraction: priced against the arithmetic peak it runs on
-        # (matrix cores for FP16 / BF16 kernels, FP32 FMAs otherwise), bytes kept beside
+        # the propagation is a contraction: priced against the arithmetic peak it runs on (the
+        # matrix cores; an FP32 kernel takes six bfloat16 products per FP32 product), bytes
+        # kept beside
         tflops = prop_flops / (avg_ms[dom] * 1e-3) / 1e12
         on_fma = os.environ.get("NLOS_RSD_MFMA", "1") == "0"
-        # FP32 matrix cores and FP32 vector FMAs share the published 157.3 TFLOP/s
-        peak = MFMA_F16_PEAK_TFLOPS if args.prec != "fp32" else F32_VALU_PEAK_TFLOPS
+        peak = MFMA_F16_PEAK_TFLOPS / (6 if args.prec == "fp32" else 1)
+        if on_fma:
+            peak = F32_VALU_PEAK_TFLOPS
         roofline = {"bound": "alu" if on_fma else "mfma", "kernel": dom,
                     "achieved": round(tflops, 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(tflops / peak, 4), "traffic": traffic, "algorithmic_flops": prop_flops,
@@ -552,7 +585,9 @@ def main():
                 torch.cuda.synchronize()
                 precision_path[pr] = {"value": round(1.0 / psec, 3), "unit": unit, "ms_per_step": round(psec * 1e3, 4),
                                       "speedup_vs_fp32": round(sec / psec, 3),
-                                      "step_bytes": sum(fk_pass_bytes(ny, nx, nt, cfg.pad, 4).values()),
+                                      "step_bytes": sum(fk_pass_bytes(
+                                          ny, nx, nt, cfg.pad, 4,
+                                          geom=(cfg.wall_w, cfg.wall_h, cfg.bin_ps)).values()),
                                       "per_call": pc, "accuracy": golden_accuracy(f"fk_{cname}", vol, img)}
                 del pws
             step()  # leave the FP32 result in vol / img
