@@ -4,6 +4,8 @@
 #ifndef NLOS_DEBUG_H
 #define NLOS_DEBUG_H
 
+#include "nlos.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -14,6 +16,11 @@ extern "C" {
  * NLOS_ERR_OUT_OF_MEMORY with nothing enqueued and nothing leaked, and the context stays
  * usable.  n = 0 clears the injection.  Process wide; for fault-path tests. */
 void nlos_debug_fail_allocations(int n);
+
+/* Host only: entries of the work lists (tiles and columns that can be non-zero after the
+ * Stolt remap) an f-k plan of this descriptor is created with; 0 where its passes run over
+ * every tile and column. */
+nlos_status nlos_debug_fk_lists(const nlos_fk_desc *desc, size_t *n_items);
 
 #ifdef __cplusplus
 }

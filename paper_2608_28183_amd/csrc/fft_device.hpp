@@ -20,6 +20,8 @@
 #include <type_traits>
 #include <utility>
 
+#include "nlos_internal.hpp"
+
 namespace nlos {
 
 constexpr int kTwiddleN = 2048;  // length of the device twiddle table W_2048^k
@@ -109,9 +111,8 @@ __device__ __forceinline__ void st_stream(float4* p, float4 v) {
 // A buffer view of the bytes at a wave-uniform base: a load from kBufNone returns zero and a
 // store to it is dropped, both without memory traffic, so that a thread issues the same
 // accesses whether an element is wanted or not (no branch between loads in flight).
-// Offsets in bytes, below kBufMax.
+// Offsets in bytes, below kBufMax (strided_fits).
 constexpr unsigned int kBufNone = 0xfffffff8u;
-constexpr long long kBufMax = 0xfffffff0LL;
 typedef unsigned int nlos_u2 __attribute__((ext_vector_type(2)));
 typedef unsigned int nlos_u4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_view(const void* base) {

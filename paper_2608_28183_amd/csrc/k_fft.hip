@@ -499,6 +499,7 @@ static hipError_t launch_strided_n(const StridedArgs& a, int nplanes, const floa
   dim3 grid((a.ncols + C::T - 1) / C::T, nplanes);
   if constexpr (LD == LD_C64 && ST == ST_C64 && (NT || SP != SP_F32)) {
     if (a.items != nullptr) {
+      if (!strided_fits(a, SP == SP_F32 ? 8 : 4)) return hipErrorInvalidValue;
       hipLaunchKernelGGL((strided_fft<N, E, T, INV, LD, ST, SP, NT, true>), dim3((unsigned)a.nitems), dim3(C::THREADS),
                          0, s, a, tw);
       return hipGetLastError();

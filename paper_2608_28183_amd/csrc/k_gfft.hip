@@ -311,7 +311,8 @@ int gen_strided_cols(int n) { return gen_cols(n); }
 
 hipError_t launch_gen_strided(const GenPlan& g, bool inverse, int st, const StridedArgs& a, int nplanes,
                               hipStream_t s) {
-  if (a.ncols <= 0 || nplanes <= 0 || a.n_out > g.n || (a.items != nullptr && a.nitems <= 0)) return hipErrorInvalidValue;
+  if (a.ncols <= 0 || nplanes <= 0 || a.n_out > g.n || (a.items != nullptr && (a.nitems <= 0 || !strided_fits(a, 8))))
+    return hipErrorInvalidValue;
   switch (st) {
     case ST_C64: return inverse ? gen_strided_st<true, ST_C64>(g, a, nplanes, s)
                                 : gen_strided_st<false, ST_C64>(g, a, nplanes, s);

@@ -424,7 +424,7 @@ bool mfma_strided_ok(int n, int sp, const StridedArgs& a) {
 
 hipError_t launch_strided_mfma(int n, bool inverse, const StridedArgs& a, int nplanes, const MfmaTables& t,
                                const float2* tw, hipStream_t s, int sp) {
-  if (!mfma_strided_ok(n, sp, a)) return hipErrorInvalidValue;
+  if (!mfma_strided_ok(n, sp, a) || (a.items != nullptr && !strided_fits(a, 4))) return hipErrorInvalidValue;
   const int bf = sp == SP_BF16 ? 1 : 0;
   const int scaled = (inverse && sp == SP_F16) ? 1 : 0;  // FP16 inverse: outputs carry 2^-log2(N) more
   const mf_u4* t1 = static_cast<const mf_u4*>(t.a16[inverse][scaled][bf]);

@@ -689,7 +689,8 @@ nlos_status nlos_fk_desc_workspace_bytes(const nlos_fk_desc* d, size_t* bytes) {
 // neither stored nor read, and spectra that only feed zeros are not formed: a column ends
 // at nz(kx, ky) (rounded up to the inverse passes' tiles), the y pass keeps |ky| up to its
 // plane's bound, the x pass kx up to kmax.
-static hipError_t fk_schedule(nlos_fk_plan* p) {
+// Host only: fills list, kmax, nz and w4_bytes and returns the entries (none: a plan without lists).
+static std::vector<uint2> fk_schedule(nlos_fk_plan* p) {
   const nlos_fk_desc& d = p->d;
   const int nx = d.nx, nt = d.nt, Mx = p->Mx, My = p->My;
   const int sp = fk_sp(d.prec), half = p->Mt / 2;
@@ -718,10 +719,16 @@ static hipError_t fk_schedule(nlos_fk_plan* p) {
   p->kmax = hx;
   p->nz = nt;
   p->w4_bytes = (size_t)My * nx * nt * fk_elem_bytes(d.prec);
-  if (zeros < kMinZeroBytes) return hipSuccess;
-  // the listed passes address a plane with 32-bit byte offsets
+  if (zeros < kMinZeroBytes) return {};
+  // the listed passes address a plane with 32-bit byte offsets: without lists where the furthest
+  // sample of any of them lies beyond (the y-IFFT's rows are nx nt long, without padding almost
+  // twice the half spectrum's)
   const FkLayout L = fk_layout(&d);
-  if (std::max((size_t)My * L.rs_half, (size_t)Mx * nt) * L.es > 0xf0000000u) return hipSuccess;
+  const size_t rows[6][2] = {{(size_t)d.ny, L.rs_half}, {(size_t)My, L.rs_half},         // y pass: in, out
+                             {(size_t)Mx, (size_t)nt}, {(size_t)nx, (size_t)nt},         // x-IFFT
+                             {(size_t)My, fk_row_stride(nx, nt, L.es)}, {(size_t)d.ny, (size_t)nx * nt}};  // y-IFFT
+  for (const auto& r : rows)
+    if (nlos::plane_span(r[0], r[1], nt, L.es) > nlos::kBufMax) return {};
   p->kmax = 0;
   while (p->kmax < hx && NZ(0, p->kmax + 1) > 0) ++p->kmax;
   p->nz = NZ(0, 0);
@@ -761,10 +768,42 @@ static hipError_t fk_schedule(nlos_fk_plan* p) {
       push(x, j, c);
     }
   p->list[4] = (int)it.size();
-  hipError_t e = nlos::dev_alloc((void**)&p->d_items, it.size() * sizeof(uint2));
-  if (e == hipSuccess) e = hipMemcpy(p->d_items, it.data(), it.size() * sizeof(uint2), hipMemcpyHostToDevice);
-  return e;
+  return it;
 }
+
+// The sizes and factors of a plan of (valid) descriptor d
+static void fk_plan_sizes(const nlos_fk_desc* d, nlos_fk_plan* p) {
+  p->d = *d;
+  p->Mx = d->pad * d->nx;
+  p->My = d->pad * d->ny;
+  p->Mt = d->pad * d->nt;
+  const double c_dt = kC * d->bin_ps * 1e-12;
+  const double sx = c_dt / (2.0 * (d->wall_w_m / d->nx));
+  const double sy = c_dt / (2.0 * (d->wall_h_m / d->ny));
+  p->sxk = sx * (double)p->Mt / (double)p->Mx;
+  p->syk = sy * (double)p->Mt / (double)p->My;
+  p->norm = (float)(1.0 / ((double)p->Mx * (double)p->My * (double)p->Mt));
+  // general axis lengths (the x pass also for odd nt: see gen_xr2c)
+  p->gen_x = !is_pow2_in(p->Mx, 8, 2048);
+  p->gen_y = !is_pow2_in(p->My, 8, 2048);
+  p->gen_t = !is_pow2_in(p->Mt, 8, 2048);
+  p->gen_xr2c = p->gen_x || (d->nt & 1) != 0;
+}
+
+nlos_status nlos_debug_fk_lists(const nlos_fk_desc* d, size_t* n_items) {
+  try {
+    const nlos_status st = nlos_fk_check(d);
+    if (st != NLOS_OK) return st;
+    if (!n_items) return fail(nullptr, NLOS_ERR_INVALID_ARG, "nlos_debug_fk_lists: n_items is NULL");
+    nlos_fk_plan p;
+    fk_plan_sizes(d, &p);
+    *n_items = fk_schedule(&p).size();
+    return NLOS_OK;
+  } catch (const std::bad_alloc&) {
+    return fail(nullptr, NLOS_ERR_OUT_OF_MEMORY, "nlos_debug_fk_lists: host allocation failed");
+  }
+}
+
 
 nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_plan** out) {
   try {
@@ -774,28 +813,18 @@ nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_pl
     nlos::host_alloc_point();
     nlos_fk_plan* p = new (std::nothrow) nlos_fk_plan();
     if (!p) return fail(ctx, NLOS_ERR_OUT_OF_MEMORY, "fk_plan_create: host allocation");
-    p->d = *d;
+    fk_plan_sizes(d, p);
     p->device = ctx->device;
-    p->Mx = d->pad * d->nx;
-    p->My = d->pad * d->ny;
-    p->Mt = d->pad * d->nt;
-    const double c_dt = kC * d->bin_ps * 1e-12;
-    const double sx = c_dt / (2.0 * (d->wall_w_m / d->nx));
-    const double sy = c_dt / (2.0 * (d->wall_h_m / d->ny));
-    p->sxk = sx * (double)p->Mt / (double)p->Mx;
-    p->syk = sy * (double)p->Mt / (double)p->My;
-    p->norm = (float)(1.0 / ((double)p->Mx * (double)p->My * (double)p->Mt));
-    // general axis lengths (the x pass also for odd nt: see gen_xr2c)
-    p->gen_x = !is_pow2_in(p->Mx, 8, 2048);
-    p->gen_y = !is_pow2_in(p->My, 8, 2048);
-    p->gen_t = !is_pow2_in(p->Mt, 8, 2048);
-    p->gen_xr2c = p->gen_x || (d->nt & 1) != 0;
     const int m[3] = {p->Mx, p->My, p->Mt};
     const bool use[3] = {p->gen_xr2c, p->gen_y, p->gen_t};
     nlos::GenPlan* const g[3] = {&p->gx, &p->gy, &p->gt};
     hipError_t e = gen_tables(ctx->device, m, use, g, 3, &p->d_gtw);
-    if (e == hipSuccess) e = hipSetDevice(ctx->device);
-    if (e == hipSuccess) e = fk_schedule(p);
+    const std::vector<uint2> it = fk_schedule(p);
+    if (e == hipSuccess && !it.empty()) {
+      e = hipSetDevice(ctx->device);
+      if (e == hipSuccess) e = nlos::dev_alloc((void**)&p->d_items, it.size() * sizeof(uint2));
+      if (e == hipSuccess) e = hipMemcpy(p->d_items, it.data(), it.size() * sizeof(uint2), hipMemcpyHostToDevice);
+    }
     if (e != hipSuccess) {
       nlos_fk_plan_destroy(p);
       return fail(ctx, e == hipErrorOutOfMemory ? NLOS_ERR_OUT_OF_MEMORY : NLOS_ERR_DEVICE,

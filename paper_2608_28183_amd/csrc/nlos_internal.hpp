@@ -30,6 +30,14 @@ inline long long resident_blocks(int threads) {
   return (long long)cus * per;
 }
 
+// 32-bit byte offsets of a buffer view (buf_view) reach less than kBufMax bytes beyond its base
+constexpr long long kBufMax = 0xfffffff0LL;
+// Bytes from a plane's first sample to the end of its last: `rows` rows `line` samples of es
+// bytes apart, ncols columns.
+constexpr long long plane_span(long long rows, long long line, long long ncols, long long es) {
+  return ((rows - 1) * line + ncols) * es;
+}
+
 // storage precision of complex intermediates (float2, __half2, __hip_bfloat162)
 enum { SP_F32 = 0, SP_F16 = 1, SP_BF16 = 2 };
 
@@ -170,6 +178,11 @@ struct RsdPropArgs {
   int mfma;                // propagation on the matrix cores: 0 no (FP32 FMAs), 1 yes, 2 yes
                            // with the other depth tiling
 };
+
+// Every sample of a plane within reach of 32-bit buffer offsets, as the listed passes need
+inline bool strided_fits(const StridedArgs& a, int es) {
+  return plane_span(a.n_in, a.in_line, a.ncols, es) <= kBufMax && plane_span(a.n_out, a.out_line, a.ncols, es) <= kBufMax;
+}
 
 // stream: the f-k passes (FP32 LD_C64 -> ST_C64), as resident blocks where the shape allows
 // Columns per tile of launch_strided (stream as below), launch_strided_mfma (32) and

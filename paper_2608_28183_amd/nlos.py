@@ -132,6 +132,7 @@ _SIGNATURES = {
     "nlos_graph_launch": (_ST, [_VP, _VP]),
     "nlos_graph_destroy": (_ST, [_VP]),
     "nlos_debug_fail_allocations": (None, [ctypes.c_int]),
+    "nlos_debug_fk_lists": (_ST, [ctypes.POINTER(nlos_fk_desc), ctypes.POINTER(ctypes.c_size_t)]),
 }
 
 _lib = None
@@ -182,6 +183,13 @@ def _stream_handle(stream) -> Optional[int]:
 def nlos_debug_fail_allocations(n: int) -> None:
     """Test hook (include/nlos_debug.h): the next n allocations of the library fail."""
     lib().nlos_debug_fail_allocations(n)
+
+
+def nlos_debug_fk_lists(desc: nlos_fk_desc) -> int:
+    """Test hook (include/nlos_debug.h): entries of the work lists of a plan of desc (host only)."""
+    out = ctypes.c_size_t(0)
+    _check(lib().nlos_debug_fk_lists(ctypes.byref(desc), ctypes.byref(out)), "nlos_debug_fk_lists")
+    return out.value
 
 
 def nlos_version() -> int:
