@@ -163,7 +163,9 @@ __global__ __launch_bounds__(kGenMaxThreads) void gen_contig(ContigArgs a, GenPl
       const int W = P < 64 ? P : 64;  // lanes of one line within a wave
       for (int off = 1; off < W; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, W));
       if (P > 64) {  // a line over several waves (one line per block from 256 threads)
-        __shared__ float part[kGenMaxThreads / 64];
+        // in the twiddle table's place, which every thread is done with: LDS of its own cost
+        // 2000-point lines their fifth block per CU (156 -> 173 us at 128 x 128 x 1000)
+        float* part = reinterpret_cast<float*>(twl);
         if ((tid & 63) == 0) part[tid >> 6] = m;
         __syncthreads();
         if (p == 0)
