@@ -10,8 +10,6 @@
 #include "nlos_internal.hpp"
 #include "prec.hpp"
 
-#include <algorithm>
-
 namespace nlos {
 
 // NT: non-temporal loads and stores of the FP32 complex lines (the f-k volumes)
@@ -558,7 +556,7 @@ static bool launch_strided_stream(int n, bool inverse, const StridedArgs& a, int
   const bool fwd_half = !inverse && 2 * a.n_in == n && a.n_out == n;
   const bool inv_half = inverse && a.n_in == n && 2 * a.n_out == n;
   if (!fwd_half && !inv_half) return false;
-  if (8 * (a.ncols + n * std::max(a.in_line, a.out_line)) > kBufMax) return false;  // buffer offsets
+  if (!strided_fits(a, 8)) return false;  // buffer offsets
   switch (n) {
     case 256: err = inverse ? launch_strided_stream_n<256, true, false, true>(a, nplanes, tw, s)
                             : launch_strided_stream_n<256, false, true, false>(a, nplanes, tw, s); return true;
