@@ -198,6 +198,10 @@ nlos_status nlos_fk_check(const nlos_fk_desc *desc);
  * only, no plan required): about half the FP32 figure for NLOS_FP16 / NLOS_BF16 (FP16 adds
  * 4.3 KB of scale scratch). */
 nlos_status nlos_fk_desc_workspace_bytes(const nlos_fk_desc *desc, size_t *bytes);
+/* A plan whose remapped spectrum has many zeros also holds lists of the tiles and columns that
+ * can be non-zero in device memory (up to a few MB); where that cannot be had it runs without,
+ * slower and with the last bits rounded otherwise.  Plans of power-of-two sizes can be created,
+ * and destroyed, while streams are under capture. */
 nlos_status nlos_fk_plan_create(nlos_ctx *ctx, const nlos_fk_desc *desc, nlos_fk_plan **out);
 nlos_status nlos_fk_plan_destroy(nlos_fk_plan *plan);
 /* Exact device workspace one nlos_fk call on plan needs (host only; the same figure as

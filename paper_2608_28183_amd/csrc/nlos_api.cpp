@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <thread>
@@ -28,8 +29,13 @@ using nlos::StridedArgs;
 namespace nlos {
 
 std::atomic<int> g_fail_allocs{0};
+std::atomic<int> g_pass_allocs{0};  // allocations let through before the failing ones
 namespace {
 bool take_injected_failure() {
+  if (g_fail_allocs.load() <= 0) return false;
+  int k = g_pass_allocs.load();
+  while (k > 0)
+    if (g_pass_allocs.compare_exchange_weak(k, k - 1)) return false;
   int n = g_fail_allocs.load();
   while (n > 0)
     if (g_fail_allocs.compare_exchange_weak(n, n - 1)) return true;
@@ -188,12 +194,12 @@ struct nlos_fk_plan {
   nlos_fk_desc d{};
   int device = 0;
   // The work lists (fk_schedule) of the y pass, the column pass and the x- and y-IFFT: entries
-  // list[i] .. list[i + 1] of d_items (null: every item).  kmax: largest kx needed; nz: depth
+  // list[i] .. list[i + 1] of items (null: every item).  kmax: largest kx needed; nz: depth
   // samples stored ahead of the z pass.
   int list[5] = {0, 0, 0, 0, 0};
   int kmax = 0, nz = 0;
   size_t w4_bytes = 0;        // of W4 that the x-IFFT writes
-  uint2* d_items = nullptr;
+  std::shared_ptr<uint2> items;
   int Mx = 0, My = 0, Mt = 0;
   double sxk = 0, syk = 0;
   float norm = 0.f;
@@ -226,6 +232,53 @@ struct nlos_rsd_plan {
   nlos::GenPlan gx{}, gy{}, gt{};
   float2* d_gtw = nullptr;
 };
+
+namespace {
+
+// For the time of its life, calls that a capture in progress would refuse (allocations) are
+// let through on this thread without touching the capture, and the current device may be
+// changed.
+struct Aside {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  int device = -1;
+  Aside() {
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (hipGetDevice(&device) != hipSuccess) device = -1;
+  }
+  ~Aside() {
+    if (device >= 0) (void)hipSetDevice(device);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+  Aside(const Aside&) = delete;
+  Aside& operator=(const Aside&) = delete;
+};
+
+// `v` in device memory, or null where there is none to be had.  The upload goes by a stream
+// of its own: it waits for no stream of the caller and enters no capture.
+template <class T>
+std::shared_ptr<T> device_copy(int device, const std::vector<T>& v) {
+  Aside aside;
+  void* d = nullptr;
+  hipStream_t s = nullptr;
+  hipError_t e = hipSetDevice(device);
+  if (e == hipSuccess) e = nlos::dev_alloc(&d, v.size() * sizeof(T));
+  if (e == hipSuccess) e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e == hipSuccess) e = hipMemcpyAsync(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (s) (void)hipStreamDestroy(s);
+  if (e != hipSuccess) {
+    if (d) (void)hipFree(d);
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return std::shared_ptr<T>(static_cast<T*>(d), [device](T* q) {
+    Aside a;
+    (void)hipSetDevice(device);
+    (void)hipFree(q);
+  });
+}
+
+}  // namespace
 
 static nlos_status fail(nlos_ctx* ctx, nlos_status s, const char* fmt, ...) {
   char buf[512];
@@ -287,7 +340,13 @@ static const char* const kPassNames[NLOS_PASS_COUNT] = {
 
 extern "C" {
 
-void nlos_debug_fail_allocations(int n) { nlos::g_fail_allocs.store(n > 0 ? n : 0); }
+void nlos_debug_fail_allocations(int n) { nlos_debug_fail_allocations_after(0, n); }
+
+void nlos_debug_fail_allocations_after(int k, int n) {
+  nlos::g_fail_allocs.store(0);
+  nlos::g_pass_allocs.store(k > 0 ? k : 0);
+  nlos::g_fail_allocs.store(n > 0 ? n : 0);
+}
 
 int nlos_version(void) { return 100; }
 
@@ -682,6 +741,14 @@ nlos_status nlos_fk_desc_workspace_bytes(const nlos_fk_desc* d, size_t* bytes) {
   return NLOS_OK;
 }
 
+// A plan's passes over every tile and column
+static void fk_no_lists(nlos_fk_plan* p) {
+  std::fill(p->list, p->list + 5, 0);
+  p->kmax = p->Mx / 2;
+  p->nz = p->d.nt;
+  p->w4_bytes = (size_t)p->My * p->d.nx * p->d.nt * fk_elem_bytes(p->d.prec);
+}
+
 // The work lists of a plan.  The Stolt remap of column (kx, ky) is zero where
 // A(kx, ky) + kz^2 > (Mt/2 - 1)^2 (A of stolt_pair): outside an ellipsoid of frequencies,
 // which fills 0.35 of the remapped half spectrum at 256 x 256 x 512 (1 m wall, 32 ps) and
@@ -689,8 +756,10 @@ nlos_status nlos_fk_desc_workspace_bytes(const nlos_fk_desc* d, size_t* bytes) {
 // neither stored nor read, and spectra that only feed zeros are not formed: a column ends
 // at nz(kx, ky) (rounded up to the inverse passes' tiles), the y pass keeps |ky| up to its
 // plane's bound, the x pass kx up to kmax.
-// Host only: fills list, kmax, nz and w4_bytes and returns the entries (none: a plan without lists).
+// Host only: fills list, kmax, nz and w4_bytes and returns the entries (none: a plan without
+// lists, all four as they were).
 static std::vector<uint2> fk_schedule(nlos_fk_plan* p) {
+  nlos::host_alloc_point();
   const nlos_fk_desc& d = p->d;
   const int nx = d.nx, nt = d.nt, Mx = p->Mx, My = p->My;
   const int sp = fk_sp(d.prec), half = p->Mt / 2;
@@ -716,9 +785,6 @@ static std::vector<uint2> fk_schedule(nlos_fk_plan* p) {
   size_t zeros = 0;
   for (int j = 0; j <= hy; ++j)
     for (int k = 0; k <= hx; ++k) zeros += (size_t)(nt - NZ(j, k)) * fk_elem_bytes(d.prec) * 4;
-  p->kmax = hx;
-  p->nz = nt;
-  p->w4_bytes = (size_t)My * nx * nt * fk_elem_bytes(d.prec);
   if (zeros < kMinZeroBytes) return {};
   // the listed passes address a plane with 32-bit byte offsets: without lists where the furthest
   // sample of any of them lies beyond (the y-IFFT's rows are nx nt long, without padding almost
@@ -788,6 +854,18 @@ static void fk_plan_sizes(const nlos_fk_desc* d, nlos_fk_plan* p) {
   p->gen_y = !is_pow2_in(p->My, 8, 2048);
   p->gen_t = !is_pow2_in(p->Mt, 8, 2048);
   p->gen_xr2c = p->gen_x || (d->nt & 1) != 0;
+  fk_no_lists(p);
+}
+
+// The work lists of a new plan, where it gets any.  They only save time: a plan whose lists
+// find no memory, on the host or on the device, runs over every tile and column.
+static void fk_plan_lists(nlos_fk_plan* p) {
+  try {
+    const std::vector<uint2> it = fk_schedule(p);
+    if (!it.empty()) p->items = device_copy(p->device, it);
+  } catch (const std::bad_alloc&) {
+  }
+  if (!p->items) fk_no_lists(p);
 }
 
 nlos_status nlos_debug_fk_lists(const nlos_fk_desc* d, size_t* n_items) {
@@ -819,17 +897,12 @@ nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_pl
     const bool use[3] = {p->gen_xr2c, p->gen_y, p->gen_t};
     nlos::GenPlan* const g[3] = {&p->gx, &p->gy, &p->gt};
     hipError_t e = gen_tables(ctx->device, m, use, g, 3, &p->d_gtw);
-    const std::vector<uint2> it = fk_schedule(p);
-    if (e == hipSuccess && !it.empty()) {
-      e = hipSetDevice(ctx->device);
-      if (e == hipSuccess) e = nlos::dev_alloc((void**)&p->d_items, it.size() * sizeof(uint2));
-      if (e == hipSuccess) e = hipMemcpy(p->d_items, it.data(), it.size() * sizeof(uint2), hipMemcpyHostToDevice);
-    }
     if (e != hipSuccess) {
       nlos_fk_plan_destroy(p);
       return fail(ctx, e == hipErrorOutOfMemory ? NLOS_ERR_OUT_OF_MEMORY : NLOS_ERR_DEVICE,
                   "fk_plan_create: general-length twiddle tables: %s", hipGetErrorString(e));
     }
+    fk_plan_lists(p);
     *out = p;
     return NLOS_OK;
   } catch (const std::bad_alloc&) {
@@ -845,10 +918,9 @@ nlos_status nlos_fk_workspace_bytes(const nlos_fk_plan* p, size_t* bytes) {
 
 nlos_status nlos_fk_plan_destroy(nlos_fk_plan* p) {
   if (!p) return NLOS_OK;
-  if (p->d_gtw || p->d_items) {
+  if (p->d_gtw) {
     (void)hipSetDevice(p->device);
-    if (p->d_gtw) (void)hipFree(p->d_gtw);
-    if (p->d_items) (void)hipFree(p->d_items);
+    (void)hipFree(p->d_gtw);
   }
   delete p;
   return NLOS_OK;
@@ -888,7 +960,7 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   }
   const bool mf = ctx->mfma && sp != nlos::SP_F32;
   auto list = [&](StridedArgs& a, int i) {
-    a.items = p->d_items ? p->d_items + p->list[i] : nullptr;
+    a.items = p->items ? p->items.get() + p->list[i] : nullptr;
     a.nitems = p->list[i + 1] - p->list[i];
   };
   // Cached or streaming (ordinary or non-temporal): an intermediate that fits the last-level cache is read from it by the
@@ -924,8 +996,8 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   // column and its mirror; the remapped spectra (kz < nt) go to W3
   FkPairArgs c{};
   c.in = W2; c.out = W3; c.in_row = RH; c.out_row = RF;
-  c.items = p->d_items ? p->d_items + p->list[1] : nullptr;
-  c.nwork = p->d_items ? p->list[2] - p->list[1] : (Mx / 2 - 1) * My + 2 * (My / 2 + 1);
+  c.items = p->items ? p->items.get() + p->list[1] : nullptr;
+  c.nwork = p->items ? p->list[2] - p->list[1] : (Mx / 2 - 1) * My + 2 * (My / 2 + 1);
   c.nt = (int)nt; c.Mx = (int)Mx; c.My = (int)My;
   c.sxk = p->sxk; c.syk = p->syk; c.norm = p->norm;
   c.e_in = ex; c.e_out = ex ? ex + 1 : nullptr;

@@ -132,6 +132,7 @@ _SIGNATURES = {
     "nlos_graph_launch": (_ST, [_VP, _VP]),
     "nlos_graph_destroy": (_ST, [_VP]),
     "nlos_debug_fail_allocations": (None, [ctypes.c_int]),
+    "nlos_debug_fail_allocations_after": (None, [ctypes.c_int, ctypes.c_int]),
     "nlos_debug_fk_lists": (_ST, [ctypes.POINTER(nlos_fk_desc), ctypes.POINTER(ctypes.c_size_t)]),
 }
 
@@ -183,6 +184,11 @@ def _stream_handle(stream) -> Optional[int]:
 def nlos_debug_fail_allocations(n: int) -> None:
     """Test hook (include/nlos_debug.h): the next n allocations of the library fail."""
     lib().nlos_debug_fail_allocations(n)
+
+
+def nlos_debug_fail_allocations_after(k: int, n: int) -> None:
+    """Test hook: the next k allocations of the library succeed, the n after them fail."""
+    lib().nlos_debug_fail_allocations_after(k, n)
 
 
 def nlos_debug_fk_lists(desc: nlos_fk_desc) -> int:
