@@ -235,6 +235,16 @@ struct nlos_rsd_plan {
 
 namespace {
 
+// An object whose C-style destructor runs unless it is released (a plan half built when an
+// allocation fails)
+template <auto Destroy>
+struct DestroyWith {
+  template <class T>
+  void operator()(T* p) const { (void)Destroy(p); }
+};
+template <class T, auto Destroy>
+using Owned = std::unique_ptr<T, DestroyWith<Destroy>>;
+
 // For the time of its life, calls that a capture in progress would refuse (allocations) are
 // let through on this thread without touching the capture, and the current device may be
 // changed.
@@ -628,7 +638,9 @@ nlos_status nlos_phasor_plan_create(nlos_ctx* ctx, const nlos_bin_desc* d, int n
       if (freq_bin[f] < 0 || freq_bin[f] >= d->nt)
         return fail(ctx, NLOS_ERR_INVALID_ARG, "phasor_plan_create: freq_bin[%d] = %d outside [0, nt)", f, freq_bin[f]);
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    nlos_phasor_plan* p = new (std::nothrow) nlos_phasor_plan();
+    nlos::host_alloc_point();
+    Owned<nlos_phasor_plan, nlos_phasor_plan_destroy> own(new (std::nothrow) nlos_phasor_plan());
+    nlos_phasor_plan* p = own.get();
     if (!p) return fail(ctx, NLOS_ERR_OUT_OF_MEMORY, "phasor_plan_create: host allocation");
     p->d = *d;
     p->device = ctx->device;
@@ -645,16 +657,14 @@ nlos_status nlos_phasor_plan_create(nlos_ctx* ctx, const nlos_bin_desc* d, int n
     if (e == hipSuccess) e = hipMemcpy(p->d_bins, freq_bin, n_freq * sizeof(int), hipMemcpyHostToDevice);
     const size_t ntab = nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), nullptr);
     if (e == hipSuccess && ntab <= kMaxPhasorTable) {
+      nlos::host_alloc_point();
       std::vector<float> tab(ntab);
       nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), tab.data());
       e = nlos::dev_alloc((void**)&p->d_tab, ntab * sizeof(float));
       if (e == hipSuccess) e = hipMemcpy(p->d_tab, tab.data(), ntab * sizeof(float), hipMemcpyHostToDevice);
     }
-    if (e != hipSuccess) {
-      nlos_phasor_plan_destroy(p);
-      return fail(ctx, NLOS_ERR_DEVICE, "phasor_plan_create: %s", hipGetErrorString(e));
-    }
-    *out = p;
+    if (e != hipSuccess) return fail(ctx, NLOS_ERR_DEVICE, "phasor_plan_create: %s", hipGetErrorString(e));
+    *out = own.release();
     return NLOS_OK;
   } catch (const std::bad_alloc&) {
     return fail(ctx, NLOS_ERR_OUT_OF_MEMORY, "nlos_phasor_plan_create: host allocation failed");
@@ -889,7 +899,8 @@ nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_pl
     nlos_status st = nlos_fk_check(d);
     if (st != NLOS_OK) return fail(ctx, st, "%s", g_err.c_str());
     nlos::host_alloc_point();
-    nlos_fk_plan* p = new (std::nothrow) nlos_fk_plan();
+    Owned<nlos_fk_plan, nlos_fk_plan_destroy> own(new (std::nothrow) nlos_fk_plan());
+    nlos_fk_plan* p = own.get();
     if (!p) return fail(ctx, NLOS_ERR_OUT_OF_MEMORY, "fk_plan_create: host allocation");
     fk_plan_sizes(d, p);
     p->device = ctx->device;
@@ -897,13 +908,11 @@ nlos_status nlos_fk_plan_create(nlos_ctx* ctx, const nlos_fk_desc* d, nlos_fk_pl
     const bool use[3] = {p->gen_xr2c, p->gen_y, p->gen_t};
     nlos::GenPlan* const g[3] = {&p->gx, &p->gy, &p->gt};
     hipError_t e = gen_tables(ctx->device, m, use, g, 3, &p->d_gtw);
-    if (e != hipSuccess) {
-      nlos_fk_plan_destroy(p);
+    if (e != hipSuccess)
       return fail(ctx, e == hipErrorOutOfMemory ? NLOS_ERR_OUT_OF_MEMORY : NLOS_ERR_DEVICE,
                   "fk_plan_create: general-length twiddle tables: %s", hipGetErrorString(e));
-    }
     fk_plan_lists(p);
-    *out = p;
+    *out = own.release();
     return NLOS_OK;
   } catch (const std::bad_alloc&) {
     return fail(ctx, NLOS_ERR_OUT_OF_MEMORY, "nlos_fk_plan_create: host allocation failed");
