@@ -771,6 +771,7 @@ static void fk_no_lists(nlos_fk_plan* p) {
 static std::vector<uint2> fk_schedule(nlos_fk_plan* p) {
   nlos::host_alloc_point();
   const nlos_fk_desc& d = p->d;
+  if (!std::isfinite(p->sxk) || !std::isfinite(p->syk)) return {};  // (a wall of 1e-310 m: no bounds to draw)
   const int nx = d.nx, nt = d.nt, Mx = p->Mx, My = p->My;
   const int sp = fk_sp(d.prec), half = p->Mt / 2;
   const int Ty = p->gen_y ? nlos::gen_strided_cols(My) : nlos::strided_cols(My, false, sp);

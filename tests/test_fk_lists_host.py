@@ -51,6 +51,14 @@ def test_lists_within_32_bit_offsets(ny, nx, nt, pad):
     assert nlos.nlos_debug_fk_lists(nlos.fk_desc(nx, ny, nt, 1.0, 1.0, 32.0, pad=pad)) > 0
 
 
+@pytest.mark.parametrize("w,h", [(1e-310, 1.0), (1.0, 1e-312), (5e-324, 5e-324)])
+def test_no_lists_where_the_ellipsoid_has_no_extent(w, h):
+    """A wall so small that the ratio of bin to pitch overflows: accepted, but without bounds."""
+    d = nlos.fk_desc(64, 64, 256, w, h, 32.0)
+    assert nlos.nlos_fk_check(d) == nlos.NLOS_OK
+    assert nlos.nlos_debug_fk_lists(d) == 0
+
+
 def test_random_descriptors_stay_within_reach():
     """Over the accepted sizes: lists only where every listed pass stays within reach."""
     r = random.Random(5)
