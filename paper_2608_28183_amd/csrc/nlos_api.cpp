@@ -613,7 +613,7 @@ struct nlos_phasor_plan {
   int nf = 0;
   float2* d_lut = nullptr;  // W_nt^m, m < nt (FP64-generated)
   int* d_bins = nullptr;
-  float* d_tab = nullptr;   // operands of the tiled path (null: too many bins, never taken)
+  std::shared_ptr<float> tab;  // operands of the tiled path (null: never taken)
 };
 
 nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan* p) {
@@ -621,7 +621,6 @@ nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan* p) {
   (void)hipSetDevice(p->device);
   if (p->d_lut) (void)hipFree(p->d_lut);
   if (p->d_bins) (void)hipFree(p->d_bins);
-  if (p->d_tab) (void)hipFree(p->d_tab);
   delete p;
   return NLOS_OK;
 }
@@ -655,15 +654,19 @@ nlos_status nlos_phasor_plan_create(nlos_ctx* ctx, const nlos_bin_desc* d, int n
     if (e == hipSuccess) e = nlos::dev_alloc((void**)&p->d_bins, n_freq * sizeof(int));
     if (e == hipSuccess) e = hipMemcpy(p->d_lut, lut.data(), lut.size() * sizeof(float2), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_bins, freq_bin, n_freq * sizeof(int), hipMemcpyHostToDevice);
-    const size_t ntab = nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), nullptr);
-    if (e == hipSuccess && ntab <= kMaxPhasorTable) {
-      nlos::host_alloc_point();
-      std::vector<float> tab(ntab);
-      nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), tab.data());
-      e = nlos::dev_alloc((void**)&p->d_tab, ntab * sizeof(float));
-      if (e == hipSuccess) e = hipMemcpy(p->d_tab, tab.data(), ntab * sizeof(float), hipMemcpyHostToDevice);
-    }
     if (e != hipSuccess) return fail(ctx, NLOS_ERR_DEVICE, "phasor_plan_create: %s", hipGetErrorString(e));
+    // the table only saves time: a plan that finds no memory for it, on the host or on the
+    // device, keeps the per-event atomics
+    const size_t ntab = nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), nullptr);
+    if (ntab <= kMaxPhasorTable) {
+      try {
+        nlos::host_alloc_point();
+        std::vector<float> tab(ntab);
+        nlos::phasor_table(d->nt, n_freq, freq_bin, lut.data(), tab.data());
+        p->tab = device_copy(p->device, tab);
+      } catch (const std::bad_alloc&) {
+      }
+    }
     *out = own.release();
     return NLOS_OK;
   } catch (const std::bad_alloc&) {
@@ -690,12 +693,12 @@ nlos_status nlos_phasor_bin(nlos_ctx* ctx, const nlos_phasor_plan* p, const nlos
   // frequencies 190 and 103.
   const double products = (double)d.nx * d.ny * d.nt * p->nf;
   const bool tiles = products <= 2.6e8 + 97.0 * (double)n_events * p->nf;
-  const size_t wsb = p->d_tab ? nlos::phasor_workspace_bytes(d.nx * d.ny, d.nt, n_events) : 0;
+  const size_t wsb = p->tab ? nlos::phasor_workspace_bytes(d.nx * d.ny, d.nt, n_events) : 0;
   void* ws = nullptr;
   if (wsb > 0 && tiles && pool_at_hand(ctx, wsb, &ws)) {
     HIP_TRY(ctx, timed(ctx, NLOS_PASS_PHASOR_BIN, [&] {
       return nlos::launch_phasor_tiled(d_events, n_events, reinterpret_cast<float2*>(d_phasor), d_dropped, d.nx * d.ny,
-                                       d.nt, d.bin_ps, d.t0_ps, p->d_tab, p->nf, d.accumulate, ws, ctx->stream);
+                                       d.nt, d.bin_ps, d.t0_ps, p->tab.get(), p->nf, d.accumulate, ws, ctx->stream);
     }));
     return NLOS_OK;
   }
