@@ -201,7 +201,8 @@ nlos_status nlos_fk_desc_workspace_bytes(const nlos_fk_desc *desc, size_t *bytes
 /* A plan whose remapped spectrum has many zeros also holds lists of the tiles and columns that
  * can be non-zero in device memory (up to a few MB); where that cannot be had it runs without,
  * slower and with the last bits rounded otherwise.  Plans of power-of-two sizes can be created,
- * and destroyed, while streams are under capture. */
+ * and destroyed, while streams are under capture; a graph keeps the lists it reads, until
+ * nlos_graph_destroy or, captured by the caller, until nlos_destroy of the context. */
 nlos_status nlos_fk_plan_create(nlos_ctx *ctx, const nlos_fk_desc *desc, nlos_fk_plan **out);
 nlos_status nlos_fk_plan_destroy(nlos_fk_plan *plan);
 /* Exact device workspace one nlos_fk call on plan needs (host only; the same figure as

@@ -182,6 +182,7 @@ struct nlos_ctx {
   std::vector<hipEvent_t> spare;      // recycled events
   hipStream_t aux = nullptr;          // second stream of the mixture of experts
   hipEvent_t fork[3] = {nullptr, nullptr, nullptr};
+  std::vector<std::shared_ptr<uint2>> kept;  // work lists that captured calls read (keep_captured)
   void* scratch = nullptr;            // this device's static scratch (nlos_fk_noalloc)
   void* d_mfma = nullptr;             // matrix-core DFT operands (FP64-built)
   nlos::MfmaTables mt{};
@@ -939,9 +940,29 @@ nlos_status nlos_fk_plan_destroy(nlos_fk_plan* p) {
   return NLOS_OK;
 }
 
+// Called under capture, the kernels' list addresses go into the caller's graph: the context
+// (or nlos_graph) then holds the lists too, so that the graph stays valid when the plan is
+// destroyed, as for plans without lists.
+static nlos_status keep_captured(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s) {
+  if (!p->items) return NLOS_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap != hipStreamCaptureStatusActive) return NLOS_OK;
+  for (const auto& k : ctx->kept)
+    if (k == p->items) return NLOS_OK;
+  try {
+    ctx->kept.push_back(p->items);
+  } catch (const std::bad_alloc&) {
+    return fail(ctx, NLOS_ERR_OUT_OF_MEMORY, "nlos_fk: host allocation failed");
+  }
+  return NLOS_OK;
+}
+
 // The f-k pass sequence on stream s with workspace ws (validated by the caller).
 static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, const float* d_tau, float* d_vol,
                           float* d_img, void* ws, float2* d_psi = nullptr) {
+  const nlos_status held = keep_captured(ctx, p, s);
+  if (held != NLOS_OK) return held;
   const nlos_fk_desc& d = p->d;
   const long long nx = d.nx, ny = d.ny, nt = d.nt, Mx = p->Mx, My = p->My;
   const FkLayout L = fk_layout(&d);
@@ -1578,6 +1599,7 @@ nlos_status nlos_rsd_complex(nlos_ctx* ctx, const nlos_rsd_plan* p, const float*
 // ---------------------------------------------------------------------------
 
 struct nlos_graph {
+  std::vector<std::shared_ptr<uint2>> kept;  // as nlos_ctx::kept, of this graph's plan
   int device = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1594,6 +1616,8 @@ static nlos_status capture_graph(nlos_ctx* ctx, const char* who, Run run, nlos_g
   ctx->timing = false;
   nlos_status st = NLOS_OK;
   hipGraph_t g = nullptr;
+  std::vector<std::shared_ptr<uint2>> kept;  // what this capture adds to the context's
+  kept.swap(ctx->kept);
   hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     st = run(cs);
@@ -1601,6 +1625,7 @@ static nlos_status capture_graph(nlos_ctx* ctx, const char* who, Run run, nlos_g
     if (st == NLOS_OK) e = e_end;
   }
   ctx->timing = timing;
+  kept.swap(ctx->kept);
   nlos_graph* gr = nullptr;
   if (st == NLOS_OK && e == hipSuccess) {
     gr = new (std::nothrow) nlos_graph();
@@ -1609,6 +1634,7 @@ static nlos_status capture_graph(nlos_ctx* ctx, const char* who, Run run, nlos_g
     } else {
       gr->device = ctx->device;
       gr->graph = g;
+      gr->kept = std::move(kept);
       e = hipGraphInstantiate(&gr->exec, g, nullptr, nullptr, 0);
     }
   }

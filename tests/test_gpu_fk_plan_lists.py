@@ -95,3 +95,39 @@ def test_a_plan_under_capture(lib):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(vol, ref[0]) and torch.equal(img, ref[1])
+
+
+@pytest.mark.parametrize("how", ["stream", "graph"])
+def test_a_graph_outlives_its_plan(lib, how):
+    """The plan is destroyed after its call was captured (by the caller on the context's stream,
+    or by nlos_fk_graph_create), and memory like its lists' is taken and filled, before the
+    graph is replayed."""
+    say("fk graph outlives its plan:", how)
+    s = torch.cuda.Stream()
+    ctx = runtime.Context(0, s)
+    plan = runtime.FkPlan(ctx, *POW2)
+    ws = plan.workspace()
+    tau = inputs(POW2, 1)
+    vol, img = outputs(POW2)
+    torch.cuda.synchronize()
+    if how == "stream":
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            plan(tau, vol, img, ws)
+    else:
+        g = plan.graph(tau, vol, img, ws)
+        g.plan = None  # (the helper would keep it)
+    del plan
+    gc.collect()
+    others = [runtime.FkPlan(ctx, 64, 64, 256, 0.02 + 0.03 * k, 0.4, 32.0, 2) for k in range(8)]
+    ref_plan = runtime.FkPlan(ctx, *POW2)
+    for seed in (2, 3, 4):
+        tau.copy_(inputs(POW2, seed))
+        torch.cuda.synchronize()  # (the context's stream does not wait for torch's)
+        ref = run(ref_plan, POW2, tau)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(vol, ref[0]) and torch.equal(img, ref[1])
+    if how == "graph":
+        g.close()
+    del others
