@@ -136,7 +136,8 @@ nlos_status nlos_bin_check(const nlos_bin_desc *desc);
  * time contiguous).  An event is valid iff 0 <= pixel < nx*ny, t_ps >= t0_ps and
  * b = (t_ps - t0_ps) / bin_ps < nt (integer division, left-closed bins); it adds 1
  * to d_hist[pixel][b].  Invalid events add 1 to *d_dropped (a device uint64,
- * optional: NULL skips the count; it is zeroed first unless accumulate = 1).
+ * optional: NULL skips the count; it is zeroed first unless accumulate = 1, and then added to
+ * atomically, so that calls on several streams may share it).
  * n_events may be 0.  Counts wrap modulo 2^32 per bin.  Bit-exact and order
  * independent. */
 nlos_status nlos_bin(nlos_ctx *ctx, const nlos_bin_desc *desc, const nlos_event *d_events,
@@ -160,7 +161,8 @@ nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan *plan);
  * DFT at those bins of the histogram nlos_bin would build, up to rounding.  Sorted by pixel
  * tiles (workspace from the context pool, as in nlos_bin), or, for few events on a large plan,
  * shapes without tiles and streams under capture, by hardware float atomics, where the
- * order of the sums (and the last bits) varies from run to run.  Dropped events are counted
+ * order of the sums (and the last bits) varies from run to run.  With accumulate every add to
+ * d_phasor is atomic: calls on several streams may share it.  Dropped events are counted
  * as in nlos_bin.  Feeds nlos_rsd_from_phasors. */
 nlos_status nlos_phasor_bin(nlos_ctx *ctx, const nlos_phasor_plan *plan, const nlos_event *d_events,
                             uint64_t n_events, float *d_phasor, unsigned long long *d_dropped);

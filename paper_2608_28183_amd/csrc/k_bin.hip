@@ -335,7 +335,8 @@ __device__ __forceinline__ void count_dropped(const uint16_t* __restrict__ start
   if (threadIdx.x != 0) return;
   unsigned long long d = n;
   for (int w = 0; w < NT / 64; ++w) d -= part[w];
-  *dropped = accumulate ? *dropped + d : d;
+  if (accumulate) atomicAdd(dropped, d);  // (a counter that other streams may be adding to)
+  else *dropped = d;
 }
 
 template <int NT>
@@ -394,7 +395,10 @@ __global__ __launch_bounds__(kBinGatherThreads) void bin_tile_phasor(const uint1
     float* o = P + (long long)(pix0 + px) * 2 * nf + row;
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      if (row + v < 2 * nf) o[v] = accumulate ? o[v] + d[v] : d[v];
+      if (row + v < 2 * nf) {
+        if (accumulate) unsafeAtomicAdd(o + v, d[v]);  // (phasors that other streams may be adding to)
+        else o[v] = d[v];
+      }
   };
   bin_f4 d;
   for (int s0 = 0; s0 < units * ks; s0 += kPhasorWaves) {
