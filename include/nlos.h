@@ -159,7 +159,8 @@ nlos_status nlos_phasor_plan_destroy(nlos_phasor_plan *plan);
  * exp(-2 pi i freq_bin[f] b / nt) to d_phasor[pixel][f] (float re, im pairs,
  * [ny][nx][n_freq], 8-byte aligned; zeroed first unless desc->accumulate), which is the
  * DFT at those bins of the histogram nlos_bin would build, up to rounding.  Sorted by pixel
- * tiles (workspace from the context pool, as in nlos_bin), or, for few events on a large plan,
+ * tiles (in memory that the context keeps for it, about 2 bytes an event of its largest call,
+ * allocated where a call needs more without waiting for any stream, freed by nlos_destroy), or, for few events on a large plan,
  * shapes without tiles and streams under capture, by hardware float atomics, where the
  * order of the sums (and the last bits) varies from run to run.  With accumulate every add to
  * d_phasor is atomic: calls on several streams may share it.  Dropped events are counted

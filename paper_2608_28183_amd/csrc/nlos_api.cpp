@@ -176,6 +176,8 @@ struct nlos_ctx {
   float2* d_tw = nullptr;     // W_2048^k, FP64-generated, stored FP32
   void* pool = nullptr;       // workspace when the caller passes none
   size_t pool_bytes = 0;
+  std::vector<void*> phasor_ws;  // nlos_phasor_bin's workspace (phasor_workspace): the last block
+  size_t phasor_bytes = 0;       // its size
   std::string err;
   bool timing = false;
   std::vector<TimedLaunch> recs;      // launches recorded since the last read
@@ -474,6 +476,7 @@ nlos_status nlos_destroy(nlos_ctx* ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
   if (ctx->pool) (void)hipFree(ctx->pool);
+  for (void* p : ctx->phasor_ws) (void)hipFree(p);
   if (ctx->d_tw) (void)hipFree(ctx->d_tw);
   if (ctx->d_mfma) (void)hipFree(ctx->d_mfma);
   for (auto& t : ctx->recs) {
@@ -522,18 +525,39 @@ static nlos_status get_workspace(nlos_ctx* ctx, void* d_ws, size_t ws_bytes, siz
   return NLOS_OK;
 }
 
-// The context pool with room for `need` bytes, for a path that has another to fall back on:
-// false (no error) while the stream is captured (a graph must not hold the pool's address) or
-// when the pool cannot grow.
-static bool pool_at_hand(nlos_ctx* ctx, size_t need, void** out) {
+// Workspace of nlos_phasor_bin, a block of its own that never moves under a caller: the call
+// only enqueues kernels, as without one.  A block that is too small is left in place (kernels
+// of earlier calls may be running on it) beside one of at least twice its size, so all blocks
+// together stay below twice the last; nlos_destroy frees them.  False (no error) while the
+// stream is captured (a graph would go on writing to the block) or when there is no memory:
+// the caller has another path.
+static bool phasor_workspace(nlos_ctx* ctx, size_t need, void** out) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  const std::string err = ctx->err;
-  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-      get_workspace(ctx, nullptr, 0, need, out) == NLOS_OK)
-    return true;
-  (void)hipGetLastError();
-  ctx->err = err;
-  return false;
+  if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (cap != hipStreamCaptureStatusNone) return false;
+  if (ctx->phasor_bytes < need) {
+    try {
+      ctx->phasor_ws.reserve(ctx->phasor_ws.size() + 1);
+    } catch (const std::bad_alloc&) {
+      return false;
+    }
+    Aside aside;
+    void* p = nullptr;
+    size_t bytes = std::max(need, 2 * ctx->phasor_bytes);
+    hipError_t e = hipSetDevice(ctx->device);
+    if (e == hipSuccess) e = nlos::dev_alloc(&p, bytes);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    ctx->phasor_ws.push_back(p);
+    ctx->phasor_bytes = bytes;
+  }
+  *out = ctx->phasor_ws.back();
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -696,7 +720,7 @@ nlos_status nlos_phasor_bin(nlos_ctx* ctx, const nlos_phasor_plan* p, const nlos
   const bool tiles = products <= 2.6e8 + 97.0 * (double)n_events * p->nf;
   const size_t wsb = p->tab ? nlos::phasor_workspace_bytes(d.nx * d.ny, d.nt, n_events) : 0;
   void* ws = nullptr;
-  if (wsb > 0 && tiles && pool_at_hand(ctx, wsb, &ws)) {
+  if (wsb > 0 && tiles && phasor_workspace(ctx, wsb, &ws)) {
     HIP_TRY(ctx, timed(ctx, NLOS_PASS_PHASOR_BIN, [&] {
       return nlos::launch_phasor_tiled(d_events, n_events, reinterpret_cast<float2*>(d_phasor), d_dropped, d.nx * d.ny,
                                        d.nt, d.bin_ps, d.t0_ps, p->tab.get(), p->nf, d.accumulate, ws, ctx->stream);
