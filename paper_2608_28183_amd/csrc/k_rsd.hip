@@ -363,41 +363,6 @@ __global__ __launch_bounds__(256, KSP == SP_F32 && DT == 1 ? 3 : 1) void rsd_pro
   }
 }
 
-// The plan's kernel table (RsdPropArgs::Kr) from K_r[i][f][d] in its natural order: float2
-// (SP_F32, split in three planes) or (re, im) FP16 / BF16 pairs.
-__global__ __launch_bounds__(256) void rsd_kr_table(const void* __restrict__ in, unsigned int* __restrict__ out,
-                                                    long long n, long long plane, int Nf, int Nd, int split) {
-  using M = Mfma<SP_BF16>;
-  const int FL = split ? 4 : 2, ng = 8 / FL * ((Nf + 7) / 8);
-  for (long long o = (long long)blockIdx.x * 256 + threadIdx.x; o < n; o += (long long)gridDim.x * 256) {
-    const long long r = o / FL / Nd;
-    const int d = (int)(o / FL % Nd), f = (int)(r % ng) * FL + (int)(o % FL);
-    const long long src = ((r / ng) * Nf + f) * Nd + d;
-    if (!split) {
-      out[o] = f < Nf ? static_cast<const unsigned int*>(in)[src] : 0u;
-      continue;
-    }
-    float2 k = f < Nf ? static_cast<const float2*>(in)[src] : make_float2(0.f, 0.f);
-    for (int pl = 0; pl < 3; ++pl) {
-      const unsigned int h = M::pack(k.x, k.y);
-      const float2 v = M::unpack(h);
-      out[pl * plane + o] = h;
-      k = make_float2(k.x - v.x, k.y - v.y);
-    }
-  }
-}
-
-size_t rsd_kr_plane(int nrho, int nf, int nd) { return (size_t)nrho * (8 * ((nf + 7) / 8)) * nd; }
-
-hipError_t launch_rsd_kr_table(const void* in, void* out, int nrho, int nf, int nd, int sp, hipStream_t s) {
-  const long long n = (long long)rsd_kr_plane(nrho, nf, nd);
-  if (n <= 0) return hipErrorInvalidValue;
-  const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 16384);
-  hipLaunchKernelGGL(rsd_kr_table, dim3(blocks), dim3(256), 0, s, in, static_cast<unsigned int*>(out), n, n, nf, nd,
-                     sp == SP_F32 ? 1 : 0);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // FP16 storage scales of the RSD intermediates
 // ---------------------------------------------------------------------------

@@ -1353,33 +1353,16 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
                   hipGetErrorString(e));
     };
     hipError_t e;
-    // the device's kernel table from the host's K_r (through a device copy in its own order)
-    auto kr_table = [&](const void* k, size_t bytes) -> hipError_t {
-      const int nrho = (int)(nk / ((size_t)d->n_freq * d->n_depth)), sp = fk_sp(d->kernel_prec);
+    {
+      // FP64 accumulation, a single rounding (to nearest even) of each value or plane
+      const int nrho = (int)(nk / ((size_t)d->n_freq * d->n_depth));
+      size_t pairs = 0;
+      const std::unique_ptr<uint32_t[]> kr =
+          nlos::rsd_kr_table(kre, kim, nrho, d->n_freq, d->n_depth, fk_sp(d->kernel_prec), &pairs);
       p->kr_plane = (long long)nlos::rsd_kr_plane(nrho, d->n_freq, d->n_depth);
-      void* tmp = nullptr;
-      hipError_t r = nlos::dev_alloc(&p->d_kr, (size_t)p->kr_plane * (sp == nlos::SP_F32 ? 12 : 4));
-      if (r == hipSuccess) r = nlos::dev_alloc(&tmp, bytes);
-      if (r == hipSuccess) r = hipMemcpy(tmp, k, bytes, hipMemcpyHostToDevice);
-      if (r == hipSuccess) r = nlos::launch_rsd_kr_table(tmp, p->d_kr, nrho, d->n_freq, d->n_depth, sp, ctx->stream);
-      if (r == hipSuccess) r = hipStreamSynchronize(ctx->stream);
-      if (tmp) (void)hipFree(tmp);
-      return r;
-    };
-    if (d->kernel_prec == NLOS_FP16 || d->kernel_prec == NLOS_BF16) {
-      // FP64 accumulation, a single rounding (to nearest even) to binary16 or bfloat16 on
-      // store; (re, im) pairs, re in the lower half
-      std::vector<uint16_t> kh(2 * nk);
-      const bool bf = d->kernel_prec == NLOS_BF16;
-      for (size_t i = 0; i < nk; ++i) {
-        kh[2 * i] = bf ? nlos::to_bf16_bits(kre[i]) : nlos::to_f16_bits(kre[i]);
-        kh[2 * i + 1] = bf ? nlos::to_bf16_bits(kim[i]) : nlos::to_f16_bits(kim[i]);
-      }
-      if ((e = kr_table(kh.data(), nk * 4)) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
-    } else {
-      std::vector<float2> kf(nk);
-      for (size_t i = 0; i < nk; ++i) kf[i] = make_float2((float)kre[i], (float)kim[i]);
-      if ((e = kr_table(kf.data(), nk * sizeof(float2))) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
+      if ((e = nlos::dev_alloc(&p->d_kr, pairs * 4)) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
+      if ((e = hipMemcpy(p->d_kr, kr.get(), pairs * 4, hipMemcpyHostToDevice)) != hipSuccess)
+        return cleanup(NLOS_ERR_DEVICE, "K_r upload", e);
     }
     if (d->data_prec != NLOS_FP32) {
       // kappa_d = sum_f |w_f| max_i |K_r[i][f][d]|: with L = sum |tau| it bounds the

@@ -238,10 +238,6 @@ constexpr int kScaleBlocks = 1024;
 hipError_t launch_fk_scales(const float* tau, long long n, int nt, float* partials, int* exps,
                             int l_norm, int l_first_inv, int l_second_inv, hipStream_t s);
 hipError_t launch_rsd_propagate(const RsdPropArgs& a, hipStream_t s);
-// the kernel table from K_r[Nrho][Nf][Nd] as float2 (sp SP_F32) or four-byte pairs (device
-// buffers); pairs per plane
-size_t rsd_kr_plane(int nrho, int nf, int nd);
-hipError_t launch_rsd_kr_table(const void* in, void* out, int nrho, int nf, int nd, int sp, hipStream_t s);
 // FP16 storage scales of the RSD intermediates from L = sum |tau| (n values, n even):
 // exps[0] for P, X and P^ (bound L), exps[1 + d] for C at depth d (bound L kappa[d]) and
 // exps[1 + nd + d] for D (bound My L kappa[d], l_my = log2 My); partials[kScaleBlocks].

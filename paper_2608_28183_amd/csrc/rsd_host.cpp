@@ -3,7 +3,10 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <thread>
+
+#include "nlos_internal.hpp"
 
 namespace nlos {
 
@@ -140,6 +143,54 @@ void rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<do
       im[(size_t)i * FD + fd] = sr * Pim[fd] + si * Pre[fd];
     }
   });
+}
+
+size_t rsd_kr_plane(int n_rho, int n_freq, int n_depth) {
+  return (size_t)n_rho * (8 * ((n_freq + 7) / 8)) * n_depth;
+}
+
+namespace {
+// The bfloat16 nearest to *x (to nearest even, finite *x), taken off *x.
+inline uint32_t take_bf16(float* x) {
+  uint32_t u;
+  std::memcpy(&u, x, 4);
+  u = (u + 0x7fffu + ((u >> 16) & 1u)) & 0xffff0000u;
+  float v;
+  std::memcpy(&v, &u, 4);
+  *x -= v;
+  return u >> 16;
+}
+}  // namespace
+
+std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const std::vector<double>& im, int n_rho,
+                                         int n_freq, int n_depth, int sp, size_t* pairs) {
+  const int fl = sp == SP_F32 ? 4 : 2, ng = 8 / fl * ((n_freq + 7) / 8);
+  const size_t plane = rsd_kr_plane(n_rho, n_freq, n_depth);
+  *pairs = plane * (sp == SP_F32 ? 3 : 1);
+  // (uninitialised: the threads below write, and first touch, all of it)
+  std::unique_ptr<uint32_t[]> out(new uint32_t[*pairs]);
+  uint32_t* const o = out.get();
+  parallel_for(n_rho, [=, &re, &im](long long i) {
+    for (int g = 0; g < ng; ++g) {
+      uint32_t* dst = o + ((size_t)i * ng + g) * n_depth * fl;
+      for (int d = 0; d < n_depth; ++d)
+        for (int j = 0; j < fl; ++j, ++dst) {
+          const int f = g * fl + j;
+          const size_t src = ((size_t)i * n_freq + f) * n_depth + d;
+          if (sp != SP_F32) {
+            auto bits = [sp](double v) -> uint32_t { return sp == SP_BF16 ? to_bf16_bits(v) : to_f16_bits(v); };
+            *dst = f < n_freq ? bits(re[src]) | bits(im[src]) << 16 : 0u;
+            continue;
+          }
+          float x = f < n_freq ? (float)re[src] : 0.f, y = f < n_freq ? (float)im[src] : 0.f;
+          for (int pl = 0; pl < 3; ++pl) {
+            const uint32_t h = take_bf16(&x);
+            dst[pl * plane] = h | take_bf16(&y) << 16;
+          }
+        }
+    }
+  });
+  return out;
 }
 
 void rsd_radius_map(const RsdInputs& in, const RsdGeometry& g, std::vector<double>& rho) {
