@@ -26,8 +26,8 @@ constexpr int kGroupPix = 64;   // pixels per chunk (one per lane; matches the p
 constexpr int kDepths = 8;      // depths per wave
 constexpr int kWavesPerBlock = 4;
 
-// K_r[i][f][d] from the plan's table (see RsdPropArgs::Kr); FP32 is the exact sum of its three
-// bfloat16 planes
+// K_r[i][f][d] from the plan's table (see RsdPropArgs::Kr); FP32 is the sum of its three
+// bfloat16 planes times 2^kr_exp
 template <int SP>
 __device__ __forceinline__ float2 load_kr(const RsdPropArgs& a, int i, int f, int d) {
   constexpr int FL = SP == SP_F32 ? 4 : 2;
@@ -37,7 +37,8 @@ __device__ __forceinline__ float2 load_kr(const RsdPropArgs& a, int i, int f, in
   if constexpr (SP == SP_F32) {
     using M = Mfma<SP_BF16>;
     const float2 k0 = M::unpack(kr[o]), k1 = M::unpack(kr[o + a.kr_plane]), k2 = M::unpack(kr[o + 2 * a.kr_plane]);
-    return make_float2((k2.x + k1.x) + k0.x, (k2.y + k1.y) + k0.y);
+    const float2 k = make_float2((k2.x + k1.x) + k0.x, (k2.y + k1.y) + k0.y);
+    return a.kr_exp == 0 ? k : make_float2(ldexpf(k.x, a.kr_exp), ldexpf(k.y, a.kr_exp));
   } else {
     return Mfma<SP>::unpack(kr[o]);
   }
@@ -158,7 +159,14 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
 // plan, the phasors are split in registers; each tap has its own accumulators and the tap
 // weights come last, so the split is paid once.  The sums take 3/8 of the time of FP32 matrix
 // instructions and round less often (once per 16-wide product sum instead of per 2-wide):
-// over the volume within the error of the FP32 instructions against 64 bits.
+// over the volume within the error of the FP32 instructions against 64 bits.  The split is
+// exact, and no partial product is lost, only well inside FP32's range (below 2^-109 the third
+// part leaves bfloat16's normal numbers, above 2^128 - 2^119 the first rounds to infinity).
+// The plan scales the kernel there (RsdPropArgs::kr_exp), and a wave sees from its sums, at no
+// cost to its steps, whether its phasors were: sums below kSplitMin (with |K_r| up to 2^12 and
+// 2048 terms, phasors of 2^-93 give at most 2^-64 in a lane), above kSplitMax or not a number
+// make it start again with FP32 instructions (propagate_f32).  The largest of the wave counts:
+// what smaller phasors lose is below 2^-30 of it.
 //
 // 128 x 128 x 1024 (129 frequencies, 64 depths; 8.7 GFLOP): FP32 131 -> 76 us, BF16 77 -> 47 us
 // against one 64-pixel chunk per wave with FP32 matrix instructions and scattered operand
@@ -176,6 +184,57 @@ __device__ __forceinline__ mf_u4 prop_re(mf_u4 a) { return a ^ 0x80000000u; }
 __device__ __forceinline__ mf_u4 prop_im(mf_u4 a) {
   return mf_u4{__builtin_amdgcn_alignbit(a[0], a[0], 16), __builtin_amdgcn_alignbit(a[1], a[1], 16),
                __builtin_amdgcn_alignbit(a[2], a[2], 16), __builtin_amdgcn_alignbit(a[3], a[3], 16)};
+}
+
+constexpr float kSplitMin = 0x1p-64f, kSplitMax = 0x1p100f;
+
+// A half chunk's sum with an FP32 kernel on v_mfma_f32_32x32x2f32: a step is one (frequency,
+// tap), lane l holds part l / 32 (re or im) of the tap-weighted phasor of its row and the kernel
+// value of its column as (re, -im) for the real part of the output, (im, re) for the imaginary.
+// Only for phasors beyond the split's range: plain loads, nothing in flight ahead.
+// (Everything is worked out anew from the lane number, behind a barrier to the optimiser, so that
+// none of it occupies registers during the steps of the split.)
+template <int DT>
+__device__ __forceinline__ void propagate_f32(const RsdPropArgs& a, const float2* ws, long long gh, int d0, int i0,
+                                              int i1, mf_acc (*acc)[2]) {
+  int ln = threadIdx.x & 63;
+  asm volatile("" : "+v"(ln));
+  const bool im = ln >= 32;
+  const int c = ln & 31, pix = a.chunk_pix[gh * 32 + c];
+  const float wa = a.chunk_wa[gh * 32 + c], wb = a.chunk_wb[gh * 32 + c];
+  const float2* row = static_cast<const float2*>(a.Ph) + (long long)(pix >= 0 ? pix : 0) * a.ph_stride;
+#pragma unroll
+  for (int q = 0; q < DT; ++q)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[q][0][v] = acc[q][1][v] = 0.f;
+#pragma unroll 1
+  for (int f = 0; f < a.Nf; ++f) {
+    const float2 p = row[f], wf = ws[f];
+    const float z = im ? p.x * wf.y + p.y * wf.x : p.x * wf.x - p.y * wf.y;
+    const float A[2] = {wa * z, wb * z};
+#pragma unroll
+    for (int q = 0; q < DT; ++q)
+#pragma unroll
+      for (int tap = 0; tap < 2; ++tap) {
+        const float2 k = load_kr<SP_F32>(a, tap == 0 ? i0 : i1, f, min(d0 + 32 * q + c, a.Nd - 1));
+        acc[q][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[tap], im ? -k.y : k.x, acc[q][0], 0, 0, 0);
+        acc[q][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[tap], im ? k.x : k.y, acc[q][1], 0, 0, 0);
+      }
+  }
+}
+
+// A half chunk whose every phasor w_f P^ is zero
+__device__ __forceinline__ bool all_zero(const RsdPropArgs& a, const float2* ws, long long gh) {
+  int ln = threadIdx.x & 63;
+  asm volatile("" : "+v"(ln));
+  const int pix = a.chunk_pix[gh * 32 + (ln & 31)];
+  const float2* row = static_cast<const float2*>(a.Ph) + (long long)(pix >= 0 ? pix : 0) * a.ph_stride;
+  for (int f0 = 0; f0 < a.Nf; f0 += 2) {  // (a frequency per half of the wave, which stays together)
+    const int f = min(f0 + (ln >> 5), a.Nf - 1);
+    const float2 p = row[f], wf = ws[f];
+    if (__ballot(p.x * wf.x - p.y * wf.y != 0.f || p.x * wf.y + p.y * wf.x != 0.f) != 0ull) return false;
+  }
+  return true;
 }
 
 template <int KSP, int DT, bool DATA4>
@@ -206,7 +265,7 @@ __global__ __launch_bounds__(256, KSP == SP_F32 && DT == 1 ? 3 : 1) void rsd_pro
   const int* pixs = a.chunk_pix + gh * 32;
   if (pixs[0] < 0) return;  // slots fill in order: an empty half
   const int pix = pixs[c32];
-  const float wa = a.chunk_wa[gh * 32 + c32], wb = a.chunk_wb[gh * 32 + c32];
+  float wa = a.chunk_wa[gh * 32 + c32], wb = a.chunk_wb[gh * 32 + c32];
   mf_acc acc[NT][DT][2];  // [tap][depth tile][re | im]
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -328,6 +387,29 @@ __global__ __launch_bounds__(256, KSP == SP_F32 && DT == 1 ? 3 : 1) void rsd_pro
       __builtin_amdgcn_sched_barrier(0);
     }
     if (ns & 1) step(b0, ns - 1);
+    if constexpr (NPL == 3) {
+      float m = 0.f;  // the lane's sums in magnitude (NaN, infinite if one is)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+#pragma unroll
+        for (int q = 0; q < DT; ++q)
+          m += (fabsf(acc[0][q][0][v]) + fabsf(acc[0][q][1][v])) + (fabsf(acc[1][q][0][v]) + fabsf(acc[1][q][1][v]));
+      bool whole = __ballot(!(m <= kSplitMax)) != 0ull;
+      if (!whole && __ballot(m >= kSplitMin) == 0ull)  // (all sums zero: of zeros, or too small for any product)
+        whole = __ballot(m > 0.f) != 0ull || !all_zero(a, ws, gh);
+      const float sc = ldexpf(1.f, a.kr_exp);
+      wa *= sc;
+      wb *= sc;
+      if (whole) {
+#pragma unroll
+        for (int q = 0; q < DT; ++q)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[1][q][0][v] = acc[1][q][1][v] = 0.f;
+        propagate_f32<DT>(a, ws, gh, d0, i0, i1, acc[0]);
+        wa = 1.f;  // (acc[0] is the whole sum)
+        wb = 0.f;
+      }
+    }
   }
   // D lane layout: rows 8(v/4) + 4 hl + v%4 of the tile, column c32
   int qexp[DT];  // final exponent per depth tile column: the half chunk's scale, and for FP16

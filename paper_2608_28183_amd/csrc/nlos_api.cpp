@@ -221,6 +221,7 @@ struct nlos_rsd_plan {
   nlos::RsdGeometry g{};
   void* d_kr = nullptr;       // kernel table (RsdPropArgs::Kr), kr_plane pairs a plane
   long long kr_plane = 0;
+  int kr_exp = 0;
   float* d_kappa = nullptr;   // [Nd] sum_f |w_f| max_i |K_r[i][f][d]| (four-byte data: scales)
   float2* d_w = nullptr;      // [Nf]
   int* d_bins = nullptr;      // [Nf]
@@ -1358,7 +1359,7 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
       const int nrho = (int)(nk / ((size_t)d->n_freq * d->n_depth));
       size_t pairs = 0;
       const std::unique_ptr<uint32_t[]> kr =
-          nlos::rsd_kr_table(kre, kim, nrho, d->n_freq, d->n_depth, fk_sp(d->kernel_prec), &pairs);
+          nlos::rsd_kr_table(kre, kim, nrho, d->n_freq, d->n_depth, fk_sp(d->kernel_prec), &pairs, &p->kr_exp);
       p->kr_plane = (long long)nlos::rsd_kr_plane(nrho, d->n_freq, d->n_depth);
       if ((e = nlos::dev_alloc(&p->d_kr, pairs * 4)) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
       if ((e = hipMemcpy(p->d_kr, kr.get(), pairs * 4, hipMemcpyHostToDevice)) != hipSuccess)
@@ -1488,7 +1489,7 @@ static nlos_status rsd_run(nlos_ctx* ctx, const nlos_rsd_plan* p, hipStream_t s,
   }));
   // 4. radial propagation over pixel chunks: P^ -> C[pix][d]
   nlos::RsdPropArgs r{};
-  r.Ph = Ph; r.Kr = p->d_kr; r.kr_plane = p->kr_plane; r.w = p->d_w; r.C = C;
+  r.Ph = Ph; r.Kr = p->d_kr; r.kr_plane = p->kr_plane; r.kr_exp = p->kr_exp; r.w = p->d_w; r.C = C;
   r.chunk_i0 = p->d_chunk_i0; r.chunk_pix = p->d_chunk_pix; r.chunk_wa = p->d_chunk_wa;
   r.chunk_wb = p->d_chunk_wb; r.nchunks = p->nchunks; r.nactive = p->nactive;
   r.Nf = (int)Nf; r.Nd = (int)Nd; r.ph_stride = (int)Nfs; r.c_stride = (int)Nds;
@@ -2049,7 +2050,7 @@ nlos_status nlos_moe(nlos_ctx* ctx, const nlos_moe_plan* p, const float* d_tau, 
   HIP_TRY(ctx, timed_on(ctx, s1, NLOS_PASS_MOE_PHASOR, [&] { return nlos::launch_moe_phasor_pair(ph, tw, s1); }));
   HIP_TRY(ctx, hipEventRecord(ctx->fork[1], s1));  // W2 no longer read by the RSD branch
   nlos::RsdPropArgs r{};
-  r.Ph = Ph; r.Kr = p->rsd->d_kr; r.kr_plane = p->rsd->kr_plane; r.w = p->rsd->d_w; r.C = Cr;
+  r.Ph = Ph; r.Kr = p->rsd->d_kr; r.kr_plane = p->rsd->kr_plane; r.kr_exp = p->rsd->kr_exp; r.w = p->rsd->d_w; r.C = Cr;
   r.chunk_i0 = p->rsd->d_chunk_i0; r.chunk_pix = p->rsd->d_chunk_pix; r.chunk_wa = p->rsd->d_chunk_wa;
   r.chunk_wb = p->rsd->d_chunk_wb; r.nchunks = p->rsd->nchunks; r.nactive = p->rsd->nactive;
   r.Nf = (int)Nf; r.Nd = (int)Nd; r.ph_stride = (int)Nf; r.c_stride = (int)Nd;

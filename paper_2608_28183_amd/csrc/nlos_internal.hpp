@@ -152,10 +152,12 @@ struct RsdPropArgs {
   const void* Ph;          // [npix][Nf] spectra of the padded phasor planes (float2, or
                            // four-byte pairs when data_sp != SP_F32)
   // radial kernel: planes of kr_plane four-byte (re, im) pairs, f zero-padded to a multiple of
-  // 8.  FP16 / BF16: one plane [Nrho][f / 2][Nd][f % 2]; FP32: three bfloat16 planes that add
-  // up to it exactly, [Nrho][f / 4][Nd][f % 4]
+  // 8.  FP16 / BF16: one plane [Nrho][f / 2][Nd][f % 2]; FP32: three bfloat16 planes
+  // [Nrho][f / 4][Nd][f % 4] that add up to it times 2^-kr_exp (kr_exp 0 unless the kernel's
+  // largest value lies outside [2^-12, 2^12])
   const void* Kr;
   long long kr_plane;
+  int kr_exp;
   const float2* w;         // [Nf] complex frequency weights
   void* C;                 // [npix][Nd] propagated spectra (float2 or four-byte pairs)
   const int* chunk_i0;     // [nchunks] lower radial bin (-1: all-zero chunk)

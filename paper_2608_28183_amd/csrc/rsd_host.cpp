@@ -163,13 +163,27 @@ inline uint32_t take_bf16(float* x) {
 }  // namespace
 
 std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const std::vector<double>& im, int n_rho,
-                                         int n_freq, int n_depth, int sp, size_t* pairs) {
+                                         int n_freq, int n_depth, int sp, size_t* pairs, int* exp) {
   const int fl = sp == SP_F32 ? 4 : 2, ng = 8 / fl * ((n_freq + 7) / 8);
   const size_t plane = rsd_kr_plane(n_rho, n_freq, n_depth);
   *pairs = plane * (sp == SP_F32 ? 3 : 1);
   // (uninitialised: the threads below write, and first touch, all of it)
   std::unique_ptr<uint32_t[]> out(new uint32_t[*pairs]);
   uint32_t* const o = out.get();
+  *exp = 0;
+  if (sp == SP_F32) {
+    std::vector<double> top(n_rho, 0.0);
+    const size_t row = (size_t)n_freq * n_depth;
+    parallel_for(n_rho, [&, row](long long i) {
+      double t = 0.0;
+      for (size_t k = i * row; k < (i + 1) * row; ++k) t = std::max(t, std::max(std::fabs(re[k]), std::fabs(im[k])));
+      top[i] = t;
+    });
+    const double m = *std::max_element(top.begin(), top.end());
+    if (m > 0.0 && std::isfinite(m) && (m < 0x1p-12 || m > 0x1p12)) (void)std::frexp(m, exp);
+    *exp = std::min(std::max(*exp, -126), 126);  // (2^exp an FP32 number)
+  }
+  const double scale = std::ldexp(1.0, -*exp);
   parallel_for(n_rho, [=, &re, &im](long long i) {
     for (int g = 0; g < ng; ++g) {
       uint32_t* dst = o + ((size_t)i * ng + g) * n_depth * fl;
@@ -182,7 +196,7 @@ std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const st
             *dst = f < n_freq ? bits(re[src]) | bits(im[src]) << 16 : 0u;
             continue;
           }
-          float x = f < n_freq ? (float)re[src] : 0.f, y = f < n_freq ? (float)im[src] : 0.f;
+          float x = f < n_freq ? (float)(re[src] * scale) : 0.f, y = f < n_freq ? (float)(im[src] * scale) : 0.f;
           for (int pl = 0; pl < 3; ++pl) {
             const uint32_t h = take_bf16(&x);
             dst[pl * plane] = h | take_bf16(&y) << 16;
