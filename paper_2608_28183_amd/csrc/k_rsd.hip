@@ -5,13 +5,12 @@
 //             = sum_f (wa w_f P^) K_r[i0][f][d] + (wb w_f P^) K_r[i0+1][f][d]
 //
 // The plan sorts the pixels by their lower radial bin i0 and groups them into chunks of
-// up to 64 that share i0.  One wave64 takes a chunk, one pixel per lane, and a slice of
-// kDepths depths: the two kernel rows K_r[i0][f][d0..d0+kDepths) and K_r[i0+1][f][...]
-// are the same for the whole wave, so they come in through the scalar unit and enter the
-// FMAs as scalar operands, and each kernel value is loaded once per 64 pixels.  The
-// lane's own phasor P^[pix][f] is read from its contiguous frequency row.  Every C
-// element is produced by one lane in a fixed frequency order.  This form (FP32 FMAs) runs
-// on request only; the matrix cores below are the default.
+// up to 64 that share i0.  On FP32 FMAs (rsd_propagate, on request only; the matrix cores below
+// are the default) one wave64 takes a chunk, one pixel per lane, and a slice of kDepths depths:
+// the kernel rows K_r[i0][f][d0..d0+kDepths) and K_r[i0+1][f][...] have the same address in
+// every lane, each value read from its plane or planes and put together (load_kr) once per 64
+// pixels.  The lane's own phasor P^[pix][f] is read from its contiguous frequency row.  Every C
+// element is produced by one lane in a fixed frequency order.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
