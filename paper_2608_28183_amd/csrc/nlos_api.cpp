@@ -268,7 +268,8 @@ struct Aside {
 };
 
 // `v` in device memory, or null where there is none to be had.  The upload goes by a stream
-// of its own: it waits for no stream of the caller and enters no capture.
+// of its own: it is ordered behind no stream of the caller's (on a hardware queue that both
+// share it may still run behind their work) and enters no capture.
 template <class T>
 std::shared_ptr<T> device_copy(int device, const std::vector<T>& v) {
   Aside aside;
