@@ -157,7 +157,6 @@ struct RsdPropArgs {
   // largest value lies outside [2^-12, 2^12])
   const void* Kr;
   long long kr_plane;
-  int kr_exp;
   const float2* w;         // [Nf] complex frequency weights
   void* C;                 // [npix][Nd] propagated spectra (float2 or four-byte pairs)
   const int* chunk_i0;     // [nchunks] lower radial bin (-1: all-zero chunk)
@@ -179,6 +178,7 @@ struct RsdPropArgs {
   long long img_n;         // at most one value per padded pixel
   int mfma;                // propagation on the matrix cores: 0 no (FP32 FMAs), 1 yes, 2 yes
                            // with the other depth tiling
+  int kr_exp;              // of the FP32 kernel table
 };
 
 // Every sample of a plane within reach of 32-bit buffer offsets, as the listed passes need
