@@ -114,9 +114,9 @@ hipError_t gen_tables(int device, const int* m, const bool* use, nlos::GenPlan* 
 // memory channels at a power-of-two stride.  es is the bytes per complex element.
 size_t fk_row_stride(size_t Mx, size_t nt, size_t es) { return Mx * nt + 256 / es; }
 
-// An intermediate of at most this many bytes is kept in the 256 MB last-level cache for the
-// next pass (ordinary accesses); larger ones stream past it.
-constexpr size_t kCacheBytes = size_t(160) << 20;
+// W4 of at most this many bytes is written with ordinary stores, a larger one past the 256 MB
+// last-level cache (fk_run).
+constexpr size_t kW4CacheBytes = size_t(320) << 20;
 
 // Zeros of the remapped spectrum below which a plan does without work lists.
 constexpr size_t kMinZeroBytes = size_t(16) << 20;
@@ -1023,19 +1023,20 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
     a.items = p->items ? p->items.get() + p->list[i] : nullptr;
     a.nitems = p->list[i + 1] - p->list[i];
   };
-  // Cached or streaming (ordinary or non-temporal): an intermediate that fits the last-level cache is read from it by the
-  // next pass (fk_y 98 -> 80 us at 128x128x1024, whose W1 is 135 MB), a larger one only
-  // displaces what could still be reused
-  const int w1_nt = (size_t)ny * (p->kmax + 1) * nt * L.es > kCacheBytes;
-  const int w5_nt = (size_t)ny * nx * p->nz * L.es > kCacheBytes;
-  // W4 is written in the cache up to a little beyond its size (268 MB at 128x128x1024: x-IFFT
-  // 152 -> 130 us, y-IFFT unchanged; 344 MB at 256x256x512: 172 both ways, y-IFFT 143 -> 168 us)
-  const int w4_nt = p->w4_bytes > 2 * kCacheBytes;
+  // Ordinary or non-temporal accesses.  W1 and W5 are written and W1 read by ordinary ones: the
+  // next pass finds in the last-level cache what fits, and beyond its size nothing is lost.
+  // Measured (ordinary against non-temporal, x and y pass of W1, y- and z-IFFT of W5): 135 MB 118
+  // and 140 us, 125 and 128; 203 MB 159 and 203, 341 and 369; 337 MB 297 and 317, 535 and 563;
+  // 539 MB 493 and 509, 468 and 475; 256x256x512 with its lists 183 and 182, 205 and 207.
+  // W4's stores are ordinary up to a little beyond the cache: x- and y-IFFT 205 and 221 us at 268
+  // MB, 252 and 250 at 315, 344 and 349 at 419, 471 and 464 at 537; with lists, whose reads of it
+  // have gaps, 326 and 309 at 344 (256x256x512).
+  const int w4_nt = p->w4_bytes > kW4CacheBytes;
   // pass 1: x-FFT of tau * t/(nt-1), zero padded to Mx, kx in [0, kmax]
   FkXArgs x{};
   x.tau = d_tau; x.out = W1; x.out_plane = RH; x.nx = (int)nx; x.nt = (int)nt;
   x.tscale = (float)(1.0 / (double)(nt - 1));
-  x.e_out = ex; x.kmax = p->kmax; x.nt_out = w1_nt;
+  x.e_out = ex; x.kmax = p->kmax; x.nt_out = 0;
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_X, [&] {
     return p->gen_xr2c ? nlos::launch_gen_xr2c(p->gx, x, (int)ny, s) : nlos::launch_fk_xr2c((int)Mx, x, (int)ny, tw, s, sp);
   }));
@@ -1044,7 +1045,7 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   a.in = W1; a.out = W2;
   a.in_plane = nt; a.in_line = RH; a.out_plane = nt; a.out_line = RH;
   a.ncols = (int)nt; a.n_in = (int)ny; a.n_out = (int)My;
-  a.e_in = ex; a.e_out = ex; a.nt_in = w1_nt; a.nt_out = 1;
+  a.e_in = ex; a.e_out = ex; a.nt_in = 0; a.nt_out = 1;
   list(a, 0);
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_Y, [&] {
     if (mf && nlos::mfma_strided_ok((int)My, sp, a))
@@ -1089,7 +1090,7 @@ static nlos_status fk_run(nlos_ctx* ctx, const nlos_fk_plan* p, hipStream_t s, c
   a.in = W4; a.out = W5;
   a.in_plane = nt; a.in_line = RX; a.out_plane = nt; a.out_line = nx * nt;
   a.ncols = (int)nt; a.n_in = (int)My; a.n_out = (int)ny;
-  a.e_in = ex ? ex + 2 : nullptr; a.e_out = ex ? ex + 3 : nullptr; a.nt_in = 1; a.nt_out = w5_nt;
+  a.e_in = ex ? ex + 2 : nullptr; a.e_out = ex ? ex + 3 : nullptr; a.nt_in = 1; a.nt_out = 0;
   list(a, 3);
   HIP_TRY(ctx, timed_on(ctx, s, NLOS_PASS_FK_YI, [&] {
     if (mf && nlos::mfma_strided_ok((int)My, sp, a))
