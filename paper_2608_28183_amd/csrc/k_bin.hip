@@ -135,14 +135,15 @@ hipError_t launch_bin(const void* events, unsigned long long n, uint32_t* hist,
 //     writes the tile's rows with plain stores (all of them, so no clearing pass).
 // Events are read once; all adds are integer adds, so the histogram is exact and does not
 // depend on the order in which the LDS atomics land.  Both passes wait on latency (the loads,
-// the LDS atomics) more than on the 108 MB they move at 1e7 events and 64 x 64 x 512: 31 and
-// 24 us, 54 in all against 104 before with scattered reflecting points (the gather searched
+// the LDS atomics) more than on the 108 MB they move at 1e7 events and 64 x 64 x 512: 28 and
+// 23 us, 51 in all against 108 before with scattered reflecting points (the gather searched
 // and walked a flat range of all runs per element; see also count_dropped).
 
 constexpr int kBinThreads = 256;
-// tp nt <= kBinTileWords (codes fit 16 bits).  At 64 x 64 x 512 with 1e7 events, tiles of
-// 4096 words (512 tiles) measured faster than 8192 words (0.066 to 0.074 ms; the gather's time is
-// its busiest tile's: fewer, larger tiles balance worse) and 2048 words (0.080 ms).
+// tp nt <= kBinTileWords (codes fit 16 bits).  Tiles of 2048 words are slower (63 us against 50
+// for 1e7 events at 64 x 64 x 512, 137 against 50 for 3e6 at 200 x 200 x 512: beyond kBinMaxTiles
+// tiles the atomics).  8192 words take the same 50 us at both and less where a tile holds few
+// pixels or few events (42 -> 35 us for 5e6 at 64 x 64 x 1024, 22 -> 19 for 1e6 at 128 x 128 x 256).
 constexpr int kBinTileWords = 4096;
 constexpr int kBinMaxTiles = 8192;
 constexpr int kBinGatherThreads = 1024;

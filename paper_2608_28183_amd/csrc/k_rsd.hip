@@ -151,21 +151,22 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
 // DATA4: P^ and C are stored in the kernel's four-byte format too (FP16 P^ times 2^e_ph, FP16
 // C at depth d written times 2^e_c[d]), the exponents folded into one final ldexp.
 //
-// FP32 kernels: every FP32 value is the exact sum of three bfloat16 values x0 + x1 + x2 (each
-// the rounded remainder of the previous; 3 x 8 bits), so the product is the sum of the six
-// bfloat16 products of order below 2^-24: a0 b0, a0 b1, a1 b0, a0 b2, a1 b1, a2 b0 (the dropped
-// a1 b2 + a2 b1 are about 2^-26 of it, of random sign).  The kernel's planes come with the
-// plan, the phasors are split in registers; each tap has its own accumulators and the tap
-// weights come last, so the split is paid once.  The sums take 3/8 of the time of FP32 matrix
-// instructions and round less often (once per 16-wide product sum instead of per 2-wide):
-// over the volume within the error of the FP32 instructions against 64 bits.  The split is
-// exact, and no partial product is lost, only well inside FP32's range (below 2^-109 the third
-// part leaves bfloat16's normal numbers, above 2^128 - 2^119 the first rounds to infinity).
-// The plan scales the kernel there (RsdPropArgs::kr_exp), and a wave sees from its sums, at no
-// cost to its steps, whether its phasors were: sums below kSplitMin (with |K_r| up to 2^12 and
-// 2048 terms, phasors of 2^-93 give at most 2^-64 in a lane), above kSplitMax or not a number
-// make it start again with FP32 instructions (propagate_f32).  The largest of the wave counts:
-// what smaller phasors lose is below 2^-30 of it.
+// FP32 kernels (the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", 2019): an FP32 value is the sum of
+// three bfloat16 values x0 + x1 + x2 (each the rounded remainder of the previous; 3 x 8 bits), so
+// a product is the sum of the six bfloat16 products of order below 2^-24: a0 b0, a0 b1, a1 b0,
+// a0 b2, a1 b1, a2 b0 (the dropped a1 b2 + a2 b1 are about 2^-26 of it, of random sign).  The
+// kernel's planes come with the plan, the phasors are split in registers; each tap has its own
+// accumulators and the tap weights come last, so the split is paid once.  The sums take 3/8 of
+// the time of FP32 matrix instructions and round less often (once per 16-wide product sum instead
+// of per 2-wide): over the volume within the error of the FP32 instructions against 64 bits.
+// The split is exact, and no partial product is lost, only well inside FP32's range: below 2^-109
+// the third part leaves bfloat16's normal numbers, above 2^128 - 2^119 the first rounds to
+// infinity.  The plan scales the kernel there (RsdPropArgs::kr_exp), and a wave sees from its
+// sums, at no cost to its steps, whether its phasors were: sums below kSplitMin (with |K_r| up to
+// 2^12 and 2048 terms, phasors of 2^-93 give at most 2^-64 in a lane), above kSplitMax or not a
+// number make it start again with FP32 instructions (propagate_f32).  The largest of the wave
+// counts: what smaller phasors lose is below 2^-30 of it.
 //
 // 128 x 128 x 1024 (129 frequencies, 64 depths; 8.7 GFLOP): FP32 131 -> 76 us, BF16 77 -> 47 us
 // against one 64-pixel chunk per wave with FP32 matrix instructions and scattered operand
