@@ -164,13 +164,13 @@ __global__ __launch_bounds__(256) void rsd_propagate(RsdPropArgs a) {
 // the third part leaves bfloat16's normal numbers, above 2^128 - 2^119 the first rounds to
 // infinity.  The plan scales the kernel there (RsdPropArgs::kr_exp), and a wave sees from its
 // sums, at no cost to its steps, whether its phasors were: sums below kSplitMin (with |K_r| up to
-// 2^12 and 2048 terms, phasors of 2^-93 give at most 2^-64 in a lane), above kSplitMax or not a
-// number make it start again with FP32 instructions (propagate_f32).  The largest of the wave
+// 2^12 and 2048 terms, phasors of 2^-93 give at most 2^-70), above kSplitMax or not a number make
+// it start again with FP32 instructions (propagate_f32).  The largest of the wave
 // counts: what smaller phasors lose is below 2^-30 of it.
 //
 // 128 x 128 x 1024 (129 frequencies, 64 depths; 8.7 GFLOP): FP32 131 -> 76 us, BF16 77 -> 47 us
 // against one 64-pixel chunk per wave with FP32 matrix instructions and scattered operand
-// loads.  The matrix cores are busy 38 % and the vector units (the splits) 32 % of it.
+// loads.  The matrix cores are busy 32 % and the vector units (the splits) 27 % of it.
 template <int KSP>
 struct PropFmt {  // matrix-core format and planes of a kernel's storage
   static constexpr int SP = KSP == SP_F32 ? (int)SP_BF16 : KSP;
@@ -186,7 +186,7 @@ __device__ __forceinline__ mf_u4 prop_im(mf_u4 a) {
                __builtin_amdgcn_alignbit(a[2], a[2], 16), __builtin_amdgcn_alignbit(a[3], a[3], 16)};
 }
 
-constexpr float kSplitMin = 0x1p-64f, kSplitMax = 0x1p100f;
+constexpr float kSplitMin = 0x1p-70f, kSplitMax = 0x1p100f;
 
 // A half chunk's sum with an FP32 kernel on v_mfma_f32_32x32x2f32: a step is one (frequency,
 // tap), lane l holds part l / 32 (re or im) of the tap-weighted phasor of its row and the kernel
@@ -388,12 +388,14 @@ __global__ __launch_bounds__(256, KSP == SP_F32 && DT == 1 ? 3 : 1) void rsd_pro
     }
     if (ns & 1) step(b0, ns - 1);
     if constexpr (NPL == 3) {
-      float m = 0.f;  // the lane's sums in magnitude (NaN, infinite if one is)
+      float m = 0.f;  // the lane's largest sum in magnitude (NaN if one is)
 #pragma unroll
       for (int v = 0; v < 16; ++v)
 #pragma unroll
         for (int q = 0; q < DT; ++q)
-          m += (fabsf(acc[0][q][0][v]) + fabsf(acc[0][q][1][v])) + (fabsf(acc[1][q][0][v]) + fabsf(acc[1][q][1][v]));
+#pragma unroll
+          for (int t = 0; t < 2; ++t)
+            m = __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, fabsf(acc[t][q][0][v])), fabsf(acc[t][q][1][v]));
       bool whole = __ballot(!(m <= kSplitMax)) != 0ull;
       if (!whole && __ballot(m >= kSplitMin) == 0ull)  // (all sums zero: of zeros, or too small for any product)
         whole = __ballot(m > 0.f) != 0ull || !all_zero(a, ws, gh);

@@ -715,9 +715,9 @@ nlos_status nlos_phasor_bin(nlos_ctx* ctx, const nlos_phasor_plan* p, const nlos
   // By pixel tiles (nlos_bin's runs, then each tile's DFT) except for few events on a large
   // plan: the tiles cost their DFT, about 1.3e13 (pixel, bin, frequency) products a second,
   // the events' float atomics 1.34e11 adds a second (97 products each) and 20 us more to
-  // start (2.6e8 products).  Measured: 1e6 events at 64x64x512 with 39 frequencies 39 us by
-  // tiles, 590 by atomics; 3e4 events 22 and 41; 1e4 events at 128x128x1024 with 129
-  // frequencies 190 and 103.
+  // start (2.6e8 products).  Measured (tiles, atomics): 1e6 events at 64x64x512 with 39
+  // frequencies 23 and 588 us, 3e4 events 17 and 40; 1e4 events at 128x128x1024 with 129
+  // frequencies 190 and 102.
   const double products = (double)d.nx * d.ny * d.nt * p->nf;
   const bool tiles = products <= 2.6e8 + 97.0 * (double)n_events * p->nf;
   const size_t wsb = p->tab ? nlos::phasor_workspace_bytes(d.nx * d.ny, d.nt, n_events) : 0;

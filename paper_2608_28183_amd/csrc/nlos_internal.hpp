@@ -186,11 +186,11 @@ inline bool strided_fits(const StridedArgs& a, int es) {
   return plane_span(a.n_in, a.in_line, a.ncols, es) <= kBufMax && plane_span(a.n_out, a.out_line, a.ncols, es) <= kBufMax;
 }
 
-// stream: the f-k passes (FP32 LD_C64 -> ST_C64), as resident blocks where the shape allows
 // Columns per tile of launch_strided (stream as below), launch_strided_mfma (32) and
 // launch_gen_strided for lines of n points: what an item list of theirs is cut into.
 int strided_cols(int n, bool inverse, int sp);
 int gen_strided_cols(int n);
+// stream: the f-k passes (FP32 LD_C64 -> ST_C64), as resident blocks where the shape allows
 hipError_t launch_strided(int n, bool inverse, int ld, int st, const StridedArgs& a, int nplanes,
                           const float2* tw, hipStream_t s, int sp = 0, bool stream = false);
 hipError_t launch_contig(int n, bool inverse, int ld, int st, const ContigArgs& a,
