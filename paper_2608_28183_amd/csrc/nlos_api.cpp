@@ -1346,7 +1346,7 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
     const nlos::RsdInputs in = rsd_inputs(d);
     p->g = nlos::rsd_geometry(in);
     std::vector<double> kre, kim;
-    nlos::rsd_radial_kernel(in, p->g, kre, kim);
+    const double top = nlos::rsd_radial_kernel(in, p->g, kre, kim);
     nlos::RsdChunks ch;
     nlos::rsd_build_chunks(in, p->g, ch);
     const size_t nk = kre.size();
@@ -1361,7 +1361,7 @@ nlos_status nlos_rsd_plan_create(nlos_ctx* ctx, const nlos_rsd_desc* d, nlos_rsd
       const int nrho = (int)(nk / ((size_t)d->n_freq * d->n_depth));
       size_t pairs = 0;
       const std::unique_ptr<uint32_t[]> kr =
-          nlos::rsd_kr_table(kre, kim, nrho, d->n_freq, d->n_depth, fk_sp(d->kernel_prec), &pairs, &p->kr_exp);
+          nlos::rsd_kr_table(kre, kim, top, nrho, d->n_freq, d->n_depth, fk_sp(d->kernel_prec), &pairs, &p->kr_exp);
       p->kr_plane = (long long)nlos::rsd_kr_plane(nrho, d->n_freq, d->n_depth);
       if ((e = nlos::dev_alloc(&p->d_kr, pairs * 4)) != hipSuccess) return cleanup(NLOS_ERR_DEVICE, "K_r", e);
       if ((e = hipMemcpy(p->d_kr, kr.get(), pairs * 4, hipMemcpyHostToDevice)) != hipSuccess)

@@ -98,8 +98,8 @@ RsdGeometry rsd_geometry(const RsdInputs& in) {
   return g;
 }
 
-void rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<double>& re,
-                       std::vector<double>& im) {
+double rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<double>& re,
+                         std::vector<double>& im) {
   const int NR = g.n_r, NP = g.n_rho, NF = in.n_freq, ND = in.n_depth;
   // ring radii, trapezoid weights and ring basis B(r_j, rho_i) = 2 pi r_j J0(2 pi r_j rho_i)
   std::vector<double> r(NR), q(NR, g.dr);
@@ -128,9 +128,11 @@ void rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<do
   });
   re.assign((size_t)NP * FD, 0.0);
   im.assign((size_t)NP * FD, 0.0);
+  std::vector<double> top(NP, 0.0);
   parallel_for(NP, [&](long long i) {
     if ((double)i > g.rho_cut_bin + 1e-9) return;  // beyond the cutoff: zero
     const double* b = &B[(size_t)i * NR];
+    double t = 0.0;
     for (size_t fd = 0; fd < FD; ++fd) {
       const double* ar = &Are[fd * NR];
       const double* ai = &Aim[fd * NR];
@@ -139,10 +141,14 @@ void rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<do
         sr += b[j] * ar[j];
         si += b[j] * ai[j];
       }
-      re[(size_t)i * FD + fd] = sr * Pre[fd] - si * Pim[fd];
-      im[(size_t)i * FD + fd] = sr * Pim[fd] + si * Pre[fd];
+      const double kr = sr * Pre[fd] - si * Pim[fd], ki = sr * Pim[fd] + si * Pre[fd];
+      re[(size_t)i * FD + fd] = kr;
+      im[(size_t)i * FD + fd] = ki;
+      t = std::max(t, std::max(std::fabs(kr), std::fabs(ki)));
     }
+    top[i] = t;
   });
+  return *std::max_element(top.begin(), top.end());
 }
 
 size_t rsd_kr_plane(int n_rho, int n_freq, int n_depth) {
@@ -162,8 +168,8 @@ inline uint32_t take_bf16(float* x) {
 }
 }  // namespace
 
-std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const std::vector<double>& im, int n_rho,
-                                         int n_freq, int n_depth, int sp, size_t* pairs, int* exp) {
+std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const std::vector<double>& im, double top,
+                                         int n_rho, int n_freq, int n_depth, int sp, size_t* pairs, int* exp) {
   const int fl = sp == SP_F32 ? 4 : 2, ng = 8 / fl * ((n_freq + 7) / 8);
   const size_t plane = rsd_kr_plane(n_rho, n_freq, n_depth);
   *pairs = plane * (sp == SP_F32 ? 3 : 1);
@@ -172,15 +178,7 @@ std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const st
   uint32_t* const o = out.get();
   *exp = 0;
   if (sp == SP_F32) {
-    std::vector<double> top(n_rho, 0.0);
-    const size_t row = (size_t)n_freq * n_depth;
-    parallel_for(n_rho, [&, row](long long i) {
-      double t = 0.0;
-      for (size_t k = i * row; k < (i + 1) * row; ++k) t = std::max(t, std::max(std::fabs(re[k]), std::fabs(im[k])));
-      top[i] = t;
-    });
-    const double m = *std::max_element(top.begin(), top.end());
-    if (m > 0.0 && std::isfinite(m) && (m < 0x1p-12 || m > 0x1p12)) (void)std::frexp(m, exp);
+    if (top > 0.0 && std::isfinite(top) && (top < 0x1p-12 || top > 0x1p12)) (void)std::frexp(top, exp);
     *exp = std::min(std::max(*exp, -126), 126);  // (2^exp an FP32 number)
   }
   const double scale = std::ldexp(1.0, -*exp);

@@ -33,20 +33,20 @@ struct RsdGeometry {
 };
 
 RsdGeometry rsd_geometry(const RsdInputs& in);
-// K_r[i][f][d] (re, im) for i < n_rho, f < n_freq, d < n_depth.
-void rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<double>& re,
-                       std::vector<double>& im);
+// K_r[i][f][d] (re, im) for i < n_rho, f < n_freq, d < n_depth; returns the largest component.
+double rsd_radial_kernel(const RsdInputs& in, const RsdGeometry& g, std::vector<double>& re,
+                         std::vector<double>& im);
 // K_r as the propagation reads it (RsdPropArgs::Kr), sp its storage (SP_*): planes of
 // rsd_kr_plane four-byte (re, im) pairs, re in the lower half, frequencies zero-padded to a
 // multiple of 8.  FP16 / BF16: one plane [Nrho][f / 2][Nd][f % 2], K_r rounded once; FP32: three
 // bfloat16 planes [Nrho][f / 4][Nd][f % 4], each the rounded remainder of those before it, that
-// add up to K_r 2^-exp in FP32.  *exp is 0 where the largest |K_r| lies in [2^-12, 2^12], beyond
-// (tiny or huge walls) what brings it to [1/2, 1), at most 126 in magnitude, since parts of
-// much smaller or larger values leave bfloat16's range.  Returns the pairs of all planes,
-// *pairs of them.
+// add up to K_r 2^-exp in FP32.  *exp is 0 where top, the largest component, lies in
+// [2^-12, 2^12], beyond (tiny or huge walls) what brings it to [1/2, 1), at most 126 in
+// magnitude, since parts of much smaller or larger values leave bfloat16's range.  Returns the
+// pairs of all planes, *pairs of them.
 size_t rsd_kr_plane(int n_rho, int n_freq, int n_depth);
-std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const std::vector<double>& im, int n_rho,
-                                         int n_freq, int n_depth, int sp, size_t* pairs, int* exp);
+std::unique_ptr<uint32_t[]> rsd_kr_table(const std::vector<double>& re, const std::vector<double>& im, double top,
+                                         int n_rho, int n_freq, int n_depth, int sp, size_t* pairs, int* exp);
 // rho~(u, v) in bin units on the My x Mx grid, signed FFT indices (FP64).
 void rsd_radius_map(const RsdInputs& in, const RsdGeometry& g, std::vector<double>& rho);
 
